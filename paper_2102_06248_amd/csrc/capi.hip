@@ -138,6 +138,44 @@ PArrays<T> parr_off(Species& s, int which, int64_t off) {
 
 size_t field_size(const fepic_ctx* c) { return c->opt.precision == FEPIC_ALL_FP64 ? 8 : 4; }
 
+// The row blocks of the edge matrices' columns (slice pointers and columns on the device),
+// built there: counts, then lists and indices.  On failure c->bc is left as it was.
+int build_blocks(fepic_ctx* c, const SellMatrix& mat, const int64_t* sp, const int32_t* col) {
+    BlockCols g;
+    g.n_slices = mat.n_slices;
+    g.nb = (mat.n_rows + kBlockRows - 1) / kBlockRows;
+    int32_t* cnt = dalloc<int32_t>(c, g.nb);
+    if (!cnt) return fail(c, FEPIC_E_OOM, "device allocation failed");
+    g.cnt = cnt;
+    int32_t* halo = nullptr;
+    uint16_t* lcol = nullptr;
+    auto drop = [&](int rc) {
+        for (void* p : {(void*)cnt, (void*)halo, (void*)lcol}) dfree(c, p);
+        return rc;
+    };
+    std::vector<int32_t> h(g.nb);
+    launch_block_count(c->stream, g, sp, col, cnt);
+    hipError_t e = hipMemcpyAsync(h.data(), cnt, sizeof(int32_t) * g.nb, hipMemcpyDeviceToHost, c->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+    if (e != hipSuccess) return drop(hip_fail(c, e, "row block counts"));
+    int most = 1;
+    for (int32_t n : h) most = std::max(most, n);
+    g.stride = (most + kBlockRows - 1) / kBlockRows * kBlockRows;
+    halo = dalloc<int32_t>(c, g.nb * g.stride);
+    lcol = dalloc<uint16_t>(c, mat.slice_ptr.back());
+    if (!halo || !lcol) return drop(fail(c, FEPIC_E_OOM, "device allocation failed"));
+    launch_block_fill(c->stream, g, sp, col, halo, lcol);
+    e = hipGetLastError();
+    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+    if (e != hipSuccess) return drop(hip_fail(c, e, "row block columns"));
+    g.halo = halo;
+    g.lcol = lcol;
+    for (const void* p : {(const void*)c->bc.cnt, (const void*)c->bc.halo, (const void*)c->bc.lcol})
+        dfree(c, const_cast<void*>(p));
+    c->bc = g;
+    return FEPIC_OK;
+}
+
 size_t array_bytes(const fepic_ctx* c, int a, int64_t n) {
     if (a == 0) return 4 * (size_t)n;
     if (a == 7) return 8 * (size_t)n;
@@ -620,7 +658,8 @@ int ensure_operator_f32(fepic_ctx* c) {
         for (float2* p : c->d_zp32) HIPCHK(c, hipMemsetAsync(p, 0, sizeof(float2) * ne, c->stream));
     }
     if (!c->A32_valid) {
-        launch_operator_f32(c->stream, nnz, c->d_A, c->d_A32, ne, c->d_dinv, c->d_dinv32, c->aux);
+        launch_operator_f32(c->stream, c->mesh.mat.n_slices, c->d_sp, c->d_A, c->d_A32, ne, c->d_dinv, c->d_dinv32,
+                            c->aux);
         c->A32_valid = true;
     }
     return FEPIC_OK;
@@ -909,11 +948,11 @@ int field_phase(fepic_ctx* c, double dt, double beta, double gamma) {
             // the pass ends when its own residual has fallen by mixed_inner_tol, or below half
             // the outer target
             const double tol_in = std::max(c->opt.mixed_inner_tol, 0.5 * std::sqrt(tol2 / h.rr_true));
-            launch_pcg_init_f32(c->stream, ne, c->d_sp, c->d_col, c->d_A32, c->d_dinv32, c->d_rt, c->d_x32, c->aux,
-                                ZP32[0], c->d_rq32, c->d_partial, c->d_sc, tol_in);
+            launch_pcg_init_f32(c->stream, ne, c->d_sp, c->d_col, c->d_dinv32, c->d_rt, c->d_x32, c->aux, ZP32[0],
+                                c->d_rq32, c->d_partial, c->d_sc, tol_in);
             const int first = c->last_pass_iters[pass] > 0 ? std::max(batch, c->last_pass_iters[pass] + 2) : batch;
             rc = iterate(first, [&](int i) {
-                launch_pcg_iter_f32(c->stream, i, ne, c->d_sp, c->d_col, c->d_A32, c->d_dinv32, c->d_x32, c->aux,
+                launch_pcg_iter_f32(c->stream, i, ne, c->d_sp, c->d_col, c->bc, c->d_A32, c->d_dinv32, c->d_x32, c->aux,
                                     ZP32, c->d_rq32, c->d_partial, c->d_sc);
             });
             if (rc != FEPIC_OK) return rc;
@@ -946,7 +985,7 @@ int field_phase(fepic_ctx* c, double dt, double beta, double gamma) {
             const int first = (restart == 0 && c->last_cg_iters > 0) ? std::max(batch, c->last_cg_iters + 2) : batch;
             int rc = iterate(first, [&](int i) {
                 if (aux)
-                    launch_pcg_iter(c->stream, i, ne, c->d_sp, c->d_col, c->d_A, c->d_dinv, c->d_x, c->aux, ZP,
+                    launch_pcg_iter(c->stream, i, ne, c->d_sp, c->d_col, c->bc, c->d_A, c->d_dinv, c->d_x, c->aux, ZP,
                                     c->d_rq, c->d_partial, c->d_sc);
                 else
                     launch_cg_iter(c->stream, i, ne, c->d_sp, c->d_col, c->d_A, c->d_dinv, c->d_x, V, c->d_partial,
@@ -1583,8 +1622,8 @@ int fepic_set_absorbing_faces(fepic_ctx* c, int64_t n, const int32_t* faces) {
         const int64_t nnz = trial.mat.slice_ptr.back();
         if ((rc = upload(c, &sp, trial.mat.slice_ptr)) || (rc = upload(c, &col, trial.mat.col)) ||
             (rc = upload(c, &M, trial.mat.M)) || (rc = upload(c, &S, trial.mat.S)) || (rc = upload(c, &K, trial.mat.K)) ||
-            (rc = upload(c, &fx, fixed)) || !(A = dalloc<double>(c, nnz))) {
-            for (void* p : {(void*)sp, (void*)col, (void*)M, (void*)S, (void*)K, (void*)fx}) dfree(c, p);
+            (rc = upload(c, &fx, fixed)) || !(A = dalloc<double>(c, nnz)) || (rc = build_blocks(c, trial.mat, sp, col))) {
+            for (void* p : {(void*)sp, (void*)col, (void*)M, (void*)S, (void*)K, (void*)fx, (void*)A}) dfree(c, p);
             return rc ? rc : fail(c, FEPIC_E_OOM, "device allocation failed");
         }
         for (void* p : {(void*)c->d_sp, (void*)c->d_col, (void*)c->d_M, (void*)c->d_S, (void*)c->d_A,
@@ -1651,6 +1690,7 @@ int fepic_upload_mesh(fepic_ctx* c, int64_t n_nodes, const double* xyz, int64_t 
         (rc = upload(c, &c->d_S, m.mat.S)) || (rc = upload(c, &c->d_cell_start, m.cell_start)) ||
         (rc = upload(c, &c->d_cell_tets, m.cell_tets)) || (rc = upload(c, &c->d_int_edges, m.dev_int_edges)))
         return rc;
+    if ((rc = build_blocks(c, m.mat, c->d_sp, c->d_col))) return rc;
     std::vector<double> g3 = {m.grid_lo[0], m.grid_lo[1], m.grid_lo[2], m.grid_inv_h[0], m.grid_inv_h[1], m.grid_inv_h[2]};
     std::vector<int32_t> gn = {m.grid_n[0], m.grid_n[1], m.grid_n[2]};
     if ((rc = upload(c, &c->d_grid, g3)) || (rc = upload(c, &c->d_grid_n, gn))) return rc;

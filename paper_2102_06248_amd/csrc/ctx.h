@@ -91,6 +91,7 @@ struct fepic_ctx {
     void* d_blk = nullptr;
     int64_t* d_sp = nullptr;
     int32_t* d_col = nullptr;
+    fepic::BlockCols bc;   // the same columns by row block
     double *d_M = nullptr, *d_S = nullptr, *d_A = nullptr, *d_dinv = nullptr;
     int32_t *d_cell_start = nullptr, *d_cell_tets = nullptr, *d_grid_n = nullptr;
     double* d_grid = nullptr;  // lo[3], inv_h[3]

@@ -195,6 +195,27 @@ struct DiagAcc {
     unsigned int pad;
 };
 
+// The columns of the edge matrices by row block: blocks of kBlockRows consecutive rows
+// (one workgroup each), every stored slot's column as a 16-bit index into the block's own
+// rows followed by its halo, the sorted list of the other columns its rows store.  A
+// product stages those few values in LDS (a block has about 640 halo columns on the
+// workloads' meshes, against 8,300 stored slots) and gathers from there.  512 rows are the
+// window in which the host groups rows by length: blocks of 256 share most of their halo
+// with their window's other half and were slower on every mesh (the beam's FP32 product
+// 9.8 against 7.9 us).  lcol has the
+// slots of SELL-64 in pairs: column pair j of a slice of width w at 128 j + 2 lane (+ 1),
+// an odd last column at 64 (w - 1) + lane, so that a lane loads two indices at once.
+struct BlockCols {
+    int64_t nb = 0, n_slices = 0;
+    int stride = 0;                  // room per block in halo, a multiple of kBlockRows
+    const int32_t* halo = nullptr;   // [nb][stride], padded with the block's first row
+    const int32_t* cnt = nullptr;    // [nb] halo columns; -1: more than kHaloMax, the block's
+                                     // rows gather from memory by their 32-bit columns
+    const uint16_t* lcol = nullptr;  // [slots]
+};
+constexpr int kBlockRows = 512;
+constexpr int kHaloMax = 4096;
+
 struct SellMatrix {
     int64_t n_rows = 0;
     int64_t n_slices = 0;
@@ -287,6 +308,10 @@ void launch_cg_iter(hipStream_t s, int i, int64_t n_rows, const int64_t* slice_p
                     const double* A, const double* dinv, double* x, CgVec* const v[2], double* partial,
                     CgScalars* sc, bool det = false);
 void launch_cg_rr0(hipStream_t s, int64_t n_rows, double* partial, CgScalars* sc);
+// Halo sizes of the row blocks into cnt (count), then halo lists and 16-bit columns (fill).
+void launch_block_count(hipStream_t s, const BlockCols& g, const int64_t* slice_ptr, const int32_t* col, int32_t* cnt);
+void launch_block_fill(hipStream_t s, const BlockCols& g, const int64_t* slice_ptr, const int32_t* col,
+                       int32_t* halo, uint16_t* lcol);
 // PCG with the nodal auxiliary-space preconditioner: per row z = B r with the previous
 // search direction p (zp, double buffered), and r and q = A p as two arrays of n_rows
 // doubles in rq (r first; each written whole by one kernel).
@@ -296,16 +321,17 @@ void launch_pcg_init(hipStream_t s, int64_t n_rows, const int64_t* slice_ptr, co
                      const double* dinv, const double* b, const double* x, const AuxSpace& g, double2* zp0,
                      double2* rq, double* partial, CgScalars* sc, double tol);
 void launch_pcg_iter(hipStream_t s, int i, int64_t n_rows, const int64_t* slice_ptr, const int32_t* col,
-                     const double* A, const double* dinv, double* x, const AuxSpace& g, double2* const zp[2],
-                     double2* rq, double* partial, CgScalars* sc);
+                     const BlockCols& bc, const double* A, const double* dinv, double* x, const AuxSpace& g,
+                     double2* const zp[2], double2* rq, double* partial, CgScalars* sc);
 void launch_pcg_init_f32(hipStream_t s, int64_t n_rows, const int64_t* slice_ptr, const int32_t* col,
-                         const float* A32, const float* dinv32, const double* r_true, float* d, const AuxSpace& g,
-                         float2* zp0, float* rq, double* partial, CgScalars* sc, double tol);
+                         const float* dinv32, const double* r_true, float* d, const AuxSpace& g, float2* zp0, float* rq,
+                         double* partial, CgScalars* sc, double tol);
+// A32: the FP32 values in the pair layout of BlockCols::lcol.
 void launch_pcg_iter_f32(hipStream_t s, int i, int64_t n_rows, const int64_t* slice_ptr, const int32_t* col,
-                         const float* A32, const float* dinv32, float* d, const AuxSpace& g, float2* const zp[2],
-                         float* rq, double* partial, CgScalars* sc);
-void launch_operator_f32(hipStream_t s, int64_t nnz, const double* A, float* A32, int64_t n_rows, const double* dinv,
-                         float* dinv32, const AuxSpace& g);
+                         const BlockCols& bc, const float* A32, const float* dinv32, float* d, const AuxSpace& g,
+                         float2* const zp[2], float* rq, double* partial, CgScalars* sc);
+void launch_operator_f32(hipStream_t s, int64_t n_slices, const int64_t* slice_ptr, const double* A, float* A32,
+                         int64_t n_rows, const double* dinv, float* dinv32, const AuxSpace& g);
 void launch_add_f32(hipStream_t s, double* x, const float* d, int64_t n);
 void launch_pcg_rhs_norm(hipStream_t s, int64_t n_rows, double* partial, CgScalars* sc, double tol);
 void launch_pcg_rr0(hipStream_t s, double* partial, CgScalars* sc);

@@ -774,6 +774,244 @@ __device__ __forceinline__ typename Vec<S>::t3 edge_vec_t(const AuxSpace& g, int
     return v;
 }
 
+// Sum over the wave by DPP moves (row shifts, then the rows' totals carried across), the
+// same bits in every lane: VALU moves, where shuffles would be LDS permutes.
+template <int kCtrl, int kRowMask>
+__device__ __forceinline__ double dpp_add(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), kCtrl, kRowMask, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), kCtrl, kRowMask, 0xf, true);
+    return v + __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double wave_total(double v) {
+    v = dpp_add<0x111, 0xf>(v);   // row_shr:1
+    v = dpp_add<0x112, 0xf>(v);
+    v = dpp_add<0x114, 0xf>(v);
+    v = dpp_add<0x118, 0xf>(v);
+    v = dpp_add<0x142, 0xa>(v);   // row_bcast:15
+    v = dpp_add<0x143, 0xc>(v);   // row_bcast:31
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 63),
+                            __builtin_amdgcn_readlane(__double2loint(v), 63));
+}
+
+// A reduction's kCgSlots slots, one per lane: every wave loads and sums them itself (the
+// same bits everywhere), which costs a few cache hits and no barrier.
+template <int NV>
+__device__ __forceinline__ void slot_load_wave(const double* buf, double t[NV]) {
+    static_assert(kCgSlots == 64, "one slot per lane");
+#pragma unroll
+    for (int j = 0; j < NV; ++j) t[j] = buf[j * kCgSlots + (threadIdx.x & 63)];
+}
+
+// Workgroup totals of v into the workgroup's slots (R threads; one barrier).
+template <int NV, int R>
+__device__ __forceinline__ void block_slot_add(const double v[NV], double* buf) {
+    __shared__ double s[NV][R / 64];
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+        const double w = wave_total(v[j]);
+        if ((threadIdx.x & 63) == 0) s[j][threadIdx.x >> 6] = w;
+    }
+    __syncthreads();
+    if (threadIdx.x < NV) {
+        double a = 0.0;
+#pragma unroll
+        for (int q = 0; q < R / 64; ++q) a += s[threadIdx.x][q];
+        unsafeAtomicAdd(buf + threadIdx.x * kCgSlots + (blockIdx.x & (kCgSlots - 1)), a);
+    }
+}
+
+// One row's slice of the matrix, its first 2 kPairs slots in registers (issued before the
+// staged vector is known): all of a row on the workloads' meshes (at most 19 slots).
+template <typename S>
+struct BlockRow {
+    static constexpr int kPairs = 10;
+    S a[2 * kPairs];
+    uint32_t c[kPairs];
+    int64_t k0;   // the lane's first slot
+    int w;        // slots per row of the slice (0 past the matrix)
+
+    // slots 2 j and 2 j + 1 (the second zero past the width)
+    __device__ __forceinline__ void pair(const BlockCols& bc, const S* __restrict__ A, int j, S& a0, S& a1,
+                                         uint32_t& cc) const {
+        const int lane = threadIdx.x & 63;
+        if (2 * j + 1 < w) {
+            const int64_t k = k0 + 128 * j + 2 * lane;
+            cc = *reinterpret_cast<const uint32_t*>(bc.lcol + k);
+            if constexpr (sizeof(S) == 4) {   // the FP32 copy has the pair layout
+                const float2 v = *reinterpret_cast<const float2*>(A + k);
+                a0 = v.x;
+                a1 = v.y;
+            } else {
+                a0 = A[k0 + 128 * j + lane];
+                a1 = A[k0 + 128 * j + 64 + lane];
+            }
+        } else {
+            cc = bc.lcol[k0 + 128 * j + lane];
+            a0 = A[k0 + 128 * j + lane];
+            a1 = S(0);
+        }
+    }
+    __device__ __forceinline__ void load(const BlockCols& bc, int64_t slice, const int64_t* __restrict__ sp,
+                                         const S* __restrict__ A) {
+        const int sl = __builtin_amdgcn_readfirstlane((int)slice);   // wave-uniform: scalar loads
+        k0 = 0;
+        w = 0;
+        if (sl < bc.n_slices) {
+            k0 = sp[sl];
+            w = (int)((sp[sl + 1] - k0) >> 6);
+        }
+#pragma unroll
+        for (int j = 0; j < kPairs; ++j)
+            if (2 * j < w) pair(bc, A, j, a[2 * j], a[2 * j + 1], c[j]);
+    }
+    // sum over the row of A f(local column)
+    template <typename F>
+    __device__ __forceinline__ S dot(const BlockCols& bc, const S* __restrict__ A, F f) const {
+        S s0 = S(0), s1 = S(0);
+#pragma unroll
+        for (int j = 0; j < kPairs; ++j)
+            if (2 * j < w) {
+                s0 += a[2 * j] * f(c[j] & 0xffffu);
+                s1 += a[2 * j + 1] * f(c[j] >> 16);
+            }
+        for (int j = kPairs; 2 * j < w; ++j) {
+            S a0, a1;
+            uint32_t cc;
+            pair(bc, A, j, a0, a1, cc);
+            s0 += a0 * f(cc & 0xffffu);
+            s1 += a1 * f(cc >> 16);
+        }
+        return s0 + s1;
+    }
+    // the same by the 32-bit columns (a block whose halo exceeds kHaloMax)
+    template <typename F>
+    __device__ __forceinline__ S dot_wide(const int32_t* __restrict__ col, const S* __restrict__ A, F f) const {
+        const int lane = threadIdx.x & 63;
+        S s = S(0);
+#pragma unroll 4
+        for (int k = 0; k < w; ++k) {
+            int64_t ka = k0 + 64 * k + lane;
+            if (sizeof(S) == 4 && (k | 1) < w) ka = k0 + 128 * (k >> 1) + 2 * lane + (k & 1);
+            s += A[ka] * f(col[k0 + 64 * k + lane]);
+        }
+        return s;
+    }
+};
+
+// Halo columns a thread stages from registers (1,024 per block; more in a loop).
+constexpr int kHaloRegs = 1024 / kBlockRows;
+
+__device__ __forceinline__ void halo_ids(const BlockCols& bc, int64_t b, int h[kHaloRegs]) {
+#pragma unroll
+    for (int k = 0; k < kHaloRegs; ++k)
+        if (k * kBlockRows < bc.stride) h[k] = bc.halo[b * bc.stride + k * kBlockRows + threadIdx.x];
+}
+
+// One workgroup per row block.  The halo (distinct columns outside the block) is found by
+// inserting the block's columns into an LDS hash table, then sorted, so that its gathers run
+// through memory in order; with kFill the lists and each slot's 16-bit index (own rows
+// first, then the halo position, by binary search) are written, otherwise the counts only.
+// A block of more than kHaloMax halo columns gets cnt -1 and no indices.  Every loop is
+// bounded: the table has twice kHaloMax slots, inserts stop once kHaloMax is passed (at most
+// one more per thread is under way), and a probe visits each slot once.
+template <bool kFill>
+__global__ __launch_bounds__(kBlock) void k_block_cols(BlockCols g, const int64_t* __restrict__ sp,
+                                                        const int32_t* __restrict__ col, int32_t* __restrict__ cnt,
+                                                        int32_t* __restrict__ halo, uint16_t* __restrict__ lcol) {
+    constexpr int kTable = 2 * kHaloMax;
+    __shared__ int s_key[kTable];
+    __shared__ int s_list[kHaloMax];
+    __shared__ int s_n, s_m;
+    const int64_t b = blockIdx.x, r0 = b * kBlockRows, r1 = r0 + kBlockRows;
+    const int64_t sl0 = r0 >> 6, sl1 = min((int64_t)(r1 >> 6), g.n_slices);
+    const int64_t k0 = sp[sl0], k1 = sp[sl1];
+    for (int k = threadIdx.x; k < kTable; k += kBlock) s_key[k] = -1;
+    if (threadIdx.x == 0) s_n = s_m = 0;
+    __syncthreads();
+    for (int64_t k = k0 + threadIdx.x; k < k1; k += kBlock) {
+        const int c = col[k];
+        if (c >= r0 && c < r1) continue;
+        unsigned h = ((unsigned)c * 2654435761u) >> (32 - 13);
+        static_assert(kTable == 1 << 13, "hash width");
+        for (int p = 0; p < kTable; ++p) {
+            const int old = __hip_atomic_load(s_key + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (old == c) break;
+            if (old == -1) {
+                if (__hip_atomic_load(&s_n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) > kHaloMax) break;
+                const int was = atomicCAS(s_key + h, -1, c);
+                if (was == -1) atomicAdd(&s_n, 1);
+                if (was == -1 || was == c) break;
+            }
+            h = (h + 1) & (kTable - 1);
+        }
+    }
+    __syncthreads();
+    const int n = s_n;
+    if (!kFill) {
+        if (threadIdx.x == 0) cnt[b] = n > kHaloMax ? -1 : n;
+        return;
+    }
+    if (n > kHaloMax) {
+        for (int k = threadIdx.x; k < g.stride; k += kBlock) halo[b * g.stride + k] = (int32_t)r0;
+        return;
+    }
+    int n2 = 1;
+    while (n2 < n) n2 <<= 1;
+    for (int k = threadIdx.x; k < kTable; k += kBlock)
+        if (s_key[k] >= 0) s_list[atomicAdd(&s_m, 1)] = s_key[k];
+    __syncthreads();
+    for (int k = n + threadIdx.x; k < n2; k += kBlock) s_list[k] = INT32_MAX;
+    __syncthreads();
+    for (int sz = 2; sz <= n2; sz <<= 1)   // bitonic sort
+        for (int d = sz >> 1; d > 0; d >>= 1) {
+            for (int k = threadIdx.x; k < n2 / 2; k += kBlock) {
+                const int i = 2 * k - (k & (d - 1)), j = i + d;
+                const int x = s_list[i], y = s_list[j];
+                if ((x > y) == ((i & sz) == 0)) {
+                    s_list[i] = y;
+                    s_list[j] = x;
+                }
+            }
+            __syncthreads();
+        }
+    for (int k = threadIdx.x; k < g.stride; k += kBlock) halo[b * g.stride + k] = k < n ? s_list[k] : (int32_t)r0;
+    for (int64_t sl = sl0; sl < sl1; ++sl) {
+        const int64_t base = sp[sl];
+        const int w = (int)((sp[sl + 1] - base) >> 6);
+        for (int e = threadIdx.x; e < 64 * w; e += kBlock) {
+            const int k = e >> 6, lane = e & 63, c = col[base + e];
+            int idx;
+            if (c >= r0 && c < r1) {
+                idx = (int)(c - r0);
+            } else {
+                int lo = 0, hi = n - 1;
+                while (lo < hi) {
+                    const int mid = (lo + hi) >> 1;
+                    if (s_list[mid] < c) lo = mid + 1;
+                    else hi = mid;
+                }
+                idx = kBlockRows + lo;
+            }
+            lcol[base + ((k | 1) < w ? 128 * (k >> 1) + 2 * lane + (k & 1) : e)] = (uint16_t)idx;
+        }
+    }
+}
+
+// The FP32 values of a SELL-64 matrix in the pair layout (one wave per slice).
+__global__ __launch_bounds__(kBlock) void k_pack_f32(int64_t n_slices, const int64_t* __restrict__ sp,
+                                                      const double* __restrict__ A, float* __restrict__ A32) {
+    const int64_t sl = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+    if (sl >= n_slices) return;
+    const int lane = threadIdx.x & 63;
+    const int64_t k0 = sp[sl];
+    const int w = (int)((sp[sl + 1] - k0) >> 6);
+    int k = 0;
+    for (; k + 1 < w; k += 2)
+        *reinterpret_cast<float2*>(A32 + k0 + 64 * k + 2 * lane) =
+            make_float2((float)A[k0 + 64 * k + lane], (float)A[k0 + 64 * k + 64 + lane]);
+    if (k < w) A32[k0 + 64 * k + lane] = (float)A[k0 + 64 * k + lane];
+}
+
 // ||b||^2 from the partials of the kernel that summed it (the right-hand side's, or the
 // true residual's for an inner solve); r = b - A x, or with zero_x r = b and x = 0 (the
 // inner solves start from zero); q = 0; clears the four reduction buffers and the far
@@ -817,75 +1055,47 @@ __global__ __launch_bounds__(kBlock) void k_pcg_init(int64_t n_rows, RowGrid rg,
     }
 }
 
-// Row j of A p split by the iteration's scalar: sum_k A_jk z_k and sum_k A_jk p_k over
-// the stored entries, so the gathers are issued before beta is known; own (z, p).
-template <typename S>
-struct QPart {
-    S sZ, sP;
-    typename Vec<S>::t2 own;
-};
-
-template <typename S>
-__device__ __forceinline__ void q_part(QPart<S>& P, const int64_t* __restrict__ sp, const int32_t* __restrict__ col,
-                                       const S* __restrict__ A, const typename Vec<S>::t2* __restrict__ ZP,
-                                       int64_t row, bool real) {
-    const int64_t sl = row >> 6;
-    const int lane = (int)(row & 63);
-    const int64_t k1 = sp[sl + 1];
-    int64_t k = sp[sl] + lane;
-    P.own = ZP[real ? row : 0];
-    S z0 = S(0), p0 = S(0), z1 = S(0), p1 = S(0);
-    for (; k + (kUnroll - 1) * 64 < k1; k += kUnroll * 64) {
-        int c[kUnroll];
-        S a[kUnroll];
-#pragma unroll
-        for (int q = 0; q < kUnroll; ++q) {
-            c[q] = col[k + 64 * q];
-            a[q] = A[k + 64 * q];
-        }
-        typename Vec<S>::t2 zp[kUnroll];
-#pragma unroll
-        for (int q = 0; q < kUnroll; ++q) zp[q] = ZP[c[q]];
-#pragma unroll
-        for (int q = 0; q < kUnroll; q += 2) {
-            z0 += a[q] * zp[q].x;
-            p0 += a[q] * zp[q].y;
-            z1 += a[q + 1] * zp[q + 1].x;
-            p1 += a[q + 1] * zp[q + 1].y;
-        }
-    }
-    for (; k < k1; k += 64) {
-        const S a = A[k];
-        const typename Vec<S>::t2 zp = ZP[col[k]];
-        z0 += a * zp.x;
-        p0 += a * zp.y;
-    }
-    P.sZ = z0 + z1;
-    P.sP = p0 + p1;
-}
-
 // The convergence test of iterate i (its (r, r) from reduction 2i - 1), beta, the new
 // direction p = z + beta p and q = A p (only q is stored: the update kernel forms the same
 // p from the same operands); (p, q) into reduction 2i.
+// One workgroup per row block.  Bound by HBM on the large meshes, by the chain of dependent
+// loads on the small ones; both were set by the gathers (per stored slot a 32-bit column,
+// then a (z, p) pair from L2, six slots at a time: up to twelve round trips in a row).
+// Staging p of the block's own and halo columns in LDS leaves one round trip (list, pairs)
+// beside the matrix stream, 6 instead of 8 bytes per FP32 slot, and one LDS read per slot.
+// FP32: 998k tets 31.2 -> 23.6 us (about 150 MB: 6.4 TB/s), 384k tets 16.6 -> 12.4, beam
+// 11.8 -> 7.9; FP64: 197k tets 13.8 -> 10.8, 73k 7.7 -> 6.1, 41k 6.4 -> 5.8.
 template <typename S>
-__global__ __launch_bounds__(kBlock) void k_pcg_q(int64_t n_rows, RowGrid rg, int i, const int64_t* __restrict__ sp,
-                                                   const int32_t* __restrict__ col, const S* __restrict__ A,
-                                                   const typename Vec<S>::t2* __restrict__ ZP, S* __restrict__ Q,
-                                                   double* __restrict__ cg_slots, CgScalars* sc, AuxSpace aux) {
+__global__ __launch_bounds__(kBlockRows) void k_pcg_q(int64_t n_rows, RowGrid rg, int i, const int64_t* __restrict__ sp,
+                                             const int32_t* __restrict__ col, BlockCols bc, const S* __restrict__ A,
+                                             const typename Vec<S>::t2* __restrict__ ZP, S* __restrict__ Q,
+                                             double* __restrict__ cg_slots, CgScalars* sc, AuxSpace aux) {
+    using V2 = typename Vec<S>::t2;
+    extern __shared__ double lds_raw[];
+    S* s_p = reinterpret_cast<S*>(lds_raw);
+    constexpr int R = kBlockRows, H = kHaloRegs;
     const int conv = sc->converged;
+    const double tol2_bb = sc->tol2_bb, bb = sc->bb, gam_old = sc->gam[(i + 1) & 1];
     double t[2];
-    slot_load<2>(red_buf(cg_slots, 2 * i - 1), t);
-    int64_t lb = rg_first(rg);
-    const int64_t le = rg_end(rg);
-    QPart<S> P;
-    int64_t row = lb * kBlock + threadIdx.x;
-    bool active = lb < le && ((row >> 6) << 6) < n_rows;
-    if (active) q_part<S>(P, sp, col, A, ZP, row, row < n_rows);
+    slot_load_wave<2>(red_buf(cg_slots, 2 * i - 1), t);
+    const int64_t b = rg_first(rg);
+    if (b >= rg_end(rg)) return;   // the whole workgroup
+    const int64_t row = b * R + threadIdx.x;
+    // in flight together: the row's values and indices, its own pair, and the halo's
+    BlockRow<S> P;
+    P.load(bc, b * (R / 64) + (threadIdx.x >> 6), sp, A);
+    const V2 own = ZP[row < n_rows ? row : 0];
+    const int cnt = bc.cnt[b];
+    int h[H];
+    halo_ids(bc, b, h);
+    V2 zp[H];
+#pragma unroll
+    for (int k = 0; k < H; ++k)
+        if (k * R < bc.stride) zp[k] = ZP[h[k]];
     if (conv) return;
-    block_sum_all<2>(t);
-    const double g = t[0], rr = t[1];
-    const bool done = !(rr > sc->tol2_bb) || sc->bb == 0.0;
-    const double beta = (i == 0) ? 0.0 : g / sc->gam[(i - 1) & 1];
+    const double g = wave_total(t[0]), rr = wave_total(t[1]);
+    const bool done = !(rr > tol2_bb) || bb == 0.0;
+    const double beta = (i == 0) ? 0.0 : g / gam_old;
     const bool bad = !done && !(g > 0.0 && g < INFINITY && beta >= 0.0 && beta < INFINITY);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         sc->gam[i & 1] = g;
@@ -898,21 +1108,31 @@ __global__ __launch_bounds__(kBlock) void k_pcg_q(int64_t n_rows, RowGrid rg, in
     if (done || bad) return;
     if (blockIdx.x == 0) clear_far(aux);   // read by the previous update, added to by the next node pass
     const S bs = (S)beta;
-    double v[1] = {0.0};
-    while (lb < le) {
-        if (active && row < n_rows) {
-            const S p = P.own.x + bs * P.own.y;
-            const S q = P.sZ + bs * P.sP;
-            Q[row] = q;
-            v[0] += (double)p * (double)q;
-        }
-        lb += rg.g;
-        row = lb * kBlock + threadIdx.x;
-        active = lb < le && ((row >> 6) << 6) < n_rows;
-        if (active) q_part<S>(P, sp, col, A, ZP, row, row < n_rows);
+    const S p = own.x + bs * own.y;
+    s_p[threadIdx.x] = p;
+#pragma unroll
+    for (int k = 0; k < H; ++k)
+        if (k * R < bc.stride) s_p[(k + 1) * R + threadIdx.x] = zp[k].x + bs * zp[k].y;
+    for (int k = H * R + threadIdx.x; k < cnt; k += R) {
+        const V2 v = ZP[bc.halo[b * bc.stride + k]];
+        s_p[R + k] = v.x + bs * v.y;
     }
-    block_sum_all<1>(v);
-    slot_add<1>(red_buf(cg_slots, 2 * i), v);
+    __syncthreads();
+    S q;
+    if (cnt >= 0) {
+        q = P.dot(bc, A, [&](unsigned c) { return s_p[c]; });
+    } else {
+        q = P.dot_wide(col, A, [&](int c) {
+            const V2 v = ZP[c];
+            return v.x + bs * v.y;
+        });
+    }
+    double v[1] = {0.0};
+    if (row < n_rows) {
+        Q[row] = q;
+        v[0] = (double)p * (double)q;
+    }
+    block_slot_add<1, R>(v, red_buf(cg_slots, 2 * i));
 }
 
 // Sums over a node's edges of s_e r_e, s_e q_e, th_e r_e and th_e q_e (r' = r - alpha q is
@@ -1519,6 +1739,24 @@ void launch_aux_scale(hipStream_t s, const AuxSpace& g, const int64_t* sp, const
 }
 
 namespace {
+// One workgroup per row block, consecutive blocks on the same XCD.
+inline RowGrid block_grid(const BlockCols& bc) {
+    RowGrid r;
+    r.nb = bc.nb;
+    r.per = (r.nb + 7) / 8;
+    r.g = (int)std::max<int64_t>(1, r.per);
+    r.grid = 8u * (unsigned)r.g;
+    return r;
+}
+
+template <typename S>
+void product(hipStream_t s, int i, int64_t n_rows, const int64_t* sp, const int32_t* col, const BlockCols& bc,
+             const S* A, const typename Vec<S>::t2* zp, S* Q, double* slots, CgScalars* sc, const AuxSpace& g) {
+    const RowGrid rg = block_grid(bc);
+    hipLaunchKernelGGL(k_pcg_q<S>, dim3(rg.grid), dim3(kBlockRows), sizeof(S) * (kBlockRows + bc.stride), s, n_rows, rg,
+                       i, sp, col, bc, A, zp, Q, slots, sc, g);
+}
+
 template <typename S>
 void pcg_start(hipStream_t s, int64_t n_rows, const int64_t* sp, const int32_t* col, const S* A, const S* dinv,
                const double* b, S* x, bool zero_x, const AuxSpace& g, typename Vec<S>::t2* zp0, S* R, S* Q,
@@ -1538,13 +1776,12 @@ void pcg_start(hipStream_t s, int64_t n_rows, const int64_t* sp, const int32_t* 
 }
 
 template <typename S>
-void pcg_iter(hipStream_t s, int i, int64_t n_rows, const int64_t* sp, const int32_t* col, const S* A, const S* dinv,
-              S* x, const AuxSpace& g, typename Vec<S>::t2* const zp[2], S* R, S* Q, double* slots, CgScalars* sc) {
-    const RowGrid rg = row_grid_full(n_rows);
+void pcg_iter(hipStream_t s, int i, int64_t n_rows, const int64_t* sp, const int32_t* col, const BlockCols& bc,
+              const S* A, const S* dinv, S* x, const AuxSpace& g, typename Vec<S>::t2* const zp[2], S* R, S* Q,
+              double* slots, CgScalars* sc) {
     const RowGrid ng = node_grid(g.n_aux);
     const int a = i & 1, b = 1 - a;
-    hipLaunchKernelGGL(k_pcg_q<S>, dim3(rg.grid), dim3(kBlock), 0, s, n_rows, rg, i, sp, col, A,
-                       (const typename Vec<S>::t2*)zp[a], Q, slots, sc, g);
+    product<S>(s, i, n_rows, sp, col, bc, A, zp[a], Q, slots, sc, g);
     hipLaunchKernelGGL(k_pcg_nodes<S>, dim3(ng.grid), dim3(kBlock), 0, s, ng, i, g, (const S*)R, (const S*)Q, slots,
                        sc);
     if (g.n_far > 0)
@@ -1567,38 +1804,50 @@ void launch_pcg_init(hipStream_t s, int64_t n_rows, const int64_t* sp, const int
 
 // Iteration i: (z, p) pairs read from buffer i & 1, the new pair written to (i + 1) & 1;
 // r in the first n_rows doubles of rq, q in the next n_rows.
-void launch_pcg_iter(hipStream_t s, int i, int64_t n_rows, const int64_t* sp, const int32_t* col, const double* A,
-                     const double* dinv, double* x, const AuxSpace& g, double2* const zp[2], double2* rq,
-                     double* partial, CgScalars* sc) {
+void launch_pcg_iter(hipStream_t s, int i, int64_t n_rows, const int64_t* sp, const int32_t* col,
+                     const BlockCols& bc, const double* A, const double* dinv, double* x, const AuxSpace& g,
+                     double2* const zp[2], double2* rq, double* partial, CgScalars* sc) {
     double* R = reinterpret_cast<double*>(rq);
-    pcg_iter<double>(s, i, n_rows, sp, col, A, dinv, x, g, zp, R, R + n_rows, partial + SLOT_CG * kSlot, sc);
+    pcg_iter<double>(s, i, n_rows, sp, col, bc, A, dinv, x, g, zp, R, R + n_rows, partial + SLOT_CG * kSlot, sc);
 }
 
 // The inner solve of the mixed-precision form: A d = r in FP32 from d = 0, r the FP64
 // true residual that launch_cg_resid left in r_true (its norm from that kernel's partials).
-void launch_pcg_init_f32(hipStream_t s, int64_t n_rows, const int64_t* sp, const int32_t* col, const float* A32,
-                         const float* dinv32, const double* r_true, float* d, const AuxSpace& g, float2* zp0,
-                         float* rq, double* partial, CgScalars* sc, double tol) {
-    pcg_start<float>(s, n_rows, sp, col, A32, dinv32, r_true, d, true, g, zp0, rq, rq + n_rows,
+void launch_pcg_init_f32(hipStream_t s, int64_t n_rows, const int64_t* sp, const int32_t* col,
+                         const float* dinv32, const double* r_true, float* d, const AuxSpace& g, float2* zp0, float* rq,
+                         double* partial, CgScalars* sc, double tol) {
+    pcg_start<float>(s, n_rows, sp, col, nullptr, dinv32, r_true, d, true, g, zp0, rq, rq + n_rows,
                      partial + SLOT_RESID * kSlot, partial + SLOT_CG * kSlot, sc, tol);
 }
 
 void launch_pcg_iter_f32(hipStream_t s, int i, int64_t n_rows, const int64_t* sp, const int32_t* col,
-                         const float* A32, const float* dinv32, float* d, const AuxSpace& g, float2* const zp[2],
-                         float* rq, double* partial, CgScalars* sc) {
-    pcg_iter<float>(s, i, n_rows, sp, col, A32, dinv32, d, g, zp, rq, rq + n_rows, partial + SLOT_CG * kSlot, sc);
+                         const BlockCols& bc, const float* A32, const float* dinv32, float* d, const AuxSpace& g,
+                         float2* const zp[2], float* rq, double* partial, CgScalars* sc) {
+    pcg_iter<float>(s, i, n_rows, sp, col, bc, A32, dinv32, d, g, zp, rq, rq + n_rows, partial + SLOT_CG * kSlot, sc);
 }
 
-// FP32 copies of the operator for the inner solves: A (all nnz stored slots), D^-1, and the
+void launch_block_count(hipStream_t s, const BlockCols& g, const int64_t* sp, const int32_t* col, int32_t* cnt) {
+    if (g.nb > 0)
+        hipLaunchKernelGGL(k_block_cols<false>, dim3((unsigned)g.nb), dim3(kBlock), 0, s, g, sp, col, cnt, nullptr,
+                           nullptr);
+}
+
+void launch_block_fill(hipStream_t s, const BlockCols& g, const int64_t* sp, const int32_t* col, int32_t* halo,
+                       uint16_t* lcol) {
+    if (g.nb > 0)
+        hipLaunchKernelGGL(k_block_cols<true>, dim3((unsigned)g.nb), dim3(kBlock), 0, s, g, sp, col, nullptr, halo, lcol);
+}
+
+// FP32 copies of the operator for the inner solves: A (in the pair layout), D^-1, and the
 // auxiliary space's inverse diagonals at every level.
-void launch_operator_f32(hipStream_t s, int64_t nnz, const double* A, float* A32, int64_t n_rows, const double* dinv,
-                         float* dinv32, const AuxSpace& g) {
+void launch_operator_f32(hipStream_t s, int64_t n_slices, const int64_t* sp, const double* A, float* A32,
+                         int64_t n_rows, const double* dinv, float* dinv32, const AuxSpace& g) {
     auto cvt = [&](const void* a, void* b, int64_t n) {
         if (n > 0)
             hipLaunchKernelGGL(k_to_f32, dim3(grid_1d(n, kBlock)), dim3(kBlock), 0, s,
                                reinterpret_cast<const double*>(a), reinterpret_cast<float*>(b), n);
     };
-    cvt(A, A32, nnz);
+    hipLaunchKernelGGL(k_pack_f32, dim3(grid_1d(64 * n_slices, kBlock)), dim3(kBlock), 0, s, n_slices, sp, A, A32);
     cvt(dinv, dinv32, n_rows);
     cvt(g.scale, g.scale_f, 4 * g.n_aux);
     cvt(g.scale8, g.scale8_f, 4 * ((g.n_aux + 7) / 8));
