@@ -988,8 +988,8 @@ int field_phase(fepic_ctx* c, double dt, double beta, double gamma) {
                     launch_pcg_iter(c->stream, i, ne, c->d_sp, c->d_col, c->bc, c->d_A, c->d_dinv, c->d_x, c->aux, ZP,
                                     c->d_rq, c->d_partial, c->d_sc);
                 else
-                    launch_cg_iter(c->stream, i, ne, c->d_sp, c->d_col, c->d_A, c->d_dinv, c->d_x, V, c->d_partial,
-                                   c->d_sc, c->opt.deterministic != 0);
+                    launch_cg_iter(c->stream, i, ne, c->d_sp, c->d_col, c->bc, c->d_A, c->d_x, V, c->d_partial, c->d_sc,
+                                   c->opt.deterministic != 0);
             });
             if (rc != FEPIC_OK) return rc;
             if (restart == 0) rr0_first = c->h_sc->rr0;

@@ -305,7 +305,7 @@ void launch_cg_init(hipStream_t s, int64_t n_rows, const int64_t* slice_ptr, con
 // det: at most one workgroup per dot slot, so every slot takes a single add and the dots
 // do not depend on the order of the workgroups (deterministic mode).
 void launch_cg_iter(hipStream_t s, int i, int64_t n_rows, const int64_t* slice_ptr, const int32_t* col,
-                    const double* A, const double* dinv, double* x, CgVec* const v[2], double* partial,
+                    const BlockCols& bc, const double* A, double* x, CgVec* const v[2], double* partial,
                     CgScalars* sc, bool det = false);
 void launch_cg_rr0(hipStream_t s, int64_t n_rows, double* partial, CgScalars* sc);
 // Halo sizes of the row blocks into cnt (count), then halo lists and 16-bit columns (fill).

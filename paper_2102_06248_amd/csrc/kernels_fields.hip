@@ -394,142 +394,6 @@ __global__ __launch_bounds__(kBlock) void k_cg_init_b(int64_t n_rows, RowGrid rg
     cg_add(cg_buf(cg_slots, 0), v);
 }
 
-// The part of row j's product that does not depend on the iteration's scalars: the three
-// sums sum_k A_jk R_k, sum_k A_jk W_k, sum_k A_jk S_k over the row's stored entries, and
-// the row's own entries (1 / A_jj from the row's first slot).  A_j u' = sR - alpha sW
-// - alpha beta sS, so the gathers of a row can be issued before the scalars of this
-// iteration are known.
-struct RowPart {
-    double sR, sW, sS;
-    double2 RW, SP;   // own R, W and S, P
-    double x, dinv;
-};
-
-constexpr int kUnroll = 6;   // slots per batch of gathers (rows hold up to ~20 slots)
-
-__device__ __forceinline__ void row_part(RowPart& P, const int64_t* __restrict__ sp, const int32_t* __restrict__ col,
-                                         const double* __restrict__ A, const CgVec* __restrict__ V,
-                                         const double* __restrict__ x, const double* __restrict__ dinv, int64_t row,
-                                         bool real) {
-    const int64_t sl = row >> 6;
-    const int lane = (int)(row & 63);
-    const int64_t k1 = sp[sl + 1];
-    int64_t k = sp[sl] + lane;
-    const int64_t r = real ? row : 0;
-    const double2* own = reinterpret_cast<const double2*>(V + r);
-    P.RW = own[0];
-    P.SP = own[1];
-    P.x = x[r];
-    P.dinv = real ? 1.0 / A[sp[sl] + lane] : 1.0;   // the diagonal is slot 0 of the row
-    double r0 = 0.0, w0 = 0.0, s0 = 0.0, r1 = 0.0, w1 = 0.0, s1 = 0.0;
-    for (; k + (kUnroll - 1) * 64 < k1; k += kUnroll * 64) {
-        int c[kUnroll];
-        double a[kUnroll];
-#pragma unroll
-        for (int q = 0; q < kUnroll; ++q) {
-            c[q] = col[k + 64 * q];
-            a[q] = A[k + 64 * q];
-        }
-        double2 rw[kUnroll];
-        double sv[kUnroll];
-#pragma unroll
-        for (int q = 0; q < kUnroll; ++q) {
-            rw[q] = *reinterpret_cast<const double2*>(V + c[q]);
-            sv[q] = V[c[q]].S;
-        }
-#pragma unroll
-        for (int q = 0; q < kUnroll; q += 2) {
-            r0 += a[q] * rw[q].x;
-            w0 += a[q] * rw[q].y;
-            s0 += a[q] * sv[q];
-            r1 += a[q + 1] * rw[q + 1].x;
-            w1 += a[q + 1] * rw[q + 1].y;
-            s1 += a[q + 1] * sv[q + 1];
-        }
-    }
-    for (; k < k1; k += 64) {
-        const int c = col[k];
-        const double a = A[k];
-        const double2 rw = *reinterpret_cast<const double2*>(V + c);
-        r0 += a * rw.x;
-        w0 += a * rw.y;
-        s0 += a * V[c].S;
-    }
-    P.sR = r0 + r1;
-    P.sW = w0 + w1;
-    P.sS = s0 + s1;
-}
-
-__global__ __launch_bounds__(kBlock) void k_cg_iter(int64_t n_rows, RowGrid rg, int i, const int64_t* __restrict__ sp,
-                                                     const int32_t* __restrict__ col, const double* __restrict__ A,
-                                                     const double* __restrict__ dinv, double* __restrict__ x,
-                                                     const CgVec* __restrict__ V, CgVec* __restrict__ V_new,
-                                                     double* __restrict__ cg_slots, CgScalars* sc) {
-    // The converged flag, the previous kernel's dot slots and this workgroup's first rows
-    // are all in flight together; the flag (the same for every thread) is checked before
-    // any write, so a launch after convergence changes nothing.
-    const int conv = sc->converged;
-    double t[3] = {0.0, 0.0, 0.0};
-    {
-        const double* in = cg_buf(cg_slots, i);
-        if (threadIdx.x < kCgSlots) {
-            t[0] = in[threadIdx.x];
-            t[1] = in[kCgSlots + threadIdx.x];
-            t[2] = in[2 * kCgSlots + threadIdx.x];
-        }
-    }
-    int64_t lb = rg_first(rg);
-    const int64_t le = rg_end(rg);
-    RowPart P;
-    int64_t row = lb * kBlock + threadIdx.x;
-    bool active = lb < le && ((row >> 6) << 6) < n_rows;
-    if (active) row_part(P, sp, col, A, V, x, dinv, row, row < n_rows);
-    if (conv) return;
-    block_sum_all<3>(t);
-    const double g = t[0], d = t[1], rr = t[2];
-    const bool done = !(rr > sc->tol2_bb) || sc->bb == 0.0;
-    const double beta = (i == 0) ? 0.0 : g / sc->gam[(i - 1) & 1];
-    const double alpha = (i == 0) ? g / d : g / (d - beta * g / sc->alpha[(i - 1) & 1]);
-    const bool bad = !done && !(alpha > 0.0 && alpha < INFINITY && beta >= 0.0 && beta < INFINITY);
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        sc->gam[i & 1] = g;
-        sc->alpha[i & 1] = alpha;
-        sc->rr = rr;
-        sc->iters = i;
-        if (i == 0) sc->rr0 = rr;
-        if (done) sc->converged = 1;
-        if (bad) sc->converged = 2;
-    }
-    if (done || bad) return;
-    if (blockIdx.x == 0)   // read by the previous kernel; the next one adds into it
-        for (int k = threadIdx.x; k < 3 * kCgSlots; k += kBlock) cg_buf(cg_slots, i + 2)[k] = 0.0;
-    const double ab = alpha * beta;
-    double v[3] = {0.0, 0.0, 0.0};
-    while (lb < le) {
-        if (active && row < n_rows) {
-            const double acc = P.sR - alpha * P.sW - ab * P.sS;   // (A u')_j
-            const double pj = P.RW.x + beta * P.SP.y;
-            const double sj = P.RW.y + beta * P.SP.x;   // D^-1 s
-            x[row] = P.x + alpha * pj;
-            const double un = P.RW.x - alpha * sj;      // D^-1 r' = u'
-            const double rn = un / P.dinv;
-            const double wn = P.dinv * acc;
-            double2* o = reinterpret_cast<double2*>(V_new + row);
-            o[0] = make_double2(un, wn);
-            o[1] = make_double2(sj, pj);
-            v[0] += rn * un;
-            v[1] += un * acc;
-            v[2] += rn * rn;
-        }
-        lb += rg.g;
-        row = lb * kBlock + threadIdx.x;
-        active = lb < le && ((row >> 6) << 6) < n_rows;
-        if (active) row_part(P, sp, col, A, V, x, dinv, row, row < n_rows);
-    }
-    block_sum_all<3>(v);
-    cg_add(cg_buf(cg_slots, i + 1), v);
-}
-
 // ------------------------------------------------------------------------------------
 // PCG with the nodal auxiliary-space preconditioner of Hiptmair and Xu (2007), additive,
 // one Jacobi step in each space:  B r = D^-1 r + G D_G^-1 G^T r + Pi D_Pi^-1 Pi^T r,
@@ -1010,6 +874,112 @@ __global__ __launch_bounds__(kBlock) void k_pack_f32(int64_t n_slices, const int
         *reinterpret_cast<float2*>(A32 + k0 + 64 * k + 2 * lane) =
             make_float2((float)A[k0 + 64 * k + lane], (float)A[k0 + 64 * k + 64 + lane]);
     if (k < w) A32[k0 + 64 * k + lane] = (float)A[k0 + 64 * k + lane];
+}
+
+// One Jacobi-PCG iteration per row block (in the deterministic mode a workgroup takes every
+// rg.g-th block, so that each dot slot takes a single add).  The neighbours'
+// u' = R - alpha (W + beta S) are staged in LDS like the auxiliary-space product's p, one
+// value per column instead of three gathered values per stored slot; a row's diagonal is its
+// slot 0.  Bound by HBM on large meshes (998k tets: 92.8 -> 55.4 us), by the chain of
+// dependent loads on small ones, where the six-at-a-time gathers took up to twelve round
+// trips: beam 19.7 -> 13.1 us, 29k tets 8.2 -> 6.9, 1.3k tets 7.6 -> 5.1; deterministic, 13k
+// tets, 10.6 -> 6.0.
+__global__ __launch_bounds__(kBlockRows) void k_cg_iter(int64_t n_rows, RowGrid rg, int i,
+                                                         const int64_t* __restrict__ sp,
+                                                         const int32_t* __restrict__ col, BlockCols bc,
+                                                         const double* __restrict__ A, double* __restrict__ x,
+                                                         const CgVec* __restrict__ V, CgVec* __restrict__ V_new,
+                                                         double* __restrict__ cg_slots, CgScalars* sc) {
+    extern __shared__ double s_u[];
+    constexpr int R = kBlockRows, H = kHaloRegs;
+    // The converged flag, the previous kernel's dot slots and this workgroup's first block
+    // are all in flight together; the flag (the same for every thread) is checked before
+    // any write, so a launch after convergence changes nothing.
+    const int conv = sc->converged;
+    const double tol2_bb = sc->tol2_bb, bb = sc->bb, gam_old = sc->gam[(i + 1) & 1], alpha_old = sc->alpha[(i + 1) & 1];
+    double t[3];
+    slot_load_wave<3>(cg_buf(cg_slots, i), t);
+    int64_t b = rg_first(rg);
+    const int64_t le = rg_end(rg);
+    if (b >= le) return;   // the whole workgroup
+    BlockRow<double> P;
+    double2 own_rw, own_sp, rw[H];
+    double own_x, hs[H];
+    int cnt;
+    auto load = [&]() {
+        const int64_t row = b * R + threadIdx.x, r = row < n_rows ? row : 0;
+        P.load(bc, b * (R / 64) + (threadIdx.x >> 6), sp, A);
+        cnt = bc.cnt[b];
+        int h[H];
+        halo_ids(bc, b, h);
+        const double2* o = reinterpret_cast<const double2*>(V + r);
+        own_rw = o[0];
+        own_sp = o[1];
+        own_x = x[r];
+#pragma unroll
+        for (int k = 0; k < H; ++k)
+            if (k * R < bc.stride) {
+                rw[k] = *reinterpret_cast<const double2*>(V + h[k]);
+                hs[k] = V[h[k]].S;
+            }
+    };
+    load();
+    if (conv) return;
+    const double g = wave_total(t[0]), d = wave_total(t[1]), rr = wave_total(t[2]);
+    const bool done = !(rr > tol2_bb) || bb == 0.0;
+    const double beta = (i == 0) ? 0.0 : g / gam_old;
+    const double alpha = (i == 0) ? g / d : g / (d - beta * g / alpha_old);
+    const bool bad = !done && !(alpha > 0.0 && alpha < INFINITY && beta >= 0.0 && beta < INFINITY);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        sc->gam[i & 1] = g;
+        sc->alpha[i & 1] = alpha;
+        sc->rr = rr;
+        sc->iters = i;
+        if (i == 0) sc->rr0 = rr;
+        if (done) sc->converged = 1;
+        if (bad) sc->converged = 2;
+    }
+    if (done || bad) return;
+    if (blockIdx.x == 0)   // read by the previous kernel; the next one adds into it
+        for (int k = threadIdx.x; k < 3 * kCgSlots; k += R) cg_buf(cg_slots, i + 2)[k] = 0.0;
+    double v[3] = {0.0, 0.0, 0.0};
+    auto u_new = [&](double2 w, double s) { return w.x - alpha * (w.y + beta * s); };
+    for (;;) {
+        const int64_t row = b * R + threadIdx.x;
+        const double sj = own_rw.y + beta * own_sp.x;   // D^-1 s
+        const double un = own_rw.x - alpha * sj;        // D^-1 r' = u'
+        s_u[threadIdx.x] = un;
+#pragma unroll
+        for (int k = 0; k < H; ++k)
+            if (k * R < bc.stride) s_u[(k + 1) * R + threadIdx.x] = u_new(rw[k], hs[k]);
+        for (int k = H * R + threadIdx.x; k < cnt; k += R) {
+            const int c = bc.halo[b * bc.stride + k];
+            s_u[R + k] = u_new(*reinterpret_cast<const double2*>(V + c), V[c].S);
+        }
+        __syncthreads();
+        double acc;   // (A u')_j
+        if (cnt >= 0)
+            acc = P.dot(bc, A, [&](unsigned c) { return s_u[c]; });
+        else
+            acc = P.dot_wide(col, A, [&](int c) { return u_new(*reinterpret_cast<const double2*>(V + c), V[c].S); });
+        if (row < n_rows) {
+            const double diag = P.a[0];
+            const double pj = own_rw.x + beta * own_sp.y;
+            x[row] = own_x + alpha * pj;
+            const double rn = un * diag;
+            double2* o = reinterpret_cast<double2*>(V_new + row);
+            o[0] = make_double2(un, acc / diag);
+            o[1] = make_double2(sj, pj);
+            v[0] += rn * un;
+            v[1] += un * acc;
+            v[2] += rn * rn;
+        }
+        b += rg.g;
+        if (b >= le) break;
+        __syncthreads();   // the staged values are read before the next block's
+        load();
+    }
+    block_slot_add<3, R>(v, cg_buf(cg_slots, i + 1));
 }
 
 // ||b||^2 from the partials of the kernel that summed it (the right-hand side's, or the
@@ -1694,13 +1664,27 @@ inline RowGrid row_grid_full(int64_t n_rows) {
     return r;
 }
 
+// At most max_grid workgroups over the row blocks (0: one each), consecutive blocks on the
+// same XCD.
+inline RowGrid block_grid(const BlockCols& bc, int max_grid = 0) {
+    RowGrid r;
+    r.nb = bc.nb;
+    r.per = (r.nb + 7) / 8;
+    r.g = (int)std::max<int64_t>(1, max_grid ? std::min<int64_t>(r.per, max_grid / 8) : r.per);
+    r.grid = 8u * (unsigned)r.g;
+    return r;
+}
+
+// Dynamic LDS of a staged vector: the block's own rows and its halo.
+inline size_t staged_bytes(const BlockCols& bc, size_t value) { return value * (size_t)(kBlockRows + bc.stride); }
+
 // Iteration i reads the interleaved state from buffer i & 1 and writes buffer (i + 1) & 1.
-void launch_cg_iter(hipStream_t s, int i, int64_t n_rows, const int64_t* sp, const int32_t* col, const double* A,
-                    const double* dinv, double* x, CgVec* const v[2], double* partial, CgScalars* sc, bool det) {
-    const RowGrid rg = det ? row_grid(n_rows, kCgSlots) : row_grid_full(n_rows);
+void launch_cg_iter(hipStream_t s, int i, int64_t n_rows, const int64_t* sp, const int32_t* col, const BlockCols& bc,
+                    const double* A, double* x, CgVec* const v[2], double* partial, CgScalars* sc, bool det) {
+    const RowGrid rg = block_grid(bc, det ? kCgSlots : 0);
     const int a = i & 1, b = 1 - a;
-    hipLaunchKernelGGL(k_cg_iter, dim3(rg.grid), dim3(kBlock), 0, s, n_rows, rg, i, sp, col, A, dinv, x, v[a], v[b],
-                       partial + SLOT_CG * kSlot, sc);
+    hipLaunchKernelGGL(k_cg_iter, dim3(rg.grid), dim3(kBlockRows), staged_bytes(bc, sizeof(double)), s, n_rows, rg, i, sp,
+                       col, bc, A, x, v[a], v[b], partial + SLOT_CG * kSlot, sc);
 }
 
 // One workgroup per slice of 64 auxiliary nodes, consecutive slices on the same XCD.
@@ -1739,22 +1723,12 @@ void launch_aux_scale(hipStream_t s, const AuxSpace& g, const int64_t* sp, const
 }
 
 namespace {
-// One workgroup per row block, consecutive blocks on the same XCD.
-inline RowGrid block_grid(const BlockCols& bc) {
-    RowGrid r;
-    r.nb = bc.nb;
-    r.per = (r.nb + 7) / 8;
-    r.g = (int)std::max<int64_t>(1, r.per);
-    r.grid = 8u * (unsigned)r.g;
-    return r;
-}
-
 template <typename S>
 void product(hipStream_t s, int i, int64_t n_rows, const int64_t* sp, const int32_t* col, const BlockCols& bc,
              const S* A, const typename Vec<S>::t2* zp, S* Q, double* slots, CgScalars* sc, const AuxSpace& g) {
     const RowGrid rg = block_grid(bc);
-    hipLaunchKernelGGL(k_pcg_q<S>, dim3(rg.grid), dim3(kBlockRows), sizeof(S) * (kBlockRows + bc.stride), s, n_rows, rg,
-                       i, sp, col, bc, A, zp, Q, slots, sc, g);
+    hipLaunchKernelGGL(k_pcg_q<S>, dim3(rg.grid), dim3(kBlockRows), staged_bytes(bc, sizeof(S)), s, n_rows, rg, i, sp,
+                       col, bc, A, zp, Q, slots, sc, g);
 }
 
 template <typename S>

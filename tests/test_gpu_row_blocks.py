@@ -54,16 +54,22 @@ def fan(n):
 
 
 MESHES = {"one_partial_block": lambda: jittered_kuhn(2, seed=1)[:2], "ragged_blocks": lambda: jittered_kuhn(7, seed=2)[:2],
-          "fan": lambda: fan(1600)}
+          # 37,043 rows: more blocks than the deterministic mode's 64 workgroups
+          "looped_blocks": lambda: jittered_kuhn(17, seed=3)[:2], "fan": lambda: fan(1600)}
 
 
 @pytest.mark.parametrize("mesh,solve", [("one_partial_block", "fp64"), ("one_partial_block", "mixed"),
-                                        ("ragged_blocks", "fp64"), ("ragged_blocks", "mixed"), ("fan", "fp64"),
-                                        ("fan", "mixed")])
+                                        ("one_partial_block", "jacobi"), ("one_partial_block", "deterministic"),
+                                        ("ragged_blocks", "fp64"), ("ragged_blocks", "mixed"),
+                                        ("ragged_blocks", "jacobi"), ("ragged_blocks", "deterministic"),
+                                        ("looped_blocks", "deterministic"), ("fan", "fp64"), ("fan", "mixed"),
+                                        ("fan", "jacobi")])
 def test_solution_meets_stopping_rule(F, mesh, solve):
     announce(f"row blocks: {mesh}, {solve}")
     xyz, tets = MESHES[mesh]()
-    opts = {"fp64": dict(), "mixed": dict(solve_precision=F.FEPIC_SOLVE_MIXED)}[solve]
+    opts = {"fp64": dict(), "mixed": dict(solve_precision=F.FEPIC_SOLVE_MIXED),
+            "jacobi": dict(preconditioner=F.FEPIC_PC_JACOBI),
+            "deterministic": dict(preconditioner=F.FEPIC_PC_JACOBI, deterministic=1)}[solve]
     with F.Simulation(xyz, tets, device=0, cg_tol=TOL, aux_far_levels=0, **opts) as L:
         n = L.sizes["n_edges"]
         M, S = (sp.csr_matrix((v, (r, c)), shape=(n, n)) for r, c, v in (F.fepic_get_matrix(L.ctx, w) for w in (0, 1)))
