@@ -461,9 +461,9 @@ int fepic_mlp_adam_step(fepic_ctx* ctx, const float* grad, double lr, double bet
  * device; the kernels are enqueued on the context's stream and the call returns without
  * waiting (the caller synchronizes before reading the outputs).  The result is that of
  * fepic_mlp_grad on the same rows, summed in the same order.  The per-workgroup partial
- * sums live in one fixed device array of the library per GPU (2.3 MB, held until the
- * process ends), set up by fepic_create: calls that overlap on one GPU, from any context
- * or stream, race on it.  Errors: FEPIC_E_ARG for n <= 0, a NULL pointer or n above
+ * sums live in the context (4.7 MB, there since its weights were set or trained): calls on
+ * contexts of their own may overlap, calls on one context run one after another on its
+ * stream.  Errors: FEPIC_E_ARG for n <= 0, a NULL pointer or n above
  * FEPIC_MLP_NOALLOC_MAX_ROWS; FEPIC_E_STATE when the context has no network weights yet
  * (fepic_ws_set_weights or fepic_ws_train first; this call does not create them);
  * FEPIC_E_NO_DEVICE on a host-only context. */

@@ -3,7 +3,7 @@
 // operands, FP32 accumulation); layer 1 (K = 4) is computed on the vector ALUs straight
 // into the MFMA operand layout; layer 3 is a 64-wide dot reduced across lanes.  Training
 // uses the same tiles for the backward products dW2 = dZ2^T H1 (reduction over the batch
-// rows) and dH1 = dZ2 W2, staged through per-wave LDS tiles; Adam keeps FP32 masters.
+// rows, staged through LDS) and dH1 = dZ2 W2 (from registers); Adam keeps FP32 masters.
 //
 // Operand layout of v_mfma_f32_16x16x32_bf16 (wave64), lane l, g = l / 16:
 //   A (16 x 32):  row l % 16, 8 consecutive k starting at 8 g
@@ -38,7 +38,6 @@ struct MlpLds {
     float b1[kH], b2[kH], W3[kH];
     float b3;
     alignas(16) __bf16 W2[kH * kH];    // [n][k]
-    alignas(16) __bf16 W2T[kH * kH];   // [k][n]
 };
 
 __device__ __forceinline__ void load_params(MlpLds& L, const float* __restrict__ P) {
@@ -49,9 +48,7 @@ __device__ __forceinline__ void load_params(MlpLds& L, const float* __restrict__
         L.W3[i] = P[oW3 + i];
     }
     for (int i = threadIdx.x; i < kH * kH; i += blockDim.x) {
-        const __bf16 w = (__bf16)P[oW2 + i];
-        L.W2[i] = w;
-        L.W2T[(i % kH) * kH + i / kH] = w;
+        L.W2[i] = (__bf16)P[oW2 + i];
     }
     if (threadIdx.x == 0) L.b3 = P[ob3];
     __syncthreads();
@@ -145,231 +142,263 @@ __device__ __forceinline__ int64_t batch_row(const BatchSrc& s, int64_t i) {
     return s.n_all ? (int64_t)(mix64(s.seed ^ (uint64_t)i * 0xD1B54A32D192ED03ull) % (uint64_t)s.n_all) : i;
 }
 
+// Sum over each row of 16 lanes, in its last lane (DPP moves).
+template <int kCtrl>
+__device__ __forceinline__ float row_step(float v) {
+    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), kCtrl, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float row16_total(float v) {
+    v = row_step<0x111>(v);   // row_shr:1
+    v = row_step<0x112>(v);
+    v = row_step<0x114>(v);
+    return row_step<0x118>(v);
+}
+
 // Gradient of L = (1/N) sum (y - t)^2 over a minibatch; every workgroup writes the sum of
 // its rows' gradients (4545 values) and of its squared errors to part[blockIdx].
-// Waves take 32-row tiles (two 16-row halves for the forward product, one K = 32 block
-// for dW2).
+// A workgroup takes tiles of 128 rows, wave w rows 32 w to 32 w + 31 in two halves of 16.
+// The second layer is formed transposed, Z2^T = W2 H1^T (both operands as built for the
+// plain product, swapped), so that lane (c, g) holds row c's units 16 nt + 4 g + i: the
+// output and its error need two shuffles, and the rows' dz are, as they stand, the operand
+// of dH1 = dZ2 W2 with the units of a K block in the order 32 kb + 4 g + i,
+// 32 kb + 16 + 4 g + i, for which W2's columns are loaded into registers once.  dW2 = dZ2^T H1
+// runs over the rows, which no lane holds together: dZ2 and H1 go transposed through LDS,
+// shared by the workgroup, and wave w forms units 16 w to 16 w + 15 over all 128 rows, so
+// that no sum across waves is left.  Bound by latency (one wave per SIMD; about 3.6 us per
+// tile and 8 us of set-up and final sums): 65,536 rows 34.9 -> 18.5 us (32-row tiles per
+// wave, all of dW2 in every wave and summed in LDS, 128 workgroups: 24.3 with 256 of them);
+// 32,768 rows 14.9, 128 rows 12.1.  W2 staged in LDS first instead of read by every wave: 19.0.
+constexpr int kTileRows = 128;
+constexpr int kTileStride = kTileRows + 8;   // spreads the rows of the transposed tiles over the banks
+
 __global__ __launch_bounds__(kMlpBlock) void k_mlp_grad(BatchSrc src, float inv_n, const float* __restrict__ P,
                                                         float* __restrict__ part, double* __restrict__ loss_part) {
-    __shared__ MlpLds L;
-    // per-wave tiles: dZ2 [row][n] and H1 [row][k] (BF16); after the main loop the same
-    // memory holds the cross-wave reduction of dW2 (FP32 [n][k])
-    __shared__ alignas(16) __bf16 sTiles[2][4][32 * kH];
-    __bf16 (*sZ)[32 * kH] = sTiles[0];
-    __bf16 (*sH)[32 * kH] = sTiles[1];
-    float* sRed = reinterpret_cast<float*>(&sTiles[0][0][0]);
+    __shared__ float sW1[kH * kIn], sb1[kH], sb2[kH], sW3[kH];
+    __shared__ alignas(16) __bf16 sZT[kH * kTileStride];   // [unit][row]
+    __shared__ alignas(16) __bf16 sHT[kH * kTileStride];
     __shared__ float sX[4][32 * 4];
-    __shared__ float sVec[4][4 * kH + 1];
+    __shared__ float sVec[4][7 * kH];
+    __shared__ float sB3[4];
     __shared__ double sLoss[4];
-    load_params(L, P);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4, c = lane & 15;
+    for (int i = threadIdx.x; i < kH * kIn; i += kMlpBlock) sW1[i] = P[oW1 + i];
+    if (threadIdx.x < kH) {
+        sb1[threadIdx.x] = P[ob1 + threadIdx.x];
+        sb2[threadIdx.x] = P[ob2 + threadIdx.x];
+        sW3[threadIdx.x] = P[oW3 + threadIdx.x];
+    }
+    const float b3 = P[ob3];
+    // W2 rows for the forward product: row 16 nt + c, inputs 32 kb + 8 g + j; W2 columns for
+    // the backward one: column 16 kt + c, units in the order above
+    bf16x8 Wf[4][2], Wb[4][2];
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                Wf[t][kb][j] = (__bf16)P[oW2 + (16 * t + c) * kH + 32 * kb + 8 * g + j];
+                Wb[t][kb][j] = (__bf16)P[oW2 + (32 * kb + 16 * (j >> 2) + 4 * g + (j & 3)) * kH + 16 * t + c];
+            }
+    __syncthreads();
 
-    floatx4 dW2[4][4];
+    floatx4 dW2[4];
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) dW2[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
-    float dW1[4][4] = {}, db1[4] = {}, db2[4] = {}, dW3[4] = {};
+    for (int kt = 0; kt < 4; ++kt) dW2[kt] = floatx4{0.f, 0.f, 0.f, 0.f};
+    float dW1[4][4] = {}, db1[4] = {}, db2[4][4] = {}, dW3[4][4] = {};
     float db3 = 0.f;
     double loss = 0.0;
 
-    const int64_t n_tiles = (src.n + 31) / 32;
-    for (int64_t t = (int64_t)blockIdx.x * 4 + wave; t < n_tiles; t += (int64_t)gridDim.x * 4) {
-        // ---- forward and the output-layer backward, per 16-row half
+    const int64_t n_tiles = (src.n + kTileRows - 1) / kTileRows;
+    for (int64_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
+        bf16x8 dz[2][2];   // [half][kb]
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const int64_t i0 = 32 * t + 16 * h;
-            float x[4] = {0.f, 0.f, 0.f, 0.f};
-            {
-                const int64_t i = i0 + c;
-                if (i < src.n) {
-                    const float4 v = src.X[batch_row(src, i)];
-                    x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
-                }
+            const int m = 32 * wave + 16 * h + c;   // the lane's row of the tile
+            const int64_t i = t * kTileRows + m;
+            float x[4] = {0.f, 0.f, 0.f, 0.f}, target = 0.f;
+            if (i < src.n) {
+                const int64_t r = batch_row(src, i);
+                const float4 v = src.X[r];
+                x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
+                target = src.T[r];
             }
-            if (g == 0) {
+            if (g == 0) *reinterpret_cast<float4*>(&sX[wave][(16 * h + c) * 4]) = make_float4(x[0], x[1], x[2], x[3]);
+            bf16x8 a[2];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) sX[wave][(16 * h + c) * 4 + q] = x[q];
-            }
-            const bf16x8 a0 = layer1_operand(L, x, 0, g), a1 = layer1_operand(L, x, 1, g);
-            // H1 tile (row c of this half, k = 32 kb + 8 g + j)
-            *reinterpret_cast<bf16x8*>(&sH[wave][(16 * h + c) * kH + 8 * g]) = a0;
-            *reinterpret_cast<bf16x8*>(&sH[wave][(16 * h + c) * kH + 32 + 8 * g]) = a1;
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const int k = 32 * kb + 8 * g + j;
+                    const float z = sb1[k] + sW1[4 * k] * x[0] + sW1[4 * k + 1] * x[1] + sW1[4 * k + 2] * x[2] +
+                                    sW1[4 * k + 3] * x[3];
+                    a[kb][j] = (__bf16)fmaxf(z, 0.0f);
+                    sHT[k * kTileStride + m] = a[kb][j];
+                }
             floatx4 z2[4];
-            float part_y[4] = {0.f, 0.f, 0.f, 0.f};
+            float y = 0.f;
 #pragma unroll
             for (int nt = 0; nt < 4; ++nt) {
                 floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-                acc = mfma(a0, w2_operand(L, nt, 0, lane), acc);
-                acc = mfma(a1, w2_operand(L, nt, 1, lane), acc);
-                const int nn = 16 * nt + c;
+                acc = mfma(Wf[nt][0], a[0], acc);
+                acc = mfma(Wf[nt][1], a[1], acc);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    acc[i] += L.b2[nn];
-                    part_y[i] += fmaxf(acc[i], 0.0f) * L.W3[nn];
+                for (int q = 0; q < 4; ++q) {
+                    const int n = 16 * nt + 4 * g + q;
+                    acc[q] += sb2[n];
+                    y += fmaxf(acc[q], 0.0f) * sW3[n];
                 }
                 z2[nt] = acc;
             }
-            float dy[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float yv = group16_sum(part_y[i]) + L.b3;
-                const int64_t r = i0 + 4 * g + i;
-                float e = 0.f;
-                if (r < src.n) e = yv - src.T[batch_row(src, r)];
-                dy[i] = 2.0f * inv_n * e;
-                if (c == 0) {
-                    loss += (double)e * e;
-                    db3 += dy[i];
-                }
+            y += __shfl_xor(y, 16);
+            y += __shfl_xor(y, 32);
+            const float e = i < src.n ? y + b3 - target : 0.f;
+            const float dy = 2.0f * inv_n * e;
+            if (g == 0) {
+                loss += (double)e * e;
+                db3 += dy;
             }
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt) {
-                const int nn = 16 * nt + c;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float z = z2[nt][i];
-                    const float h2 = fmaxf(z, 0.0f);
-                    dW3[nt] += dy[i] * h2;
-                    const float dz = (z > 0.0f) ? dy[i] * L.W3[nn] : 0.0f;
-                    db2[nt] += dz;
-                    sZ[wave][(16 * h + 4 * g + i) * kH + nn] = (__bf16)dz;
-                }
-            }
-        }
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        // ---- dW2[n][k] += sum over the 32 rows of dZ2[m][n] H1[m][k] (K = rows)
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
-            bf16x8 a;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) a[j] = sZ[wave][(8 * g + j) * kH + 16 * nt + c];
-#pragma unroll
-            for (int kt = 0; kt < 4; ++kt) {
-                bf16x8 b;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) b[j] = sH[wave][(8 * g + j) * kH + 16 * kt + c];
-                dW2[nt][kt] = mfma(a, b, dW2[nt][kt]);
-            }
-        }
-        // ---- dH1 = dZ2 W2 per 16-row half, then through the first ReLU
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const bf16x8 a0 = *reinterpret_cast<const bf16x8*>(&sZ[wave][(16 * h + c) * kH + 8 * g]);
-            const bf16x8 a1 = *reinterpret_cast<const bf16x8*>(&sZ[wave][(16 * h + c) * kH + 32 + 8 * g]);
-#pragma unroll
-            for (int kt = 0; kt < 4; ++kt) {
-                const int k = 16 * kt + c;
-                // B[n][k] = W2[n][k], n = 32 nb + 8 g + j: contiguous in W2^T row k
-                const bf16x8 b0 = *reinterpret_cast<const bf16x8*>(&L.W2T[k * kH + 8 * g]);
-                const bf16x8 b1 = *reinterpret_cast<const bf16x8*>(&L.W2T[k * kH + 32 + 8 * g]);
-                floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-                acc = mfma(a0, b0, acc);
-                acc = mfma(a1, b1, acc);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int m = 16 * h + 4 * g + i;
-                    const float* xr = &sX[wave][m * 4];
-                    const float z1 = L.b1[k] + L.W1[4 * k] * xr[0] + L.W1[4 * k + 1] * xr[1] +
-                                     L.W1[4 * k + 2] * xr[2] + L.W1[4 * k + 3] * xr[3];
-                    const float dz1 = (z1 > 0.0f) ? acc[i] : 0.0f;
-                    db1[kt] += dz1;
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) dW1[kt][q] += dz1 * xr[q];
-                }
-            }
-        }
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    }
-
-    // ---- block reduction into part[blockIdx.x][0..4544]
-    float* out = part + (size_t)blockIdx.x * kNP;
-    __syncthreads();  // every wave is done with its tiles before they become sRed
-    for (int i = threadIdx.x; i < kH * kH; i += blockDim.x) sRed[i] = 0.f;
-    __syncthreads();
-    for (int w = 0; w < 4; ++w) {
-        if (wave == w) {
 #pragma unroll
             for (int nt = 0; nt < 4; ++nt)
 #pragma unroll
-                for (int kt = 0; kt < 4; ++kt)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) sRed[(16 * nt + 4 * g + i) * kH + 16 * kt + c] += dW2[nt][kt][i];
+                for (int q = 0; q < 4; ++q) {
+                    const int n = 16 * nt + 4 * g + q;
+                    const float z = z2[nt][q];
+                    dW3[nt][q] += dy * fmaxf(z, 0.0f);
+                    const float d = (z > 0.0f) ? dy * sW3[n] : 0.0f;
+                    db2[nt][q] += d;
+                    const __bf16 db = (__bf16)d;
+                    dz[h][nt >> 1][4 * (nt & 1) + q] = db;
+                    sZT[n * kTileStride + m] = db;
+                }
         }
         __syncthreads();
+        // ---- dW2[n][k] += sum over the tile's rows of dZ2[m][n] H1[m][k], n in 16 w .. 16 w + 15
+#pragma unroll
+        for (int s = 0; s < kTileRows / 32; ++s) {
+            const int m0 = 32 * s + 8 * g;
+            const bf16x8 za = *reinterpret_cast<const bf16x8*>(&sZT[(16 * wave + c) * kTileStride + m0]);
+#pragma unroll
+            for (int kt = 0; kt < 4; ++kt) {
+                const bf16x8 hb = *reinterpret_cast<const bf16x8*>(&sHT[(16 * kt + c) * kTileStride + m0]);
+                dW2[kt] = mfma(za, hb, dW2[kt]);
+            }
+        }
+        // ---- dH1 = dZ2 W2 per half (rows 4 g + i, input 16 kt + c), then through the first ReLU
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int kt = 0; kt < 4; ++kt) {
+                const int k = 16 * kt + c;
+                floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+                acc = mfma(dz[h][0], Wb[kt][0], acc);
+                acc = mfma(dz[h][1], Wb[kt][1], acc);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float4 xr = *reinterpret_cast<const float4*>(&sX[wave][(16 * h + 4 * g + q) * 4]);
+                    const float z1 = sb1[k] + sW1[4 * k] * xr.x + sW1[4 * k + 1] * xr.y + sW1[4 * k + 2] * xr.z +
+                                     sW1[4 * k + 3] * xr.w;
+                    const float dz1 = (z1 > 0.0f) ? acc[q] : 0.0f;
+                    db1[kt] += dz1;
+                    dW1[kt][0] += dz1 * xr.x;
+                    dW1[kt][1] += dz1 * xr.y;
+                    dW1[kt][2] += dz1 * xr.z;
+                    dW1[kt][3] += dz1 * xr.w;
+                }
+            }
+        __syncthreads();   // the tile has been read before the next one is written
     }
-    for (int i = threadIdx.x; i < kH * kH; i += blockDim.x) out[oW2 + i] = sRed[i];
-    // per-k / per-n vectors: sum over the 4 lane groups, then over waves
-    float vec[4 * 4 + 4 + 4 + 4];
+
+    // ---- part[blockIdx.x][0..4544]: dW2 as the waves hold it, the rest summed over lanes and waves
+    float* out = part + (size_t)blockIdx.x * kNP;
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) out[oW2 + (16 * wave + 4 * g + q) * kH + 16 * kt + c] = dW2[kt][q];
+    float* vec = sVec[wave];   // dW1 [4 k + q], db1, db2, dW3
 #pragma unroll
     for (int kt = 0; kt < 4; ++kt) {
+        const int k = 16 * kt + c;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) vec[4 * kt + q] = dW1[kt][q];
-        vec[16 + kt] = db1[kt];
-        vec[20 + kt] = db2[kt];
-        vec[24 + kt] = dW3[kt];
-    }
-#pragma unroll
-    for (int v = 0; v < 28; ++v) {
-        vec[v] += __shfl_xor(vec[v], 16);
-        vec[v] += __shfl_xor(vec[v], 32);
-    }
-    float b3s = db3;
-    for (int off = 32; off > 0; off >>= 1) b3s += __shfl_xor(b3s, off);
-    for (int off = 32; off > 0; off >>= 1) loss += __shfl_xor(loss, off);
-    if (g == 0) {
-#pragma unroll
-        for (int kt = 0; kt < 4; ++kt) {
-            const int k = 16 * kt + c;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) sVec[wave][4 * k + q] = vec[4 * kt + q];
+        for (int q = 0; q < 4; ++q) {
+            float v = dW1[kt][q];
+            v += __shfl_xor(v, 16);
+            v += __shfl_xor(v, 32);
+            if (g == 0) vec[4 * k + q] = v;
         }
+        float v = db1[kt];
+        v += __shfl_xor(v, 16);
+        v += __shfl_xor(v, 32);
+        if (g == 0) vec[4 * kH + k] = v;
     }
-    __syncthreads();
-    if (threadIdx.x < 4 * kH) {
-        float a = 0.f;
-        for (int w = 0; w < 4; ++w) a += sVec[w][threadIdx.x];
-        out[oW1 + threadIdx.x] = a;
-    }
-    __syncthreads();
-    if (g == 0) {
 #pragma unroll
-        for (int kt = 0; kt < 4; ++kt) {
-            const int k = 16 * kt + c;
-            sVec[wave][k] = vec[16 + kt];
-            sVec[wave][kH + k] = vec[20 + kt];
-            sVec[wave][2 * kH + k] = vec[24 + kt];
+    for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int n = 16 * nt + 4 * g + q;
+            const float v2 = row16_total(db2[nt][q]), v3 = row16_total(dW3[nt][q]);
+            if (c == 15) {
+                vec[5 * kH + n] = v2;
+                vec[6 * kH + n] = v3;
+            }
         }
+    for (int off = 8; off > 0; off >>= 1) {   // lanes of group 0 hold the rows' sums
+        db3 += __shfl_xor(db3, off);
+        loss += __shfl_xor(loss, off);
     }
     if (lane == 0) {
-        sVec[wave][4 * kH] = b3s;
+        sB3[wave] = db3;
         sLoss[wave] = loss;
     }
     __syncthreads();
-    if (threadIdx.x < 3 * kH) {
-        float a = 0.f;
-        for (int w = 0; w < 4; ++w) a += sVec[w][threadIdx.x];
-        const int which = threadIdx.x / kH, k = threadIdx.x % kH;
-        out[(which == 0 ? ob1 : which == 1 ? ob2 : oW3) + k] = a;
+    for (int v = threadIdx.x; v < 7 * kH; v += kMlpBlock) {
+        const float a = (sVec[0][v] + sVec[1][v]) + (sVec[2][v] + sVec[3][v]);
+        const int at = v < 5 * kH ? v : v < 6 * kH ? ob2 + v - 5 * kH : oW3 + v - 6 * kH;
+        static_assert(oW1 == 0 && ob1 == 4 * kH, "W1 and b1 lead the parameters");
+        out[at] = a;
     }
     if (threadIdx.x == 0) {
-        out[ob3] = sVec[0][4 * kH] + sVec[1][4 * kH] + sVec[2][4 * kH] + sVec[3][4 * kH];
-        loss_part[blockIdx.x] = sLoss[0] + sLoss[1] + sLoss[2] + sLoss[3];
+        out[ob3] = (sB3[0] + sB3[1]) + (sB3[2] + sB3[3]);
+        loss_part[blockIdx.x] = (sLoss[0] + sLoss[1]) + (sLoss[2] + sLoss[3]);
     }
 }
 
-// grad[p] = sum over blocks (fixed order); optional Adam update of the FP32 masters.
+// grad[p] = sum over blocks (fixed order); optional Adam update of the FP32 masters.  A
+// workgroup takes kRedParams parameters, kRedParts threads each summing every
+// kRedParts-th partial (loads of 128 contiguous bytes, eight in flight), so that 143
+// workgroups share what was a serial sum of all partials in 18: 31 -> 4.2 us for 65,536 rows.
+// loss (optional): the mean squared error from the partial sums, by workgroup 0.
+constexpr int kRedParams = 32, kRedParts = 8;
+
 __global__ __launch_bounds__(256) void k_mlp_reduce_adam(const float* __restrict__ part, int n_blocks,
                                                          float* __restrict__ grad, float* __restrict__ P,
                                                          float* __restrict__ m, float* __restrict__ v, int adam,
-                                                         float lr, float b1, float b2, float eps, float bc1,
-                                                         float bc2) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= kNP) return;
+                                                         float lr, float b1, float b2, float eps, float bc1, float bc2,
+                                                         const double* __restrict__ loss_part, double inv_n,
+                                                         double* __restrict__ loss) {
+    static_assert(kRedParams * kRedParts == 256, "one thread per parameter and share");
+    __shared__ float s_sum[kRedParts][kRedParams];
+    __shared__ double s_loss[4];
+    const int k = threadIdx.x % kRedParams, q = threadIdx.x / kRedParams;
+    const int p = blockIdx.x * kRedParams + k;
+    float a = 0.f;
+    if (p < kNP) {
+#pragma unroll 8
+        for (int b = q; b < n_blocks; b += kRedParts) a += part[(size_t)b * kNP + p];
+    }
+    s_sum[q][k] = a;
+    if (loss && blockIdx.x == 0) {
+        double l = 0.0;
+        for (int b = threadIdx.x; b < n_blocks; b += 256) l += loss_part[b];
+        for (int off = 32; off > 0; off >>= 1) l += __shfl_xor(l, off);
+        if ((threadIdx.x & 63) == 0) s_loss[threadIdx.x >> 6] = l;
+    }
+    __syncthreads();
+    if (loss && blockIdx.x == 0 && threadIdx.x == 0) loss[0] = ((s_loss[0] + s_loss[1]) + (s_loss[2] + s_loss[3])) * inv_n;
+    if (q != 0 || p >= kNP) return;
     float s = 0.f;
-    for (int b = 0; b < n_blocks; ++b) s += part[(size_t)b * kNP + p];
+#pragma unroll
+    for (int w = 0; w < kRedParts; ++w) s += s_sum[w][k];
     if (grad) grad[p] = s;
     if (adam) {
         const float mm = b1 * m[p] + (1.f - b1) * s;
@@ -378,15 +407,6 @@ __global__ __launch_bounds__(256) void k_mlp_reduce_adam(const float* __restrict
         v[p] = vv;
         P[p] -= lr * (mm / bc1) / (sqrtf(vv / bc2) + eps);
     }
-}
-
-// Mean squared error from the per-workgroup sums of k_mlp_grad (fixed order, one thread).
-__global__ __launch_bounds__(64) void k_mlp_loss_sum(const double* __restrict__ loss_part, int n_blocks, double inv_n,
-                                                     double* __restrict__ loss) {
-    if (threadIdx.x != 0) return;
-    double a = 0.0;
-    for (int b = 0; b < n_blocks; ++b) a += loss_part[b];
-    loss[0] = a * inv_n;
 }
 
 // Per-edge features over the interior edges: e / s_e, (e - e_prev) / s_d,
@@ -520,12 +540,12 @@ __global__ __launch_bounds__(256) void k_mlp_target_scale(int64_t n, int nb, con
 }  // namespace
 
 // ------------------------------------------------------------------------- launchers
+// One workgroup per tile of 128 rows up to one per CU (every workgroup writes and the
+// reduction reads 18 KB of partial sums).
+constexpr int kMaxGradGrid = 256;
 int mlp_grad_blocks(int64_t n) {
-    const int64_t tiles = (n + 31) / 32;
-    int64_t b = (tiles + 15) / 16;  // about 4 tiles per wave
-    if (b < 1) b = 1;
-    if (b > 512) b = 512;
-    return (int)b;
+    const int64_t tiles = (n + kTileRows - 1) / kTileRows;
+    return (int)std::min<int64_t>(std::max<int64_t>(tiles, 1), kMaxGradGrid);
 }
 
 void mlp_launch_rms(hipStream_t s, int64_t n_int, const int32_t* ie, const double* e, const double* ep,
@@ -576,14 +596,11 @@ void mlp_launch_grad(hipStream_t s, const float* X, const float* T, int64_t n, i
     hipLaunchKernelGGL(k_mlp_grad, dim3(blocks), dim3(kMlpBlock), 0, s, src, 1.0f / (float)n, P, part, loss_part);
 }
 
-void mlp_launch_loss_sum(hipStream_t s, const double* loss_part, int blocks, double inv_n, double* loss) {
-    hipLaunchKernelGGL(k_mlp_loss_sum, dim3(1), dim3(64), 0, s, loss_part, blocks, inv_n, loss);
-}
-
 void mlp_launch_reduce_adam(hipStream_t s, const float* part, int blocks, float* grad, float* P, float* m, float* v,
-                            int adam, float lr, float b1, float b2, float eps, float bc1, float bc2) {
-    hipLaunchKernelGGL(k_mlp_reduce_adam, dim3((kNP + 255) / 256), dim3(256), 0, s, part, blocks, grad, P, m, v, adam,
-                       lr, b1, b2, eps, bc1, bc2);
+                            int adam, float lr, float b1, float b2, float eps, float bc1, float bc2,
+                            const double* loss_part, double inv_n, double* loss) {
+    hipLaunchKernelGGL(k_mlp_reduce_adam, dim3((kNP + kRedParams - 1) / kRedParams), dim3(256), 0, s, part, blocks, grad, P,
+                       m, v, adam, lr, b1, b2, eps, bc1, bc2, loss_part, inv_n, loss);
 }
 
 }  // namespace fepic

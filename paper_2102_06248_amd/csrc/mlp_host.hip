@@ -17,44 +17,12 @@ int mlp_grad_blocks(int64_t n);
 void mlp_launch_grad(hipStream_t s, const float* X, const float* T, int64_t n, int64_t n_all, uint64_t seed,
                      const float* P, float* part, double* loss_part, int blocks);
 void mlp_launch_reduce_adam(hipStream_t s, const float* part, int blocks, float* grad, float* P, float* m, float* v,
-                            int adam, float lr, float b1, float b2, float eps, float bc1, float bc2);
-void mlp_launch_loss_sum(hipStream_t s, const double* loss_part, int blocks, double inv_n, double* loss);
+                            int adam, float lr, float b1, float b2, float eps, float bc1, float bc2,
+                            const double* loss_part = nullptr, double inv_n = 0.0, double* loss = nullptr);
 
 constexpr int kNP = FEPIC_MLP_N_PARAMS;
 constexpr double kMaxTargetRms = 10.0;   // recorded steps: RMS of (e^{n+1} - e^n) / s_d at most this
-constexpr int kMaxGradBlocks = 512;
-
-// ---- scratch of the allocation-free gradient (fepic_mlp_grad_noalloc)
-// The per-workgroup partial gradients (kNP floats each) and partial squared errors of
-// k_mlp_grad, for at most kNoAllocBlocks workgroups: mlp_grad_blocks(n) <= 128 exactly
-// when n <= FEPIC_MLP_NOALLOC_MAX_ROWS, so the allocation-free call launches the same grid
-// as fepic_mlp_grad and sums in the same order.  Every workgroup overwrites its whole
-// slice, so nothing needs clearing between calls.  One copy per GPU, for the life of the
-// process.
-constexpr int kNoAllocBlocks = 128;
-constexpr size_t kScratchGradBytes = sizeof(float) * (size_t)kNP * kNoAllocBlocks;
-constexpr size_t kScratchBytes = kScratchGradBytes + sizeof(double) * kNoAllocBlocks;
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
-
-// Device address of scratch on each GPU (the array's name is only a host-side handle).
-constexpr int kMaxScratchDevices = 64;
-static void* g_scratch_addr[kMaxScratchDevices] = {};
-static hipError_t g_scratch_err[kMaxScratchDevices] = {};
-static std::mutex g_scratch_mu;
-
-// Called by fepic_create with the context's device current: looks the array's address up
-// once per device.
-void mlp_noalloc_setup(int device) {
-    if (device < 0 || device >= kMaxScratchDevices) return;
-    std::lock_guard<std::mutex> lock(g_scratch_mu);
-    if (g_scratch_addr[device]) return;
-    void* p = nullptr;
-    const hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
-    if (e == hipSuccess && p) g_scratch_addr[device] = p;
-    else g_scratch_err[device] = (e == hipSuccess ? hipErrorInvalidSymbol : e);
-}
-
-static_assert(FEPIC_MLP_NOALLOC_MAX_ROWS == 32 * 16 * kNoAllocBlocks, "grid of the allocation-free gradient");
+constexpr int kMaxGradBlocks = 256;
 
 struct MlpState {
     float* P = nullptr;      // FP32 master weights
@@ -63,6 +31,8 @@ struct MlpState {
     float* grad = nullptr;
     float* part = nullptr;   // [kMaxGradBlocks][kNP]
     double* loss_part = nullptr;
+    float* na_part = nullptr;        // the same for the allocation-free gradient, which may
+    double* na_loss_part = nullptr;  // run on a stream of its own: [kMaxGradBlocks]
     double* scales = nullptr;  // s_d, s_g, line step, target RMS, s_e of the current step
     float* Xcur = nullptr;   // features of the current step [n_int][4]
     float* ycur = nullptr;
@@ -92,11 +62,13 @@ static int ensure_mlp(fepic_ctx* c) {
     s->grad = (float*)dmalloc(c, sizeof(float) * kNP);
     s->part = (float*)dmalloc(c, sizeof(float) * kNP * kMaxGradBlocks);
     s->loss_part = (double*)dmalloc(c, sizeof(double) * std::max(kMaxGradBlocks, 3 * 256));   // also the RMS partials
+    s->na_part = (float*)dmalloc(c, sizeof(float) * kNP * kMaxGradBlocks);
+    s->na_loss_part = (double*)dmalloc(c, sizeof(double) * kMaxGradBlocks);
     s->scales = (double*)dmalloc(c, sizeof(double) * 5);  // s_d, s_g, line step, target RMS, s_e
     s->Xcur = (float*)dmalloc(c, sizeof(float) * 4 * ni);
     s->ycur = (float*)dmalloc(c, sizeof(float) * ni);
     c->mlp = s;
-    if (!s->P || !s->m || !s->v || !s->grad || !s->part || !s->loss_part || !s->scales || !s->Xcur || !s->ycur)
+    if (!s->P || !s->m || !s->v || !s->grad || !s->part || !s->loss_part || !s->na_part || !s->na_loss_part || !s->scales || !s->Xcur || !s->ycur)
         return fail(c, FEPIC_E_OOM, "device allocation failed");
     return FEPIC_OK;
 }
@@ -235,7 +207,7 @@ static int eval_loss(fepic_ctx* c, const float* X, const float* T, int64_t n, do
         *loss = 0.0;
         return FEPIC_OK;
     }
-    const int blocks = std::min(mlp_grad_blocks(n), kMaxGradBlocks);
+    const int blocks = mlp_grad_blocks(n);
     mlp_launch_grad(c->stream, X, T, n, 0, 0, s->P, s->part, s->loss_part, blocks);
     std::vector<double> lp(blocks);
     HIPCHK_RET(c, hipMemcpyAsync(lp.data(), s->loss_part, sizeof(double) * blocks, hipMemcpyDeviceToHost, c->stream));
@@ -334,7 +306,7 @@ int fepic_ws_train(fepic_ctx* c, const fepic_train_opts* o, fepic_train_stats* o
     const float* Tva = s->Trec + (size_t)n_tr;
     const int64_t batch = (o->batch / 64) * 64;
     const int64_t steps_per_epoch = std::max<int64_t>(1, n_tr / batch);
-    const int blocks = std::min(mlp_grad_blocks(batch), kMaxGradBlocks);
+    const int blocks = mlp_grad_blocks(batch);
     const float b1 = (float)(o->beta1 > 0 ? o->beta1 : 0.9), b2 = (float)(o->beta2 > 0 ? o->beta2 : 0.999);
     const float eps = (float)(o->eps > 0 ? o->eps : 1e-8);
     int64_t steps = 0;
@@ -446,19 +418,11 @@ int fepic_mlp_grad_noalloc(fepic_ctx* c, int64_t n, const float* X, const float*
                         std::to_string(FEPIC_MLP_NOALLOC_MAX_ROWS));
     if (!c->mlp || !c->mlp->have_weights)
         return fail(c, FEPIC_E_STATE, "fepic_mlp_grad_noalloc: no network weights (set or train them first)");
-    const int dev = c->opt.device;
-    void* base = (dev >= 0 && dev < kMaxScratchDevices) ? g_scratch_addr[dev] : nullptr;
-    if (!base) {
-        const hipError_t e = (dev >= 0 && dev < kMaxScratchDevices) ? g_scratch_err[dev] : hipErrorInvalidDevice;
-        return hip_fail(c, e == hipSuccess ? hipErrorInvalidSymbol : e, "hipGetSymbolAddress(scratch)");
-    }
     const int blocks = mlp_grad_blocks(n);
-    if (blocks > kNoAllocBlocks) return fail(c, FEPIC_E_ARG, "fepic_mlp_grad_noalloc: grid exceeds the scratch");
-    float* part = (float*)base;
-    double* loss_part = (double*)((unsigned char*)base + kScratchGradBytes);
-    mlp_launch_grad(c->stream, X, t, n, 0, 0, c->mlp->P, part, loss_part, blocks);
-    mlp_launch_reduce_adam(c->stream, part, blocks, grad, nullptr, nullptr, nullptr, 0, 0.f, 0.f, 0.f, 0.f, 1.f, 1.f);
-    mlp_launch_loss_sum(c->stream, loss_part, blocks, 1.0 / (double)n, loss);
+    MlpState* s = c->mlp;
+    mlp_launch_grad(c->stream, X, t, n, 0, 0, s->P, s->na_part, s->na_loss_part, blocks);
+    mlp_launch_reduce_adam(c->stream, s->na_part, blocks, grad, nullptr, nullptr, nullptr, 0, 0.f, 0.f, 0.f, 0.f, 1.f, 1.f,
+                           s->na_loss_part, 1.0 / (double)n, loss);
     HIPCHK_RET(c, hipGetLastError());
     return FEPIC_OK;
 }
@@ -470,7 +434,7 @@ int fepic_mlp_grad(fepic_ctx* c, int64_t n, const float* X, const float* t, floa
     if (!c->mlp->have_weights) return fail(c, FEPIC_E_STATE, "no weights");
     if ((rc = host_batch(c, n, X, t))) return rc;
     MlpState* s = c->mlp;
-    const int blocks = std::min(mlp_grad_blocks(n), kMaxGradBlocks);
+    const int blocks = mlp_grad_blocks(n);
     mlp_launch_grad(c->stream, s->Xh, s->Th, n, 0, 0, s->P, s->part, s->loss_part, blocks);
     mlp_launch_reduce_adam(c->stream, s->part, blocks, s->grad, s->P, s->m, s->v, 0, 0.f, 0.f, 0.f, 0.f, 1.f, 1.f);
     std::vector<double> lp(blocks);
