@@ -55,10 +55,11 @@ struct PArrays {
 // (capacity = its grid * 256), with the per-workgroup counts in wg_count.
 template <typename T>
 struct CrossQueue {
-    double *l0, *l1, *l2, *l3;  // barycentric start in the entered tet
+    double *l0, *l1, *l2, *l3;  // barycentric exit point in the tet it left
     double* frac;               // fraction of the step's displacement still to go
     T *dx0, *dx1, *dx2;         // the step's displacement
-    int32_t *idx, *tet, *entry; // particle slot, entered tet, its local index of the entry face
+    int32_t *idx, *tet, *entry; // particle slot, entered tet, local index of the face between
+                                // them in the entered tet (in the left one above bit 2)
     int32_t* wg_count;
 };
 

@@ -99,14 +99,6 @@ __device__ __forceinline__ void piece_current(double qw, const double s[4], cons
     for (int i = 0; i < 6; ++i) out[i] = qw * (s[LE_A[i]] * e[LE_B[i]] - e[LE_A[i]] * s[LE_B[i]]);
 }
 
-__device__ __forceinline__ double pick4(int idx, const double v[4]) {
-    double r = v[3];
-    r = (idx == 2) ? v[2] : r;
-    r = (idx == 1) ? v[1] : r;
-    r = (idx == 0) ? v[0] : r;
-    return r;
-}
-
 // First exit of a straight piece from barycentric point ls along dl (d lambda over the
 // rest of the step): the smallest ls_k / (-dl_k) over faces with dl_k < 0, other than the
 // entry face; kb = -1 if the piece ends inside (t* >= 1).  Ties go to the smallest k.
@@ -132,13 +124,17 @@ __device__ __forceinline__ void exit_search(const double ls[4], const double dl[
 
 // Barycentric coordinates in the neighbour across the face opposite local kb, whose far
 // vertex is its local q: shared vertices keep their relative order (both tets are sorted
-// by node id), so new local k != q takes old local index r + (r >= kb), r = k - (k > q).
+// by node id), so the three others close up over kb and open again at q.  Both moves are
+// selects between neighbouring registers: picking by a computed index sent the four
+// coordinates through scratch memory.
 __device__ __forceinline__ void enter_neighbour(const double le[4], int kb, int q, double ln[4]) {
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int r = k - (k > q ? 1 : 0);
-        ln[k] = (k == q) ? 0.0 : pick4(r + (r >= kb ? 1 : 0), le);
-    }
+    const double c0 = kb <= 0 ? le[1] : le[0];
+    const double c1 = kb <= 1 ? le[2] : le[1];
+    const double c2 = kb <= 2 ? le[3] : le[2];
+    ln[0] = q == 0 ? 0.0 : c0;
+    ln[1] = q == 1 ? 0.0 : (q < 1 ? c0 : c1);
+    ln[2] = q == 2 ? 0.0 : (q < 2 ? c1 : c2);
+    ln[3] = q == 3 ? 0.0 : c2;
 }
 
 template <typename T>
@@ -263,38 +259,40 @@ constexpr int log2_const(int v) { return v <= 1 ? 0 : 1 + log2_const(v / 2); }
 // Segmented inclusive sums across the wave of N doubles, a segment starting at every lane
 // with f != 0 (lane 0 always starts one): after it, the last lane of each segment holds the
 // segment's sum.  Steps of the Hillis-Steele scan by DPP moves: row shifts by 1, 2, 4 and 8
-// inside each row of 16 lanes, then the rows' running sums carried across by broadcasting
-// lane 15 (into rows 1 and 3) and lane 31 (into rows 2 and 3).  Lanes without a source
-// receive zeros, which neither add nor end a segment.  VALU moves, where shuffles would
-// be LDS permutes.  Every lane of the wave must take part.
-template <int kCtrl, int kRowMask>
+// inside each row of 16 lanes (lanes without a source receive zeros, which neither add nor
+// end a segment), then the rows' running sums carried across by broadcasting lane 15 (taken
+// by rows 1 and 3) and lane 31 (taken by rows 2 and 3).  VALU moves, where shuffles would be
+// LDS permutes; the lanes that take a value are chosen by the add's own predicate, not by
+// a row mask, which would have the move's destination cleared first (72 moves of a push).
+// Every lane of the wave must take part.
+template <int kCtrl>
 __device__ __forceinline__ int dpp_i32(int v) {
-    return __builtin_amdgcn_update_dpp(0, v, kCtrl, kRowMask, 0xf, true);
+    return __builtin_amdgcn_mov_dpp(v, kCtrl, 0xf, 0xf, true);
 }
 
-template <int N, int kCtrl, int kRowMask>
-__device__ __forceinline__ void seg_step(double v[N], int& f) {
+template <int N, int kCtrl>
+__device__ __forceinline__ void seg_step(double v[N], int& f, bool take) {
     double o[N];
 #pragma unroll
     for (int c = 0; c < N; ++c)
-        o[c] = __hiloint2double(dpp_i32<kCtrl, kRowMask>(__double2hiint(v[c])),
-                                dpp_i32<kCtrl, kRowMask>(__double2loint(v[c])));
-    const int fo = dpp_i32<kCtrl, kRowMask>(f);
-    if (!f) {
+        o[c] = __hiloint2double(dpp_i32<kCtrl>(__double2hiint(v[c])), dpp_i32<kCtrl>(__double2loint(v[c])));
+    const int fo = dpp_i32<kCtrl>(f);
+    if (take && !f) {
 #pragma unroll
         for (int c = 0; c < N; ++c) v[c] += o[c];
     }
-    f |= fo;
+    if (take) f |= fo;
 }
 
 template <int N>
 __device__ __forceinline__ void seg_sum_wave(double v[N], int f) {
-    seg_step<N, 0x111, 0xf>(v, f);   // row_shr:1
-    seg_step<N, 0x112, 0xf>(v, f);   // row_shr:2
-    seg_step<N, 0x114, 0xf>(v, f);   // row_shr:4
-    seg_step<N, 0x118, 0xf>(v, f);   // row_shr:8
-    seg_step<N, 0x142, 0xa>(v, f);   // row_bcast:15
-    seg_step<N, 0x143, 0xc>(v, f);   // row_bcast:31
+    const int lane = threadIdx.x & 63;
+    seg_step<N, 0x111>(v, f, true);   // row_shr:1
+    seg_step<N, 0x112>(v, f, true);   // row_shr:2
+    seg_step<N, 0x114>(v, f, true);   // row_shr:4
+    seg_step<N, 0x118>(v, f, true);   // row_shr:8
+    seg_step<N, 0x142>(v, f, (lane & 16) != 0);   // row_bcast:15
+    seg_step<N, 0x143>(v, f, (lane & 32) != 0);   // row_bcast:31
 }
 
 // The six edge currents of one piece into the deterministic mode's accumulators.
@@ -373,6 +371,22 @@ __device__ __forceinline__ void walk_rest(PArrays<T>& out, int64_t i, int t, int
     }
 }
 
+// walk_rest for a slot of the crossing queue: its exit point is entered into the neighbour's
+// coordinates here, where only the crossing paths' waves do it.
+template <typename T, int kBits>
+__device__ __forceinline__ void walk_queued(PArrays<T>& out, const CrossQueue<T>& cq, int64_t slot,
+                                            const TetBlock<T>* __restrict__ blk, double* __restrict__ dg,
+                                            const PushParams& pp, int* s_key, double* s_val, unsigned int& nc,
+                                            unsigned int& na, unsigned int& ncap) {
+    const double le[4] = {cq.l0[slot], cq.l1[slot], cq.l2[slot], cq.l3[slot]};
+    const T dx[3] = {cq.dx0[slot], cq.dx1[slot], cq.dx2[slot]};
+    const int code = cq.entry[slot], q = code & 3;
+    double ls[4];
+    enter_neighbour(le, code >> 2, q, ls);
+    walk_rest<T, kBits>(out, cq.idx[slot], cq.tet[slot], q, ls, cq.frac[slot], dx, blk, dg, pp, s_key, s_val, nc, na,
+                        ncap);
+}
+
 // The particle step: gather E and B in the particle's tet, relativistic Boris, and the
 // straight path up to its first face crossing (or its end).  With kFused the crossing
 // paths are walked to their end here; otherwise they are compacted, per workgroup, into
@@ -382,6 +396,11 @@ __device__ __forceinline__ void walk_rest(PArrays<T>& out, int64_t i, int t, int
 // and walk pieces go through the workgroup's LDS table, flushed with one FP64 atomic per
 // edge, in the queue form each run adds its six sums with FP64 atomics.  kDet (fused form
 // only): every lane adds its own pieces to the fixed-point accumulators, no table.
+// Bound by the chain particle words -> tet record -> atomics at 8 waves per SIMD, with the
+// vector units issuing about 60% of the time; so instructions still count, and what only
+// crossing paths need (entering the neighbour's coordinates) is left to k_cross.  FP32,
+// queue form, 509 vector instructions against 631: 2M particles 51.1 -> 48.3 us (2.3 TB/s);
+// fused form, 1.6M 70.5 -> 64.1 us.
 template <typename T, bool kFused, int kPB, bool kDet = false>
 __global__ __launch_bounds__(kPB) __attribute__((amdgpu_waves_per_eu(kFused ? walk_waves<T>() : 1, 8))) void k_push(PArrays<T> in, PArrays<T> out, int64_t n,
                                                   const TetBlock<T>* __restrict__ blk, double* __restrict__ dg,
@@ -403,43 +422,52 @@ __global__ __launch_bounds__(kPB) __attribute__((amdgpu_waves_per_eu(kFused ? wa
         }
         __syncthreads();
     }
-    const int64_t i = (int64_t)blockIdx.x * kPB + threadIdx.x;
+    // slots relative to the workgroup's first: one scalar base per array, small offsets
+    const int64_t base = (int64_t)blockIdx.x * kPB;
+    const unsigned j = threadIdx.x;
     const int lane = threadIdx.x & 63;
     if (n_live) n = min(n, (int64_t)*n_live);
+    const bool have = base + j < n;
+    const auto at = [&](auto* a) { return a + base; };
     // the particle's own words are loaded together with its tet index (one memory round
     // trip before the tet record's), whether or not the particle is live
     int t0 = -1;
     T l1 = T(0), l2 = T(0), l3 = T(0), u[3] = {T(0), T(0), T(0)};
-    if (i < n) {
-        t0 = in.tet[i];
-        l1 = in.l1[i];
-        l2 = in.l2[i];
-        l3 = in.l3[i];
-        u[0] = in.u0[i];
-        u[1] = in.u1[i];
-        u[2] = in.u2[i];
+    if (have) {
+        t0 = at(in.tet)[j];
+        l1 = at(in.l1)[j];
+        l2 = at(in.l2)[j];
+        l3 = at(in.l3)[j];
+        u[0] = at(in.u0)[j];
+        u[1] = at(in.u1)[j];
+        u[2] = at(in.u2)[j];
     }
     double first[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     int status = 0;       // 1 absorbed, 2 crossing cap
     bool cross = false;   // continues in k_cross
-    double ln[4] = {0.0, 0.0, 0.0, 0.0}, frac = 0.0;
+    double le[4] = {0.0, 0.0, 0.0, 0.0}, frac = 0.0;   // where the first piece ends, of the rest
     T dx[3] = {T(0), T(0), T(0)};
-    int tn = 0, q = 0;
+    int tn = 0, q = 0, kb = -1;
     int o_tet = -1;       // the slot's tet after this kernel
     if (t0 >= 0) {
         const TetBlock<T>* bp = blk + t0;
         T g[4][3];
         load_grads(bp, g);
-        // gather: E = sum over edges e_ab (lambda_a grad l_b - lambda_b grad l_a)
+        // gather: E = sum over edges e_ab (lambda_a grad l_b - lambda_b grad l_a) = sum over
+        // vertices c_v grad l_v, with grad l_0 = -(the others): 24 multiply-adds, not 54
         const T lam[4] = {T(1) - l1 - l2 - l3, l1, l2, l3};
-        T E[3] = {T(0), T(0), T(0)};
+        T cv[4] = {T(0), T(0), T(0), T(0)};
 #pragma unroll
         for (int k = 0; k < 6; ++k) {
             const T ek = bp->e[k];
             const int a = LE_A[k], b = LE_B[k];
-#pragma unroll
-            for (int d = 0; d < 3; ++d) E[d] += ek * (lam[a] * g[b][d] - lam[b] * g[a][d]);
+            cv[b] += ek * lam[a];
+            cv[a] -= ek * lam[b];
         }
+        T E[3];
+#pragma unroll
+        for (int d = 0; d < 3; ++d)
+            E[d] = (cv[1] - cv[0]) * g[1][d] + (cv[2] - cv[0]) * g[2][d] + (cv[3] - cv[0]) * g[3][d];
         const T Bv[3] = {bp->B[0], bp->B[1], bp->B[2]};
         // relativistic Boris: half kick, rotation, half kick
         const T h = (T)pp.qm_half_dt;
@@ -464,9 +492,7 @@ __global__ __launch_bounds__(kPB) __attribute__((amdgpu_waves_per_eu(kFused ? wa
         double dl[4];
         path_step(g, dx, 1.0, dl);
         double best;
-        int kb;
         exit_search(ls, dl, -1, best, kb);
-        double le[4];
         if (kb < 0) {
             T r[3];
             end_point(ls, dl, r, le);
@@ -488,7 +514,6 @@ __global__ __launch_bounds__(kPB) __attribute__((amdgpu_waves_per_eu(kFused ? wa
                 cross = true;
                 tn = nb >> 2;
                 q = nb & 3;
-                enter_neighbour(le, kb, q, ln);
                 frac = 1.0 - best;
                 o_tet = tn;
             }
@@ -498,14 +523,14 @@ __global__ __launch_bounds__(kPB) __attribute__((amdgpu_waves_per_eu(kFused ? wa
     // whole cache lines: a path that goes on into another tet has its end written later (in
     // k_cross, or by the walk below); an absorbed or dead particle's words other than its
     // tet (-1) are never read.  The slot's id is kept: ids are not copied.
-    if (i < n) {
-        out.tet[i] = o_tet;
-        out.l1[i] = l1;
-        out.l2[i] = l2;
-        out.l3[i] = l3;
-        out.u0[i] = u[0];
-        out.u1[i] = u[1];
-        out.u2[i] = u[2];
+    if (have) {
+        at(out.tet)[j] = o_tet;
+        at(out.l1)[j] = l1;
+        at(out.l2)[j] = l2;
+        at(out.l3)[j] = l3;
+        at(out.u0)[j] = u[0];
+        at(out.u1)[j] = u[1];
+        at(out.u2)[j] = u[2];
     }
 
     // first-piece currents: one sum per run of lanes sharing a tet, added by the run's last
@@ -533,7 +558,11 @@ __global__ __launch_bounds__(kPB) __attribute__((amdgpu_waves_per_eu(kFused ? wa
     if (kFused) {
         // the rest of every crossing path here, currents through the LDS table
         unsigned int nc = 0, na = 0, ncap = 0;
-        if (cross) walk_rest<T, kBits, kDet>(out, i, tn, q, ln, frac, dx, blk, dg, pp, s_key, s_val, nc, na, ncap);
+        if (cross) {
+            double ln[4];
+            enter_neighbour(le, kb, q, ln);
+            walk_rest<T, kBits, kDet>(out, base + j, tn, q, ln, frac, dx, blk, dg, pp, s_key, s_val, nc, na, ncap);
+        }
         if constexpr (!kDet) {
             __syncthreads();
             flush_table<kSlots, kPB>(s_key, s_val, dg);
@@ -558,26 +587,25 @@ __global__ __launch_bounds__(kPB) __attribute__((amdgpu_waves_per_eu(kFused ? wa
             s_wc[w][2] = (int)__popcll(m_cap);
         }
         __syncthreads();
-        int base = 0, total = 0;
+        int first_rank = 0, total = 0;
 #pragma unroll
         for (int k = 0; k < kBlock / 64; ++k) {
-            base += (k < w) ? s_wc[k][0] : 0;
+            first_rank += (k < w) ? s_wc[k][0] : 0;
             total += s_wc[k][0];
         }
         if (cross) {
-            const int64_t slot =
-                (int64_t)blockIdx.x * kBlock + base + (int)__popcll(m & ((1ull << lane) - 1ull));
-            cq.l0[slot] = ln[0];
-            cq.l1[slot] = ln[1];
-            cq.l2[slot] = ln[2];
-            cq.l3[slot] = ln[3];
-            cq.frac[slot] = frac;
-            cq.dx0[slot] = dx[0];
-            cq.dx1[slot] = dx[1];
-            cq.dx2[slot] = dx[2];
-            cq.idx[slot] = (int32_t)i;
-            cq.tet[slot] = tn;
-            cq.entry[slot] = q;
+            const unsigned r = (unsigned)(first_rank + (int)__popcll(m & ((1ull << lane) - 1ull)));
+            at(cq.l0)[r] = le[0];
+            at(cq.l1)[r] = le[1];
+            at(cq.l2)[r] = le[2];
+            at(cq.l3)[r] = le[3];
+            at(cq.frac)[r] = frac;
+            at(cq.dx0)[r] = dx[0];
+            at(cq.dx1)[r] = dx[1];
+            at(cq.dx2)[r] = dx[2];
+            at(cq.idx)[r] = (int32_t)(base + j);
+            at(cq.tet)[r] = tn;
+            at(cq.entry)[r] = q | kb << 2;
         }
         if (threadIdx.x == 0) {
             cq.wg_count[blockIdx.x] = total;
@@ -626,12 +654,8 @@ __global__ __launch_bounds__(kB) __attribute__((amdgpu_waves_per_eu(walk_waves<T
     unsigned int sc = 0, mc = 0, na = 0, ncap = 0;
     for (int j = threadIdx.x; j < total; j += kB) {
         const int64_t slot = (int64_t)blockIdx.x * kBlock + j;
-        const int64_t i = cq.idx[slot];
-        double ls[4] = {cq.l0[slot], cq.l1[slot], cq.l2[slot], cq.l3[slot]};
-        const T dx[3] = {cq.dx0[slot], cq.dx1[slot], cq.dx2[slot]};
         unsigned int nc = 0;
-        walk_rest<T, kBits>(out, i, cq.tet[slot], cq.entry[slot], ls, cq.frac[slot], dx, blk, dg, pp, s_key, s_val, nc,
-                            na, ncap);
+        walk_queued<T, kBits>(out, cq, slot, blk, dg, pp, s_key, s_val, nc, na, ncap);
         sc += nc - 1;
         mc = max(mc, nc);
     }
@@ -668,12 +692,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(walk_waves<T
         const int total = b < r1 ? cq.wg_count[b] : 0;
         for (int j = 0; j < total; ++j) {
             const int64_t slot = b * kBlock + j;
-            const int64_t i = cq.idx[slot];
-            double ls[4] = {cq.l0[slot], cq.l1[slot], cq.l2[slot], cq.l3[slot]};
-            const T dx[3] = {cq.dx0[slot], cq.dx1[slot], cq.dx2[slot]};
             unsigned int nc = 0;
-            walk_rest<T, kBits>(out, i, cq.tet[slot], cq.entry[slot], ls, cq.frac[slot], dx, blk, dg, pp, s_key, s_val,
-                                nc, na, ncap);
+            walk_queued<T, kBits>(out, cq, slot, blk, dg, pp, s_key, s_val, nc, na, ncap);
             sc += nc - 1;
             mc = max(mc, nc);
         }
@@ -1191,13 +1211,16 @@ void launch_push(hipStream_t s, PArrays<T> in, PArrays<T> out, int64_t n, const 
                        cq);
     // a species whose paths rarely cross: resident one-wave workgroups visit the few
     // non-empty queue regions; otherwise one k_cross workgroup per k_push workgroup, sized
-    // for its expected queue length
+    // for its expected queue length: a width for the species' own crossings, so that a
+    // region's paths take one turn (4M electrons on 998k tets, 0.3 crossings each, or 77
+    // paths a region: 64 threads 207 us, 128 threads 197 us).  The share of all species
+    // together would halve the width where one of two species stands still
     if (own_share < kSparseShare)
         hipLaunchKernelGGL((k_cross_sparse<T>), dim3(std::min<unsigned>(n_wg, sparse_grid<T>())), dim3(64), 0, s, out,
                            cq, (int64_t)n_wg, blk, dg, pp, cnt);
-    else if (cross_share <= 0.25)
+    else if (own_share <= 0.25)
         hipLaunchKernelGGL((k_cross<T, 64>), dim3(n_wg), dim3(64), 0, s, out, cq, blk, dg, pp, cnt);
-    else if (cross_share <= 0.5)
+    else if (own_share <= 0.5)
         hipLaunchKernelGGL((k_cross<T, 128>), dim3(n_wg), dim3(128), 0, s, out, cq, blk, dg, pp, cnt);
     else
         hipLaunchKernelGGL((k_cross<T, 256>), dim3(n_wg), dim3(256), 0, s, out, cq, blk, dg, pp, cnt);
