@@ -160,6 +160,7 @@ int build_blocks(fepic_ctx* c, const SellMatrix& mat, const int64_t* sp, const i
     if (e != hipSuccess) return drop(hip_fail(c, e, "row block counts"));
     int most = 1;
     for (int32_t n : h) most = std::max(most, n);
+    g.wide = std::any_of(h.begin(), h.end(), [](int32_t n) { return n < 0; });
     g.stride = (most + kBlockRows - 1) / kBlockRows * kBlockRows;
     halo = dalloc<int32_t>(c, g.nb * g.stride);
     lcol = dalloc<uint16_t>(c, mat.slice_ptr.back());
@@ -173,6 +174,10 @@ int build_blocks(fepic_ctx* c, const SellMatrix& mat, const int64_t* sp, const i
     for (const void* p : {(const void*)c->bc.cnt, (const void*)c->bc.halo, (const void*)c->bc.lcol})
         dfree(c, const_cast<void*>(p));
     c->bc = g;
+    int device = 0, n_cu = 0;
+    c->one_launch = hipGetDevice(&device) == hipSuccess &&
+                    hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess &&
+                    cg_solve_fits(g, n_cu);
     return FEPIC_OK;
 }
 
@@ -796,6 +801,52 @@ bool mlp_start_rejected(int mode, double rr0, double bb) {
     return false;
 }
 
+// A Jacobi solve from launch_cg_init's state in one launch, if every row block has a resident
+// workgroup: *solved, with the scalars on the host.  Not solved, the iterations are launched
+// one by one: the meshes are too large, there is no memory for the exchange (8 words a row),
+// or the launch was refused, V and x as they were; or the workgroups gave up waiting for each
+// other (h_sc->converged is 3 then), x some iterate.  The context does not try again after
+// either of the last two.
+int solve_one_launch(fepic_ctx* c, const CgVec* V, int n_max, bool* solved) {
+    *solved = false;
+    c->h_sc->converged = 0;
+    if (!c->one_launch || n_max <= 0) return FEPIC_OK;
+    const int64_t n = cg_solve_boxes(c->bc);
+    bool fresh = (uint64_t)c->box_tag + (uint64_t)n_max > 0xffffffffull;
+    if (c->n_boxes != n) {
+        dfree(c, c->d_boxes);
+        c->n_boxes = 0;
+        c->d_boxes = dalloc<unsigned long long>(c, n);
+        if (!c->d_boxes) return FEPIC_OK;
+        c->n_boxes = n;
+        fresh = true;
+    }
+    if (fresh) {   // no word carries a tag from here on
+        HIPCHK(c, hipMemsetAsync(c->d_boxes, 0, sizeof(unsigned long long) * n, c->stream));
+        c->box_tag = 0;
+    }
+    hipEvent_t* ev = timer_pair(c, FAM_CG_ITER, 0);
+    if (ev) (void)hipEventRecord(ev[0], c->stream);
+    const hipError_t e = launch_cg_solve(c->stream, c->mesh.n_edges, n_max, c->d_sp, c->bc, c->d_A, c->d_x, V, c->d_boxes,
+                                         c->box_tag, c->d_partial, c->d_sc);
+    if (ev) (void)hipEventRecord(ev[1], c->stream);
+    if (e != hipSuccess) {
+        c->one_launch = false;
+        return FEPIC_OK;
+    }
+    HIPCHK(c, hipMemcpyAsync(c->h_sc, c->d_sc, sizeof(CgScalars), hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    *solved = c->h_sc->converged != 3;
+    if (!*solved) {
+        c->one_launch = false;
+        c->box_tag += (uint32_t)n_max;
+        return FEPIC_OK;
+    }
+    c->box_tag += (uint32_t)c->h_sc->iters;
+    if (ev) c->timers[FAM_CG_ITER].launches += c->h_sc->iters + 1;   // counted as the iterations it stands for
+    return FEPIC_OK;
+}
+
 // Field half: RHS, warm start, PCG, true residual, Faraday into d_bn.  Returns the
 // iteration count via the host scalars (stream synchronized at return).
 int field_phase(fepic_ctx* c, double dt, double beta, double gamma) {
@@ -983,7 +1034,13 @@ int field_phase(fepic_ctx* c, double dt, double beta, double gamma) {
                 if (rk != FEPIC_OK) return rk;
             }
             const int first = (restart == 0 && c->last_cg_iters > 0) ? std::max(batch, c->last_cg_iters + 2) : batch;
-            int rc = iterate(first, [&](int i) {
+            bool solved = false;
+            if (!aux) {
+                const int rs = solve_one_launch(c, V[0], maxit - total, &solved);
+                if (rs != FEPIC_OK) return rs;
+                if (!solved && c->h_sc->converged == 3) cg_init();   // it gave up: x is a start like another
+            }
+            int rc = solved ? FEPIC_OK : iterate(first, [&](int i) {
                 if (aux)
                     launch_pcg_iter(c->stream, i, ne, c->d_sp, c->d_col, c->bc, c->d_A, c->d_dinv, c->d_x, c->aux, ZP,
                                     c->d_rq, c->d_partial, c->d_sc);

@@ -118,6 +118,10 @@ struct fepic_ctx {
     int32_t *d_mf_col = nullptr, *d_ef_inc = nullptr;
     double *d_mf_val = nullptr, *d_h = nullptr;
     double *d_rhs = nullptr, *d_rt = nullptr, *d_Me = nullptr;
+    unsigned long long* d_boxes = nullptr;         // values exchanged within a one-launch Jacobi solve
+    int64_t n_boxes = 0;
+    uint32_t box_tag = 0;                          // last tag in use there
+    bool one_launch = false;                       // the row blocks are all resident at once
     fepic::CgVec* d_cgv[2] = {nullptr, nullptr};   // Jacobi-PCG state, double buffered
     // auxiliary-space PCG: (z, p) pairs double buffered, r and q (n_edges each), nodal arrays
     double2* d_zp[2] = {nullptr, nullptr};

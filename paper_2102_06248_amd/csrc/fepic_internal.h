@@ -209,6 +209,7 @@ struct DiagAcc {
 struct BlockCols {
     int64_t nb = 0, n_slices = 0;
     int stride = 0;                  // room per block in halo, a multiple of kBlockRows
+    bool wide = false;               // some block has cnt -1
     const int32_t* halo = nullptr;   // [nb][stride], padded with the block's first row
     const int32_t* cnt = nullptr;    // [nb] halo columns; -1: more than kHaloMax, the block's
                                      // rows gather from memory by their 32-bit columns
@@ -308,6 +309,14 @@ void launch_cg_init(hipStream_t s, int64_t n_rows, const int64_t* slice_ptr, con
 void launch_cg_iter(hipStream_t s, int i, int64_t n_rows, const int64_t* slice_ptr, const int32_t* col,
                     const BlockCols& bc, const double* A, double* x, CgVec* const v[2], double* partial,
                     CgScalars* sc, bool det = false);
+// A whole Jacobi solve in one launch: whether every row block has a resident workgroup, the
+// 64-bit words that the workgroups exchange values through, and the launch (from launch_cg_init's
+// state; tags tag0 + 1 .. tag0 + n_max must not be in the words yet).
+bool cg_solve_fits(const BlockCols& bc, int n_cu);
+int64_t cg_solve_boxes(const BlockCols& bc);
+hipError_t launch_cg_solve(hipStream_t s, int64_t n_rows, int n_max, const int64_t* sp, const BlockCols& bc,
+                           const double* A, double* x, const CgVec* V, unsigned long long* boxes, unsigned tag0,
+                           double* partial, CgScalars* sc);
 void launch_cg_rr0(hipStream_t s, int64_t n_rows, double* partial, CgScalars* sc);
 // Halo sizes of the row blocks into cnt (count), then halo lists and 16-bit columns (fill).
 void launch_block_count(hipStream_t s, const BlockCols& g, const int64_t* slice_ptr, const int32_t* col, int32_t* cnt);

@@ -970,6 +970,206 @@ __global__ __launch_bounds__(kBlockRows) void k_cg_iter(int64_t n_rows, RowGrid 
     block_slot_add<3, R>(v, cg_buf(cg_slots, i + 1));
 }
 
+// A double passed between workgroups of one running kernel: its halves as two 64-bit words,
+// each with the tag of the iteration it belongs to in the upper half.  A word is one atomic,
+// so a reader that sees the tags has the value, whatever the order in which stores arrive:
+// no fences, no cache write-backs, no flags.  Device scope: the words pass the XCDs' L2s.
+__device__ __forceinline__ void box_put(unsigned long long* p, double v, unsigned tag) {
+    const unsigned long long t = (unsigned long long)tag << 32;
+    __hip_atomic_store(p, t | (unsigned)__double2loint(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(p + 1, t | (unsigned)__double2hiint(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ unsigned long long box_word(const unsigned long long* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ bool box_has(unsigned long long a, unsigned tag) { return (unsigned)(a >> 32) == tag; }
+__device__ __forceinline__ double box_value(unsigned long long a, unsigned long long b) {
+    return __hiloint2double((int)(unsigned)b, (int)(unsigned)a);
+}
+
+// Polls of one wait before the solve gives up (a tenth of a second; a wait takes a few).
+constexpr int kSolvePolls = 1 << 17;
+// Copies of the workgroups' partials: every workgroup reads all of one, its XCD's.
+constexpr int kSolveCopies = 8;
+
+// A whole Jacobi-PCG solve in one launch, for matrices of which every row block has a
+// resident workgroup (launched cooperatively).  The same recurrence and block layout as
+// k_cg_iter; the matrix, the block's rows and the halo's (u, s), which the recurrences carry
+// along redundantly, stay in registers, so an iteration exchanges one value per row, D^-1 A u,
+// and three partial dots per workgroup.  Every workgroup sums all partials in one order (so
+// all take the same decisions, and the sums are the same in each run) and that wait is the
+// iteration's only grid-wide one.  The boxes are double buffered: a workgroup writes the
+// values of iterate i + 2 over those of i after it has seen every partial of i + 1, whose
+// writers had read theirs of i.
+// Bound by that exchange (a store and a load past the L2s, about 1.5 us) and the LDS reads of
+// the product; what grows with the mesh is the polling, so a lane polls only for what it
+// lacks, with all its loads in flight, and the partials lie in a copy per XCD.  Per iteration
+// against a launch of k_cg_iter: 1.1k rows 5.2 -> 2.8 us, 13k 6.5 -> 3.2, 37k 6.8 -> 3.8, 90k
+// 7.0 -> 4.6, 129k 7.4 -> 5.2 (registers capped for two workgroups per CU: 0.8 us more, by
+// spills).
+// Every wait is bounded: a workgroup that polls kSolvePolls times in vain sets converged to
+// 3 and leaves with x as it found it, the others follow in the same way, and the host solves
+// by k_cg_iter.
+// n_max: the iterate at which the solve stops unconverged.
+__global__ __launch_bounds__(kBlockRows) __attribute__((amdgpu_waves_per_eu(2))) void k_cg_solve(
+    int64_t n_rows, RowGrid rg, int n_max, const int64_t* __restrict__ sp, BlockCols bc, const double* __restrict__ A,
+    double* __restrict__ x, const CgVec* __restrict__ V, unsigned long long* __restrict__ boxes, unsigned tag0,
+    const double* __restrict__ cg_slots, CgScalars* sc) {
+    extern __shared__ double s_u[];
+    constexpr int R = kBlockRows, H = kHaloRegs, NW = R / 64;
+    __shared__ double s_dot[3][NW], s_own[3][NW];
+    __shared__ int s_fail;
+    const int64_t b = rg_first(rg);
+    if (b >= rg_end(rg)) return;   // the whole workgroup (the grid is a multiple of eight)
+    const int nb = (int)bc.nb, tid = threadIdx.x, wave = tid >> 6;
+    const int64_t row = b * R + tid, nr = (int64_t)nb * R;
+    // boxes: two buffers of a value per row, then two of the workgroups' three partials
+    auto w_box = [&](int buf, int64_t r) { return boxes + 2 * (buf * nr + r); };
+    auto p_box = [&](int buf, int copy, int k) {
+        return boxes + 4 * nr + 8 * (((int64_t)buf * kSolveCopies + copy) * nb + k);
+    };
+    BlockRow<double> P;
+    P.load(bc, b * (R / 64) + wave, sp, A);
+    const double tol2_bb = sc->tol2_bb, bb = sc->bb;
+    double t[3];
+    slot_load_wave<3>(cg_slots, t);
+    const int cnt = bc.cnt[b];
+    int h[H];
+    halo_ids(bc, b, h);
+    const int64_t r0 = row < n_rows ? row : 0;
+    double u = V[r0].R, w = V[r0].W, s = 0.0, p = 0.0, xr = x[r0];
+    double hu[H], hw[H], hs[H];
+#pragma unroll
+    for (int k = 0; k < H; ++k) {
+        hs[k] = hu[k] = hw[k] = 0.0;
+        if (k * R < bc.stride) {
+            hu[k] = V[h[k]].R;
+            hw[k] = V[h[k]].W;
+        }
+    }
+    if (tid == 0) s_fail = 0;
+    double g = wave_total(t[0]), d = wave_total(t[1]), rr = wave_total(t[2]);
+    const double rr0 = rr;
+    double gam_old = 0.0, alpha_old = 0.0;
+    int conv = 0, i = 0;
+    for (;; ++i) {
+        const bool done = !(rr > tol2_bb) || bb == 0.0;
+        const double beta = (i == 0) ? 0.0 : g / gam_old;
+        const double alpha = (i == 0) ? g / d : g / (d - beta * g / alpha_old);
+        const bool bad = !done && !(alpha > 0.0 && alpha < INFINITY && beta >= 0.0 && beta < INFINITY);
+        conv = done ? 1 : (bad ? 2 : 0);
+        if (conv || i >= n_max) break;
+        gam_old = g;
+        alpha_old = alpha;
+        s = __builtin_fma(beta, s, w);             // D^-1 s
+        p = __builtin_fma(beta, p, u);
+        xr = __builtin_fma(alpha, p, xr);
+        u = __builtin_fma(-alpha, s, u);           // D^-1 r'
+        s_u[tid] = u;
+#pragma unroll
+        for (int k = 0; k < H; ++k)
+            if (k * R < bc.stride) {
+                hs[k] = __builtin_fma(beta, hs[k], hw[k]);
+                hu[k] = __builtin_fma(-alpha, hs[k], hu[k]);
+                s_u[(k + 1) * R + tid] = hu[k];
+            }
+        __syncthreads();
+        const double acc = P.dot(bc, A, [&](unsigned c) { return s_u[c]; });
+        const unsigned tag = tag0 + (unsigned)(i + 1);
+        const int buf = (i + 1) & 1;
+        double v[3] = {0.0, 0.0, 0.0};
+        if (row < n_rows) {
+            const double diag = P.a[0], rn = u * diag;
+            w = acc / diag;
+            box_put(w_box(buf, row), w, tag);
+            v[0] = rn * u;
+            v[1] = u * acc;
+            v[2] = rn * rn;
+        }
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const double a = wave_total(v[j]);
+            if ((tid & 63) == 0) s_own[j][wave] = a;
+        }
+        __syncthreads();
+        if ((tid & 3) < 3 && tid < 4 * kSolveCopies) {
+            const int j = tid & 3, copy = tid >> 2;
+            double a = 0.0;
+#pragma unroll
+            for (int q = 0; q < NW; ++q) a += s_own[j][q];
+            box_put(p_box(buf, copy, (int)b) + 2 * j, a, tag);
+        }
+        // the partials of all workgroups, one per thread, and the halo's values: a round of
+        // polls has all its loads in flight together, and a lane with all it needs sits out
+        const unsigned long long *pa = p_box(buf, blockIdx.x % kSolveCopies, min(tid, nb - 1)), *ha[H];
+#pragma unroll
+        for (int k = 0; k < H; ++k) ha[k] = w_box(buf, k * R < bc.stride ? h[k] : row);
+        unsigned long long pw[6] = {0, 0, 0, 0, 0, 0}, hb[2 * H];
+        bool okp = tid >= nb, okh[H];
+#pragma unroll
+        for (int k = 0; k < H; ++k) okh[k] = k * R + tid >= cnt;
+#pragma unroll
+        for (int k = 0; k < 2 * H; ++k) hb[k] = 0;
+        for (int n = 0;; ++n) {
+            if (!okp) {
+#pragma unroll
+                for (int j = 0; j < 6; ++j) pw[j] = box_word(pa + j);
+            }
+#pragma unroll
+            for (int k = 0; k < H; ++k)
+                if (!okh[k]) {
+                    hb[2 * k] = box_word(ha[k]);
+                    hb[2 * k + 1] = box_word(ha[k] + 1);
+                }
+            if (!okp) {
+                okp = true;
+#pragma unroll
+                for (int j = 0; j < 6; ++j) okp = okp & box_has(pw[j], tag);
+            }
+            bool ok = okp;
+#pragma unroll
+            for (int k = 0; k < H; ++k) {
+                if (!okh[k]) okh[k] = box_has(hb[2 * k], tag) & box_has(hb[2 * k + 1], tag);
+                ok = ok & okh[k];
+            }
+            if (__all(ok)) break;
+            if (n >= kSolvePolls) {
+                if ((tid & 63) == 0) s_fail = 1;
+                break;
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 3; ++j) v[j] = tid < nb ? box_value(pw[2 * j], pw[2 * j + 1]) : 0.0;
+#pragma unroll
+        for (int k = 0; k < H; ++k)
+            if (k * R < bc.stride) hw[k] = box_value(hb[2 * k], hb[2 * k + 1]);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const double a = wave_total(v[j]);
+            if ((tid & 63) == 0) s_dot[j][wave] = a;
+        }
+        __syncthreads();
+        if (s_fail) {
+            if (tid == 0) sc->converged = 3;
+            return;
+        }
+        g = d = rr = 0.0;
+#pragma unroll
+        for (int q = 0; q < NW; ++q) {
+            g += s_dot[0][q];
+            d += s_dot[1][q];
+            rr += s_dot[2][q];
+        }
+    }
+    if (row < n_rows) x[row] = xr;
+    if (b == 0 && tid == 0) {
+        sc->rr = rr;
+        sc->rr0 = rr0;
+        sc->iters = i;
+        sc->converged = conv;
+    }
+}
+
 // ||b||^2 from the partials of the kernel that summed it (the right-hand side's, or the
 // true residual's for an inner solve); r = b - A x, or with zero_x r = b and x = 0 (the
 // inner solves start from zero); q = 0; clears the four reduction buffers and the far
@@ -1672,6 +1872,35 @@ void launch_cg_iter(hipStream_t s, int i, int64_t n_rows, const int64_t* sp, con
     const int a = i & 1, b = 1 - a;
     hipLaunchKernelGGL(k_cg_iter, dim3(rg.grid), dim3(kBlockRows), staged_bytes(bc, sizeof(double)), s, n_rows, rg, i, sp,
                        col, bc, A, x, v[a], v[b], partial + SLOT_CG * kSlot, sc);
+}
+
+int64_t cg_solve_boxes(const BlockCols& bc) { return bc.nb * (4 * kBlockRows + 16 * kSolveCopies); }
+
+// One workgroup per CU: 197k rows on two per CU took 18.4 us per iteration, against 11.9 by
+// k_cg_iter (129k rows, one per CU: 5.2 against 7.4).  Every halo column has a register
+// (kHaloRegs) and every partial a thread.
+bool cg_solve_fits(const BlockCols& bc, int n_cu) {
+    if (bc.nb <= 0 || bc.nb > kBlockRows || bc.wide || bc.stride > kHaloRegs * kBlockRows) return false;
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_cg_solve, kBlockRows,
+                                                     staged_bytes(bc, sizeof(double))) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return per_cu > 0 && (int64_t)block_grid(bc).grid <= n_cu;
+}
+
+hipError_t launch_cg_solve(hipStream_t s, int64_t n_rows, int n_max, const int64_t* sp, const BlockCols& bc,
+                           const double* A, double* x, const CgVec* V, unsigned long long* boxes, unsigned tag0,
+                           double* partial, CgScalars* sc) {
+    RowGrid rg = block_grid(bc);
+    BlockCols g = bc;
+    const double* slots = partial + SLOT_CG * kSlot;
+    void* args[] = {&n_rows, &rg, &n_max, &sp, &g, &A, &x, &V, &boxes, &tag0, &slots, &sc};
+    const hipError_t e = hipLaunchCooperativeKernel((const void*)k_cg_solve, dim3(rg.grid), dim3(kBlockRows), args,
+                                                    (unsigned)staged_bytes(bc, sizeof(double)), s);
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e;
 }
 
 // One workgroup per slice of 64 auxiliary nodes, consecutive slices on the same XCD.
