@@ -138,6 +138,17 @@ PArrays<T> parr_off(Species& s, int which, int64_t off) {
 
 size_t field_size(const fepic_ctx* c) { return c->opt.precision == FEPIC_ALL_FP64 ? 8 : 4; }
 
+// Compute units of the current device (0: unknown).
+int n_cu() {
+    int device = 0, n = 0;
+    if (hipGetDevice(&device) != hipSuccess ||
+        hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) {
+        (void)hipGetLastError();
+        return 0;
+    }
+    return n;
+}
+
 // The row blocks of the edge matrices' columns (slice pointers and columns on the device),
 // built there: counts, then lists and indices.  On failure c->bc is left as it was.
 int build_blocks(fepic_ctx* c, const SellMatrix& mat, const int64_t* sp, const int32_t* col) {
@@ -174,11 +185,50 @@ int build_blocks(fepic_ctx* c, const SellMatrix& mat, const int64_t* sp, const i
     for (const void* p : {(const void*)c->bc.cnt, (const void*)c->bc.halo, (const void*)c->bc.lcol})
         dfree(c, const_cast<void*>(p));
     c->bc = g;
-    int device = 0, n_cu = 0;
-    c->one_launch = hipGetDevice(&device) == hipSuccess &&
-                    hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess &&
-                    cg_solve_fits(g, n_cu);
+    c->one_launch = cg_solve_fits(g, n_cu());
     return FEPIC_OK;
+}
+
+// The lists of the one-launch solve with the auxiliary space to the device, and how many row
+// blocks its workgroups take; none if the mesh is past their limits or memory is short.
+void prepare_one_launch(fepic_ctx* c) {
+    c->solve_lists_tried = true;
+    const HostSolveLists m = build_solve_lists(c->mesh);
+    if (m.stride == 0) return;
+    int32_t *edge = nullptr, *cnt = nullptr, *xsp = nullptr, *node = nullptr, *n_node = nullptr, *agg = nullptr;
+    uint16_t *lc = nullptr, *xlc = nullptr;
+    uint8_t* node_agg = nullptr;
+    uint32_t* ends = nullptr;
+    int rc;
+    const std::string err = c->err;
+    if ((rc = upload(c, &edge, m.edge)) || (rc = upload(c, &cnt, m.cnt)) || (rc = upload(c, &xsp, m.xsp)) ||
+        (rc = upload(c, &node, m.node)) || (rc = upload(c, &n_node, m.n_node)) || (rc = upload(c, &agg, m.agg)) ||
+        (rc = upload(c, &lc, m.lc)) || (rc = upload(c, &xlc, m.xlc)) || (rc = upload(c, &node_agg, m.node_agg)) ||
+        (rc = upload(c, &ends, m.ends))) {
+        for (void* p : {(void*)edge, (void*)cnt, (void*)xsp, (void*)node, (void*)n_node, (void*)agg, (void*)lc,
+                        (void*)xlc, (void*)node_agg, (void*)ends})
+            dfree(c, p);
+        (void)hipGetLastError();
+        c->err = err;
+        return;
+    }
+    SolveLists& l = c->solve_lists;
+    l.n_slices = (int)m.cnt.size();
+    l.stride = m.stride;
+    l.edge = edge;
+    l.cnt = cnt;
+    l.lc = reinterpret_cast<const uint2*>(lc);
+    l.xsp = xsp;
+    l.xlc = reinterpret_cast<const uint2*>(xlc);
+    l.n_extra = m.xsp.back();
+    l.node = node;
+    l.n_node = n_node;
+    l.node_agg = node_agg;
+    l.agg = agg;
+    l.ends = ends;
+    const int cu = n_cu();
+    c->one_launch_pcg[0] = pcg_solve_blocks<double>(c->bc, l, cu);
+    c->one_launch_pcg[1] = pcg_solve_blocks<float>(c->bc, l, cu);
 }
 
 size_t array_bytes(const fepic_ctx* c, int a, int64_t n) {
@@ -801,19 +851,18 @@ bool mlp_start_rejected(int mode, double rr0, double bb) {
     return false;
 }
 
-// A Jacobi solve from launch_cg_init's state in one launch, if every row block has a resident
-// workgroup: *solved, with the scalars on the host.  Not solved, the iterations are launched
-// one by one: the meshes are too large, there is no memory for the exchange (8 words a row),
-// or the launch was refused, V and x as they were; or the workgroups gave up waiting for each
-// other (h_sc->converged is 3 then), x some iterate.  The context does not try again after
-// either of the last two.
-int solve_one_launch(fepic_ctx* c, const CgVec* V, int n_max, bool* solved) {
+// A solve in one launch, by launch(boxes, tag) with n words to exchange values through:
+// *solved, with the scalars on the host.  Not solved, the iterations are launched one by one:
+// there is no memory for the words or the launch was refused, the solve's state as it was; or
+// the workgroups gave up waiting for each other (h_sc->converged is 3 then), x some iterate.
+// *again: whether the context may try the next time (not after either of the last two).
+template <typename F>
+int solve_one_launch(fepic_ctx* c, int64_t n, int n_max, bool* again, bool* solved, F&& launch) {
     *solved = false;
     c->h_sc->converged = 0;
-    if (!c->one_launch || n_max <= 0) return FEPIC_OK;
-    const int64_t n = cg_solve_boxes(c->bc);
+    if (n_max <= 0) return FEPIC_OK;
     bool fresh = (uint64_t)c->box_tag + (uint64_t)n_max > 0xffffffffull;
-    if (c->n_boxes != n) {
+    if (c->n_boxes < n) {
         dfree(c, c->d_boxes);
         c->n_boxes = 0;
         c->d_boxes = dalloc<unsigned long long>(c, n);
@@ -822,27 +871,26 @@ int solve_one_launch(fepic_ctx* c, const CgVec* V, int n_max, bool* solved) {
         fresh = true;
     }
     if (fresh) {   // no word carries a tag from here on
-        HIPCHK(c, hipMemsetAsync(c->d_boxes, 0, sizeof(unsigned long long) * n, c->stream));
+        HIPCHK(c, hipMemsetAsync(c->d_boxes, 0, sizeof(unsigned long long) * c->n_boxes, c->stream));
         c->box_tag = 0;
     }
     hipEvent_t* ev = timer_pair(c, FAM_CG_ITER, 0);
     if (ev) (void)hipEventRecord(ev[0], c->stream);
-    const hipError_t e = launch_cg_solve(c->stream, c->mesh.n_edges, n_max, c->d_sp, c->bc, c->d_A, c->d_x, V, c->d_boxes,
-                                         c->box_tag, c->d_partial, c->d_sc);
+    const hipError_t e = launch(c->d_boxes, c->box_tag);
     if (ev) (void)hipEventRecord(ev[1], c->stream);
     if (e != hipSuccess) {
-        c->one_launch = false;
+        *again = false;
         return FEPIC_OK;
     }
     HIPCHK(c, hipMemcpyAsync(c->h_sc, c->d_sc, sizeof(CgScalars), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     *solved = c->h_sc->converged != 3;
     if (!*solved) {
-        c->one_launch = false;
+        *again = false;
         c->box_tag += (uint32_t)n_max;
         return FEPIC_OK;
     }
-    c->box_tag += (uint32_t)c->h_sc->iters;
+    c->box_tag += (uint32_t)c->h_sc->iters + 1;   // a breakdown leaves words of the iteration it stopped in
     if (ev) c->timers[FAM_CG_ITER].launches += c->h_sc->iters + 1;   // counted as the iterations it stands for
     return FEPIC_OK;
 }
@@ -905,6 +953,7 @@ int field_phase(fepic_ctx* c, double dt, double beta, double gamma) {
     double2* const ZP[2] = {c->d_zp[0], c->d_zp[1]};
     const bool aux = c->opt.preconditioner == FEPIC_PC_AUX;
     const bool mixed = aux && c->opt.solve_precision == FEPIC_SOLVE_MIXED;
+    if (aux && !c->solve_lists_tried) prepare_one_launch(c);
     if (mixed) {
         int rc = ensure_operator_f32(c);
         if (rc != FEPIC_OK) return rc;
@@ -1002,7 +1051,24 @@ int field_phase(fepic_ctx* c, double dt, double beta, double gamma) {
             launch_pcg_init_f32(c->stream, ne, c->d_sp, c->d_col, c->d_dinv32, c->d_rt, c->d_x32, c->aux, ZP32[0],
                                 c->d_rq32, c->d_partial, c->d_sc, tol_in);
             const int first = c->last_pass_iters[pass] > 0 ? std::max(batch, c->last_pass_iters[pass] + 2) : batch;
-            rc = iterate(first, [&](int i) {
+            bool solved = false;
+            const int n_max = maxit - total, blocks = c->aux.n_far <= 1 ? c->one_launch_pcg[1] : 0;
+            if (blocks) {
+                bool again = true;
+                rc = solve_one_launch(
+                    c, pcg_solve_boxes<float>(c->bc, c->solve_lists, ne, c->aux.n_aux, blocks), n_max, &again, &solved,
+                    [&](unsigned long long* boxes, uint32_t tag) {
+                        return launch_pcg_solve<float, float2>(c->stream, blocks, ne, n_max, c->d_sp, c->bc, c->d_A32,
+                                                               c->d_dinv32, c->d_x32, ZP32[0], c->d_rq32, c->aux,
+                                                               c->solve_lists, boxes, tag, c->d_partial, c->d_sc);
+                    });
+                if (rc != FEPIC_OK) return rc;
+                if (!again) c->one_launch_pcg[1] = 0;
+                if (!solved && c->h_sc->converged == 3)
+                    launch_pcg_init_f32(c->stream, ne, c->d_sp, c->d_col, c->d_dinv32, c->d_rt, c->d_x32, c->aux,
+                                        ZP32[0], c->d_rq32, c->d_partial, c->d_sc, tol_in);
+            }
+            if (!solved) rc = iterate(first, [&](int i) {
                 launch_pcg_iter_f32(c->stream, i, ne, c->d_sp, c->d_col, c->bc, c->d_A32, c->d_dinv32, c->d_x32, c->aux,
                                     ZP32, c->d_rq32, c->d_partial, c->d_sc);
             });
@@ -1035,11 +1101,28 @@ int field_phase(fepic_ctx* c, double dt, double beta, double gamma) {
             }
             const int first = (restart == 0 && c->last_cg_iters > 0) ? std::max(batch, c->last_cg_iters + 2) : batch;
             bool solved = false;
-            if (!aux) {
-                const int rs = solve_one_launch(c, V[0], maxit - total, &solved);
-                if (rs != FEPIC_OK) return rs;
-                if (!solved && c->h_sc->converged == 3) cg_init();   // it gave up: x is a start like another
+            int rs = FEPIC_OK;
+            const int n_max = maxit - total, blocks = c->aux.n_far <= 1 ? c->one_launch_pcg[0] : 0;
+            if (aux && blocks) {
+                bool again = true;
+                rs = solve_one_launch(
+                    c, pcg_solve_boxes<double>(c->bc, c->solve_lists, ne, c->aux.n_aux, blocks), n_max, &again, &solved,
+                    [&](unsigned long long* boxes, uint32_t tag) {
+                        const double* R = reinterpret_cast<const double*>(c->d_rq);
+                        return launch_pcg_solve<double, double2>(c->stream, blocks, ne, n_max, c->d_sp, c->bc, c->d_A,
+                                                                 c->d_dinv, c->d_x, ZP[0], R, c->aux, c->solve_lists,
+                                                                 boxes, tag, c->d_partial, c->d_sc);
+                    });
+                if (!again) c->one_launch_pcg[0] = 0;
+            } else if (!aux && c->one_launch) {
+                rs = solve_one_launch(c, cg_solve_boxes(c->bc), n_max, &c->one_launch, &solved,
+                                      [&](unsigned long long* boxes, uint32_t tag) {
+                                          return launch_cg_solve(c->stream, ne, n_max, c->d_sp, c->bc, c->d_A, c->d_x,
+                                                                 V[0], boxes, tag, c->d_partial, c->d_sc);
+                                      });
             }
+            if (rs != FEPIC_OK) return rs;
+            if (!solved && c->h_sc->converged == 3) cg_init();   // it gave up: x is a start like another
             int rc = solved ? FEPIC_OK : iterate(first, [&](int i) {
                 if (aux)
                     launch_pcg_iter(c->stream, i, ne, c->d_sp, c->d_col, c->bc, c->d_A, c->d_dinv, c->d_x, c->aux, ZP,
@@ -1810,6 +1893,7 @@ int fepic_upload_mesh(fepic_ctx* c, int64_t n_nodes, const double* xyz, int64_t 
         c->aux.inc = ainc;
         c->aux.th = ath;
         c->aux.ends = reinterpret_cast<const int2*>(aends);
+        if (c->opt.preconditioner == FEPIC_PC_AUX) prepare_one_launch(c);
         c->aux.scale = dalloc<double4>(c, m.n_aux);
         c->aux.scale8 = dalloc<double4>(c, (m.n_aux + 7) / 8);
         c->aux.scale64 = dalloc<double4>(c, (m.n_aux + 63) / 64);

@@ -121,7 +121,10 @@ struct fepic_ctx {
     unsigned long long* d_boxes = nullptr;         // values exchanged within a one-launch Jacobi solve
     int64_t n_boxes = 0;
     uint32_t box_tag = 0;                          // last tag in use there
-    bool one_launch = false;                       // the row blocks are all resident at once
+    bool one_launch = false;                       // Jacobi: the row blocks are all resident at once
+    fepic::SolveLists solve_lists;
+    bool solve_lists_tried = false;
+    int one_launch_pcg[2] = {0, 0};                // FP64, FP32: row blocks per workgroup (0: not in one launch)
     fepic::CgVec* d_cgv[2] = {nullptr, nullptr};   // Jacobi-PCG state, double buffered
     // auxiliary-space PCG: (z, p) pairs double buffered, r and q (n_edges each), nodal arrays
     double2* d_zp[2] = {nullptr, nullptr};

@@ -187,6 +187,33 @@ struct AuxSpace {
     float4* Y_f = nullptr;        // [n_aux + 1], Y_f[n_aux] = 0
 };
 
+// What a one-launch solve with the auxiliary space needs beside AuxSpace and BlockCols: the
+// node slices' distinct edges with the incidences as 16-bit indices into them, and the
+// distinct nodes and finest far aggregates at the ends of each row block's edges.  Built for
+// meshes of at most kSolveRows rows that keep within the limits below.
+constexpr int kSolveRows = 2 * 256 * 512;
+constexpr int kSolveEdges = 768;    // distinct edges of a slice (about 650 on the workloads' meshes)
+constexpr int kSolveNodes = 256;    // distinct end nodes of a row block
+constexpr int kSolveAggs = 16;      // finest far aggregates of those nodes
+constexpr int kNodeSlots = 16;      // incidences of a node in one chunk (interior nodes have about 14)
+struct SolveLists {
+    int n_slices = 0;
+    int stride = 0;                     // room per slice in edge, a multiple of 256
+    const int32_t* edge = nullptr;      // [slices][stride] ascending, padded with the first
+    const int32_t* cnt = nullptr;       // [slices]
+    const uint2* lc = nullptr;          // [slices][64 nodes][kNodeSlots] index into edge, top bit: the
+                                        // node is the tail; padding: stride
+    const int32_t* xsp = nullptr;       // [slices + 1] the slice's further chunks in xlc
+    const uint2* xlc = nullptr;         // [n_extra][64 nodes][kNodeSlots]
+    int n_extra = 0;
+    const int32_t* node = nullptr;      // [blocks][kSolveNodes] ascending
+    const int32_t* n_node = nullptr;    // [blocks]
+    const uint8_t* node_agg = nullptr;  // [blocks][kSolveNodes] index into agg
+    const int32_t* agg = nullptr;       // [blocks][kSolveAggs], padded with -1
+    const uint32_t* ends = nullptr;     // [blocks * kBlockRows] index into node of the tail, of the
+                                        // head in the upper half; wall nodes: kSolveNodes
+};
+
 // Device-side diagnostics accumulators (max-abs values stored as ordered bit patterns).
 struct DiagAcc {
     unsigned long long cont_max, gauss_max, drift_max, rho_max, divb_max;
@@ -309,6 +336,18 @@ void launch_cg_init(hipStream_t s, int64_t n_rows, const int64_t* slice_ptr, con
 void launch_cg_iter(hipStream_t s, int i, int64_t n_rows, const int64_t* slice_ptr, const int32_t* col,
                     const BlockCols& bc, const double* A, double* x, CgVec* const v[2], double* partial,
                     CgScalars* sc, bool det = false);
+// A whole solve with the auxiliary space in one launch: the row blocks per workgroup with
+// which all workgroups are resident (0: none), the exchange words, and the launch from the
+// state of launch_pcg_init (launch_pcg_init_f32), otherwise like launch_cg_solve.
+template <typename S>
+int pcg_solve_blocks(const BlockCols& bc, const SolveLists& l, int n_cu);
+template <typename S>
+int64_t pcg_solve_boxes(const BlockCols& bc, const SolveLists& l, int64_t n_rows, int64_t n_aux, int blocks);
+template <typename S, typename S2>
+hipError_t launch_pcg_solve(hipStream_t s, int blocks, int64_t n_rows, int n_max, const int64_t* sp,
+                            const BlockCols& bc, const S* A, const S* dinv, S* x, const S2* zp0, const S* r,
+                            const AuxSpace& g, const SolveLists& l, unsigned long long* boxes, unsigned tag0,
+                            double* partial, CgScalars* sc);
 // A whole Jacobi solve in one launch: whether every row block has a resident workgroup, the
 // 64-bit words that the workgroups exchange values through, and the launch (from launch_cg_init's
 // state; tags tag0 + 1 .. tag0 + n_max must not be in the words yet).

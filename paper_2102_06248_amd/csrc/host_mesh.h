@@ -67,6 +67,16 @@ int build_host_mesh(HostMesh& m, int64_t n_nodes, const double* xyz, int64_t n_t
 int assemble_edge_matrices(HostMesh& m, const std::vector<uint8_t>& fixed, const std::vector<uint8_t>& abc_face,
                            std::string& err);
 
+// Host arrays of SolveLists; stride 0: the mesh exceeds one of its limits.
+struct HostSolveLists {
+    int stride = 0;
+    std::vector<int32_t> edge, cnt, xsp, node, n_node, agg;
+    std::vector<uint16_t> lc, xlc;
+    std::vector<uint8_t> node_agg;
+    std::vector<uint32_t> ends;
+};
+HostSolveLists build_solve_lists(const HostMesh& m);
+
 // Face area vectors 1/2 (r_j - r_i) x (r_k - r_i).
 void face_area_vectors(const HostMesh& m, std::vector<double>& out);
 

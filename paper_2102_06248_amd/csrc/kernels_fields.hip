@@ -970,27 +970,111 @@ __global__ __launch_bounds__(kBlockRows) void k_cg_iter(int64_t n_rows, RowGrid 
     block_slot_add<3, R>(v, cg_buf(cg_slots, i + 1));
 }
 
-// A double passed between workgroups of one running kernel: its halves as two 64-bit words,
-// each with the tag of the iteration it belongs to in the upper half.  A word is one atomic,
-// so a reader that sees the tags has the value, whatever the order in which stores arrive:
-// no fences, no cache write-backs, no flags.  Device scope: the words pass the XCDs' L2s.
-__device__ __forceinline__ void box_put(unsigned long long* p, double v, unsigned tag) {
-    const unsigned long long t = (unsigned long long)tag << 32;
-    __hip_atomic_store(p, t | (unsigned)__double2loint(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(p + 1, t | (unsigned)__double2hiint(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ unsigned long long box_word(const unsigned long long* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ bool box_has(unsigned long long a, unsigned tag) { return (unsigned)(a >> 32) == tag; }
-__device__ __forceinline__ double box_value(unsigned long long a, unsigned long long b) {
-    return __hiloint2double((int)(unsigned)b, (int)(unsigned)a);
-}
+// Values passed between the workgroups of one running kernel: a double as two 64-bit words, a
+// float as one, each word with the tag of the iteration it belongs to in the upper half.
+// Words are written and read whole, so a reader that sees the tags has the value, whatever
+// the order in which stores arrive: no fences, no cache write-backs, no flags.  Written
+// through and read past the XCDs' L2s (sc1, device scope), both words in one access; offsets
+// in bytes.
+struct Mail {
+    static constexpr int kDeviceScope = 16;   // sc1
+    typedef unsigned v2 __attribute__((ext_vector_type(2)));
+    typedef unsigned v4 __attribute__((ext_vector_type(4)));
+    __amdgpu_buffer_rsrc_t r;
+    __device__ __forceinline__ Mail(unsigned long long* boxes, unsigned bytes)
+        : r(__builtin_amdgcn_make_buffer_rsrc(boxes, 0, (int)bytes, 0x00027000)) {}
+    __device__ __forceinline__ void put(unsigned at, double v, unsigned tag) const {
+        const v4 w = {(unsigned)__double2loint(v), tag, (unsigned)__double2hiint(v), tag};
+        __builtin_amdgcn_raw_buffer_store_b128(w, r, (int)at, 0, kDeviceScope);
+    }
+    __device__ __forceinline__ void put(unsigned at, float v, unsigned tag) const {
+        const v2 w = {__float_as_uint(v), tag};
+        __builtin_amdgcn_raw_buffer_store_b64(w, r, (int)at, 0, kDeviceScope);
+    }
+};
 
 // Polls of one wait before the solve gives up (a tenth of a second; a wait takes a few).
 constexpr int kSolvePolls = 1 << 17;
 // Copies of the workgroups' partials: every workgroup reads all of one, its XCD's.
 constexpr int kSolveCopies = 8;
+
+// K values that a lane waits for.
+template <typename S, int K>
+struct Inbox {
+    static constexpr int kBytes = 2 * sizeof(S);   // of a value in the mail
+    unsigned at[K];
+    bool need[K];
+    unsigned w[K][kBytes / 4];
+    __device__ __forceinline__ void expect(int k, unsigned offset, bool n) {
+        at[k] = offset;
+        need[k] = n;
+#pragma unroll
+        for (int j = 0; j < kBytes / 4; ++j) w[k][j] = 0;
+    }
+    __device__ __forceinline__ void load(const Mail& m) {
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            if (need[k]) {
+                if constexpr (sizeof(S) == 8) {
+                    const Mail::v4 v = __builtin_amdgcn_raw_buffer_load_b128(m.r, (int)at[k], 0, Mail::kDeviceScope);
+                    w[k][0] = v.x;
+                    w[k][1] = v.y;
+                    w[k][2] = v.z;
+                    w[k][3] = v.w;
+                } else {
+                    const Mail::v2 v = __builtin_amdgcn_raw_buffer_load_b64(m.r, (int)at[k], 0, Mail::kDeviceScope);
+                    w[k][0] = v.x;
+                    w[k][1] = v.y;
+                }
+            }
+    }
+    __device__ __forceinline__ bool check(unsigned tag) {
+        bool ok = true;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            if (need[k]) {
+                if constexpr (sizeof(S) == 8)
+                    need[k] = !((w[k][1] == tag) & (w[k][3] == tag));
+                else
+                    need[k] = w[k][1] != tag;
+            }
+            ok = ok & !need[k];
+        }
+        return ok;
+    }
+    __device__ __forceinline__ S value(int k) const {   // zero where nothing was expected
+        if constexpr (sizeof(S) == 8)
+            return __hiloint2double((int)w[k][2], (int)w[k][0]);
+        else
+            return __uint_as_float(w[k][0]);
+    }
+};
+
+// Polls until every lane of the wave has what it expects of both boxes: a round has all its
+// loads in flight together, and a lane sits out for what it has.  Nothing is looked for
+// before it can be there, because polls in vain hold up the others' stores.  Waiting 17 x 64
+// cycles first (half a microsecond, nearly what a store and a load past the L2s take), 90k
+// rows took 3.5 us per Jacobi iteration and 7.9 per FP64 PCG one; without 4.1 and 11.1, with
+// 32 x 64 3.7 and 8.5.  Up to 64 workgroups poll so little that 8 are enough (13k rows 2.98
+// us, with 16 3.09).  Gives up after kSolvePolls rounds (*fail).
+template <typename A, typename B>
+__device__ __forceinline__ void wait_boxes(const Mail& m, A& a, B& b, unsigned tag, int n_wg, int* fail) {
+    if (n_wg > 64)
+        __builtin_amdgcn_s_sleep(17);
+    else
+        __builtin_amdgcn_s_sleep(8);
+    for (int n = 0;; ++n) {
+        asm volatile("" ::: "memory");   // the words are read anew in every round
+        a.load(m);
+        b.load(m);
+        const bool ok = a.check(tag) & b.check(tag);
+        if (__all(ok)) break;
+        if (n >= kSolvePolls) {
+            if ((threadIdx.x & 63) == 0) *fail = 1;
+            break;
+        }
+    }
+}
 
 // A whole Jacobi-PCG solve in one launch, for matrices of which every row block has a
 // resident workgroup (launched cooperatively).  The same recurrence and block layout as
@@ -1001,19 +1085,17 @@ constexpr int kSolveCopies = 8;
 // iteration's only grid-wide one.  The boxes are double buffered: a workgroup writes the
 // values of iterate i + 2 over those of i after it has seen every partial of i + 1, whose
 // writers had read theirs of i.
-// Bound by that exchange (a store and a load past the L2s, about 1.5 us) and the LDS reads of
-// the product; what grows with the mesh is the polling, so a lane polls only for what it
-// lacks, with all its loads in flight, and the partials lie in a copy per XCD.  Per iteration
-// against a launch of k_cg_iter: 1.1k rows 5.2 -> 2.8 us, 13k 6.5 -> 3.2, 37k 6.8 -> 3.8, 90k
-// 7.0 -> 4.6, 129k 7.4 -> 5.2 (registers capped for two workgroups per CU: 0.8 us more, by
-// spills).
+// Bound by that exchange (a store and a load past the L2s, 0.7 us at least) and the LDS reads
+// of the product (0.75 us); what grows with the mesh is the polling, so the partials lie in a
+// copy per XCD.  Per iteration against a launch of k_cg_iter: 1.1k rows 5.2 -> 2.7 us, 13k 6.5
+// -> 3.0, 90k 7.0 -> 3.5 (registers capped for two workgroups per CU: 0.8 us more, by spills).
 // Every wait is bounded: a workgroup that polls kSolvePolls times in vain sets converged to
 // 3 and leaves with x as it found it, the others follow in the same way, and the host solves
 // by k_cg_iter.
 // n_max: the iterate at which the solve stops unconverged.
 __global__ __launch_bounds__(kBlockRows) __attribute__((amdgpu_waves_per_eu(2))) void k_cg_solve(
     int64_t n_rows, RowGrid rg, int n_max, const int64_t* __restrict__ sp, BlockCols bc, const double* __restrict__ A,
-    double* __restrict__ x, const CgVec* __restrict__ V, unsigned long long* __restrict__ boxes, unsigned tag0,
+    double* __restrict__ x, const CgVec* __restrict__ V, unsigned long long* boxes, unsigned box_bytes, unsigned tag0,
     const double* __restrict__ cg_slots, CgScalars* sc) {
     extern __shared__ double s_u[];
     constexpr int R = kBlockRows, H = kHaloRegs, NW = R / 64;
@@ -1024,10 +1106,9 @@ __global__ __launch_bounds__(kBlockRows) __attribute__((amdgpu_waves_per_eu(2)))
     const int nb = (int)bc.nb, tid = threadIdx.x, wave = tid >> 6;
     const int64_t row = b * R + tid, nr = (int64_t)nb * R;
     // boxes: two buffers of a value per row, then two of the workgroups' three partials
-    auto w_box = [&](int buf, int64_t r) { return boxes + 2 * (buf * nr + r); };
-    auto p_box = [&](int buf, int copy, int k) {
-        return boxes + 4 * nr + 8 * (((int64_t)buf * kSolveCopies + copy) * nb + k);
-    };
+    const Mail mail(boxes, box_bytes);
+    auto w_box = [&](int buf, int64_t r) { return 16 * (unsigned)(buf * nr + r); };
+    auto p_box = [&](int buf, int copy, int k) { return 16 * (unsigned)(2 * nr) + 48 * (unsigned)((buf * kSolveCopies + copy) * nb + k); };
     BlockRow<double> P;
     P.load(bc, b * (R / 64) + wave, sp, A);
     const double tol2_bb = sc->tol2_bb, bb = sc->bb;
@@ -1081,7 +1162,7 @@ __global__ __launch_bounds__(kBlockRows) __attribute__((amdgpu_waves_per_eu(2)))
         if (row < n_rows) {
             const double diag = P.a[0], rn = u * diag;
             w = acc / diag;
-            box_put(w_box(buf, row), w, tag);
+            mail.put(w_box(buf, row), w, tag);
             v[0] = rn * u;
             v[1] = u * acc;
             v[2] = rn * rn;
@@ -1097,52 +1178,20 @@ __global__ __launch_bounds__(kBlockRows) __attribute__((amdgpu_waves_per_eu(2)))
             double a = 0.0;
 #pragma unroll
             for (int q = 0; q < NW; ++q) a += s_own[j][q];
-            box_put(p_box(buf, copy, (int)b) + 2 * j, a, tag);
+            mail.put(p_box(buf, copy, (int)b) + 16 * j, a, tag);
         }
-        // the partials of all workgroups, one per thread, and the halo's values: a round of
-        // polls has all its loads in flight together, and a lane with all it needs sits out
-        const unsigned long long *pa = p_box(buf, blockIdx.x % kSolveCopies, min(tid, nb - 1)), *ha[H];
+        // the partials of all workgroups, one per thread, and the halo's values
+        Inbox<double, 3> pin;
+        Inbox<double, H> win;
 #pragma unroll
-        for (int k = 0; k < H; ++k) ha[k] = w_box(buf, k * R < bc.stride ? h[k] : row);
-        unsigned long long pw[6] = {0, 0, 0, 0, 0, 0}, hb[2 * H];
-        bool okp = tid >= nb, okh[H];
+        for (int j = 0; j < 3; ++j) pin.expect(j, p_box(buf, blockIdx.x % kSolveCopies, min(tid, nb - 1)) + 16 * j, tid < nb);
 #pragma unroll
-        for (int k = 0; k < H; ++k) okh[k] = k * R + tid >= cnt;
+        for (int k = 0; k < H; ++k) win.expect(k, w_box(buf, k * R < bc.stride ? h[k] : 0), k * R + tid < cnt);
+        wait_boxes(mail, pin, win, tag, nb, &s_fail);
 #pragma unroll
-        for (int k = 0; k < 2 * H; ++k) hb[k] = 0;
-        for (int n = 0;; ++n) {
-            if (!okp) {
+        for (int j = 0; j < 3; ++j) v[j] = pin.value(j);
 #pragma unroll
-                for (int j = 0; j < 6; ++j) pw[j] = box_word(pa + j);
-            }
-#pragma unroll
-            for (int k = 0; k < H; ++k)
-                if (!okh[k]) {
-                    hb[2 * k] = box_word(ha[k]);
-                    hb[2 * k + 1] = box_word(ha[k] + 1);
-                }
-            if (!okp) {
-                okp = true;
-#pragma unroll
-                for (int j = 0; j < 6; ++j) okp = okp & box_has(pw[j], tag);
-            }
-            bool ok = okp;
-#pragma unroll
-            for (int k = 0; k < H; ++k) {
-                if (!okh[k]) okh[k] = box_has(hb[2 * k], tag) & box_has(hb[2 * k + 1], tag);
-                ok = ok & okh[k];
-            }
-            if (__all(ok)) break;
-            if (n >= kSolvePolls) {
-                if ((tid & 63) == 0) s_fail = 1;
-                break;
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < 3; ++j) v[j] = tid < nb ? box_value(pw[2 * j], pw[2 * j + 1]) : 0.0;
-#pragma unroll
-        for (int k = 0; k < H; ++k)
-            if (k * R < bc.stride) hw[k] = box_value(hb[2 * k], hb[2 * k + 1]);
+        for (int k = 0; k < H; ++k) hw[k] = win.value(k);
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
             const double a = wave_total(v[j]);
@@ -1163,6 +1212,464 @@ __global__ __launch_bounds__(kBlockRows) __attribute__((amdgpu_waves_per_eu(2)))
     }
     if (row < n_rows) x[row] = xr;
     if (b == 0 && tid == 0) {
+        sc->rr = rr;
+        sc->rr0 = rr0;
+        sc->iters = i;
+        sc->converged = conv;
+    }
+}
+
+// u += the records of one chunk of kNodeSlots incidences, of which every lane of the node's
+// quad holds four: the index of the record (padding: the zero record) and, in the top bit,
+// whether the node is the edge's tail, which turns the sign of the gradient (component 0)
+// and not of the interpolation.
+template <typename S>
+__device__ __forceinline__ void node_chunk(S u[2], const S* rec, uint2 w, int comp) {
+    const unsigned tail = comp == 0 ? 0x8000u : 0u;
+    unsigned c[8];
+    c[0] = __builtin_amdgcn_mov_dpp((int)w.x, 0x00, 0xf, 0xf, true);   // quad_perm: lane 0 to all four
+    c[1] = __builtin_amdgcn_mov_dpp((int)w.y, 0x00, 0xf, 0xf, true);
+    c[2] = __builtin_amdgcn_mov_dpp((int)w.x, 0x55, 0xf, 0xf, true);
+    c[3] = __builtin_amdgcn_mov_dpp((int)w.y, 0x55, 0xf, 0xf, true);
+    c[4] = __builtin_amdgcn_mov_dpp((int)w.x, 0xaa, 0xf, 0xf, true);
+    c[5] = __builtin_amdgcn_mov_dpp((int)w.y, 0xaa, 0xf, 0xf, true);
+    c[6] = __builtin_amdgcn_mov_dpp((int)w.x, 0xff, 0xf, 0xf, true);
+    c[7] = __builtin_amdgcn_mov_dpp((int)w.y, 0xff, 0xf, 0xf, true);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const unsigned lo = c[q] & 0xffffu, hi = c[q] >> 16;
+        const S a = rec[4 * (lo & 0x7fffu) + comp], b = rec[4 * (hi & 0x7fffu) + comp];
+        u[0] += (lo & tail) ? -a : a;
+        u[1] += (hi & tail) ? -b : b;
+    }
+}
+
+__device__ __forceinline__ uint2 pack(const EdgeVec& t) {
+    uint2 w = {0u, 0u};
+    __builtin_memcpy(&w, &t, sizeof(EdgeVec));
+    return w;
+}
+__device__ __forceinline__ EdgeVec unpack(uint2 w) {
+    EdgeVec t;
+    __builtin_memcpy(&t, &w, sizeof(EdgeVec));
+    return t;
+}
+
+template <typename S>
+__device__ __forceinline__ typename Vec<S>::t3 widen(const EdgeVec& t) {
+    typename Vec<S>::t3 v;
+    v.x = (S)(float)t.x;
+    v.y = (S)(float)t.y;
+    v.z = (S)(float)t.z;
+    return v;
+}
+
+// A whole PCG solve with the auxiliary space in one launch: k_cg_solve's scheme for the
+// recurrence of k_pcg_q, k_pcg_nodes, k_pcg_fold and k_pcg_update, with kB row blocks and up
+// to 2 kB node slices per workgroup.  An iteration has three waits: for q at the slices'
+// edges and (p, q); for Y at the row blocks' nodes and the slices' sums of the finest far
+// level (further levels are left to the kernels); for z at the halo and (r, z), (r, r).  The
+// residual at a slice's edges and p at a block's halo are carried along by the workgroup
+// that needs them.  One set of boxes is enough: a value is overwritten in the next iteration
+// only after a grid-wide sum whose partials each workgroup gave after it had read the value.
+// Bound by the three exchanges (90k rows: 4 of 8 us), then by LDS: the product's reads, the
+// slices' sums.  With two blocks the registers hold the matrix and little else; what one
+// phase reads is kept in LDS (without that, FP64 spilled 580 bytes per lane: 239k rows 29.9
+// us, now 15.5).  Per iteration against the kernels: FP64 1.1k rows 12.0 -> 6.0 us, 51k 13.7
+// -> 7.3, 90k 17.8 -> 7.9, 239k 25.0 -> 15.5; FP32 90k 16.3 -> 7.6, beam (246k) 17.6 -> 9.8.
+template <typename S, int kB>
+__global__ __launch_bounds__(kBlockRows) __attribute__((amdgpu_waves_per_eu(2))) void k_pcg_solve(
+    int64_t n_rows, RowGrid rg, int n_max, const int64_t* __restrict__ sp, BlockCols bc, const S* __restrict__ A,
+    const S* __restrict__ dinv, S* __restrict__ x, const typename Vec<S>::t2* __restrict__ ZP, const S* __restrict__ R0,
+    AuxSpace g, SolveLists L, unsigned long long* boxes, unsigned box_bytes, unsigned shared_bytes, unsigned tag0,
+    const double* __restrict__ slots,
+    CgScalars* sc) {
+    using V4 = typename Vec<S>::t4;
+    extern __shared__ __attribute__((aligned(32))) double lds_solve[];
+    constexpr int R = kBlockRows, H = kHaloRegs, NW = R / 64, W = 2 * sizeof(S);
+    constexpr int E = kSolveEdges / 256, NY = 4 * kSolveNodes / R;   // edges, nodal values per thread
+    static_assert(32 * kSolveAggs == R && aux_far_log(0) == 9, "a thread per component and slice of an aggregate");
+    __shared__ double s_dot[2][NW], s_own[2][NW], s_far[kB][kSolveAggs][4];
+    __shared__ S s_sum[2][4][4];
+    __shared__ int s_fail, s_fail_y;   // of the waits before a sum over the workgroups, and of the one for Y
+    // one after the other in the same memory: p of the blocks and their halos, the slices'
+    // records (r', th r') with a zero record, the blocks' nodal values with a zero record
+    S* s_p = reinterpret_cast<S*>(lds_solve);
+    V4* s_rec = reinterpret_cast<V4*>(lds_solve);
+    S* s_y = reinterpret_cast<S*>(lds_solve);
+    const int64_t wg = rg_first(rg);
+    if (wg >= rg_end(rg)) return;   // the whole workgroup (the grid is a multiple of eight)
+    const int nw = (int)rg.nb, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int half = tid >> 8, ht = tid & 255, nl = ht >> 2, comp = tid & 3;
+    // the boxes: q and z per row, Y per node and component, the slices' sums, then per copy
+    // the workgroups' (p, q), and their (r, z) and (r, r)
+    const Mail mail(boxes, box_bytes);
+    const unsigned q_box = 0, z_box = W * (unsigned)n_rows, y_box = 2 * z_box, f_box = y_box + 4 * W * (unsigned)g.n_aux,
+                   p_box = f_box + 4 * W * (unsigned)L.n_slices;
+    auto pq_at = [&](int copy, int k) { return p_box + 16 * (unsigned)(copy * nw + k); };
+    auto rz_at = [&](int copy, int k) { return p_box + 16 * (unsigned)(kSolveCopies * nw + 2 * (copy * nw + k)); };
+    const int my_copy = blockIdx.x % kSolveCopies;
+    const double tol2_bb = sc->tol2_bb, bb = sc->bb;
+    double t[2];
+    slot_load_wave<2>(slots, t);
+    // the row blocks
+    // What only one phase of an iteration reads, in LDS behind the rest where a workgroup has
+    // several blocks: the edges of its slices with their residuals and vectors, x, D^-1 and
+    // (then not in the shared part) p of the rows and the halo.
+    constexpr bool kLds = kB > 1;
+    const int PS = R + bc.stride, EU = L.stride / 256;
+    unsigned char* const s_own_state = reinterpret_cast<unsigned char*>(lds_solve) + shared_bytes;
+    uint2* const s_te = reinterpret_cast<uint2*>(s_own_state);
+    S* const s_re = reinterpret_cast<S*>(s_te + kB * EU * R);
+    S* const s_x = s_re + kB * EU * R;
+    S* const s_di = s_x + kB * R;
+    if constexpr (kLds) s_p = s_di + kB * R;
+    int* const s_e = reinterpret_cast<int*>(s_di + kB * R + kB * PS);
+    BlockRow<S> P[kB];
+    int row[kB];
+    S r[kB], z[kB], hz[kB][H], p1 = S(0), hp1[H], x1 = S(0), di1 = S(0);
+    EdgeVec th[kB];
+    unsigned en[kB];
+    int h[kB][H], cnt[kB], yn[kB][NY], n_node[kB];   // yn: the node, its aggregate's index above bit 24
+    S yf[kB][NY];
+    const bool far = g.n_far > 0;
+    int f_slice[kB];
+    const V4* fs = pick<S>(g.far_scale[0], g.far_scale_f[0]);
+#pragma unroll
+    for (int b = 0; b < kB; ++b) {
+        const int64_t blk = wg * kB + b, bl = blk < bc.nb ? blk : bc.nb - 1;
+        row[b] = (int)(blk * R + tid);
+        P[b].load(bc, blk * NW + wave, sp, A);
+        const int rw = row[b] < n_rows ? row[b] : 0;
+        r[b] = R0[rw];
+        z[b] = ZP[rw].x;
+        if constexpr (kLds) {
+            s_p[b * PS + tid] = S(0);
+            s_x[b * R + tid] = x[rw];
+            s_di[b * R + tid] = dinv[rw];
+        } else {
+            x1 = x[rw];
+            di1 = dinv[rw];
+        }
+        th[b] = g.th[rw];
+        en[b] = L.ends[bl * R + tid];
+        cnt[b] = blk < bc.nb ? bc.cnt[bl] : 0;
+        halo_ids(bc, bl, h[b]);
+#pragma unroll
+        for (int k = 0; k < H; ++k) {
+            hz[b][k] = hp1[k] = S(0);
+            if (k * R < bc.stride) {
+                hz[b][k] = ZP[h[b][k]].x;
+                if constexpr (kLds) s_p[b * PS + (k + 1) * R + tid] = S(0);
+            }
+        }
+        n_node[b] = blk < bc.nb ? L.n_node[bl] : 0;
+        const int a0 = L.agg[bl * kSolveAggs + (tid >> 5)];
+        f_slice[b] = far && blk < bc.nb && a0 >= 0 ? a0 * 8 + ((tid >> 2) & 7) : L.n_slices;
+#pragma unroll
+        for (int k = 0; k < NY; ++k) {
+            const int64_t at = bl * kSolveNodes + ((tid + k * R) >> 2);
+            const int node = L.node[at];
+            yn[b][k] = node | (int)L.node_agg[at] << 24;
+            yf[b][k] = far ? reinterpret_cast<const S*>(fs + (node >> aux_far_log(0)))[comp] : S(0);
+        }
+    }
+    // the node slices, two at a time (a half of the workgroup each, four lanes per node)
+    const int s0 = (int)(wg * L.n_slices / nw), s1 = (int)((wg + 1) * L.n_slices / nw);
+    S re1[E], d1[kB], d8[kB], d64[kB];
+    EdgeVec te1[E];
+    int e1[E], ec[kB];
+    uint2 lc[kB];
+#pragma unroll
+    for (int b = 0; b < kB; ++b) {
+        const int sl = s0 + 2 * b + half;
+        ec[b] = 0;
+        d1[b] = d8[b] = d64[b] = S(0);
+        lc[b] = {0u, 0u};
+        if constexpr (!kLds) {
+#pragma unroll
+            for (int k = 0; k < E; ++k) {
+                e1[k] = 0;
+                re1[k] = S(0);
+                te1[k] = EdgeVec{};
+            }
+        }
+        if (sl >= s1) continue;
+        ec[b] = L.cnt[sl];
+        lc[b] = L.lc[(int64_t)sl * 256 + ht];
+#pragma unroll
+        for (int k = 0; k < E; ++k)
+            if (k * 256 < L.stride) {
+                const int ek = L.edge[(int64_t)sl * L.stride + k * 256 + ht];
+                if constexpr (kLds) {
+                    const int at = (b * EU + k) * R + tid;
+                    s_e[at] = ek;
+                    s_re[at] = R0[ek];
+                    s_te[at] = pack(g.th[ek]);
+                } else {
+                    e1[k] = ek;
+                    re1[k] = R0[ek];
+                    te1[k] = g.th[ek];
+                }
+            }
+        const int64_t node = (int64_t)sl * 64 + nl;
+        if (node < g.n_aux) {
+            d1[b] = reinterpret_cast<const S*>(pick<S>(g.scale, g.scale_f))[4 * node + comp];
+            d8[b] = reinterpret_cast<const S*>(pick<S>(g.scale8, g.scale8_f))[4 * (node >> 3) + comp];
+            d64[b] = reinterpret_cast<const S*>(pick<S>(g.scale64, g.scale64_f))[4 * (int64_t)sl + comp];
+        }
+    }
+    if (tid == 0) s_fail = s_fail_y = 0;
+    double gm = wave_total(t[0]), rr = wave_total(t[1]);
+    const double rr0 = rr;
+    double gam_old = 0.0;
+    int conv = 0, i = 0;
+    // the workgroup's sums of n values into every copy of its partials
+    auto give = [&](const double* v, int n, unsigned tag) {
+        for (int j = 0; j < n; ++j) {
+            const double a = wave_total(v[j]);
+            if (lane == 0) s_own[j][wave] = a;
+        }
+        __syncthreads();
+        const int j = tid & 1, copy = tid >> 1;
+        if (j < n && copy < kSolveCopies) {
+            double a = 0.0;
+#pragma unroll
+            for (int q = 0; q < NW; ++q) a += s_own[j][q];
+            mail.put(n == 1 ? pq_at(copy, (int)wg) : rz_at(copy, (int)wg) + 16 * j, a, tag);
+        }
+    };
+    // all workgroups' partials, one per thread, summed in one order; false: given up
+    auto sum = [&](double* v, int n) {
+        for (int j = 0; j < n; ++j) {
+            const double a = wave_total(v[j]);
+            if (lane == 0) s_dot[j][wave] = a;
+        }
+        __syncthreads();
+        for (int j = 0; j < n; ++j) {
+            v[j] = 0.0;
+#pragma unroll
+            for (int q = 0; q < NW; ++q) v[j] += s_dot[j][q];
+        }
+        return s_fail == 0;
+    };
+    for (;; ++i) {
+        const bool done = !(rr > tol2_bb) || bb == 0.0;
+        const double beta = (i == 0) ? 0.0 : gm / gam_old;
+        const bool bad = !done && !(gm > 0.0 && gm < INFINITY && beta >= 0.0 && beta < INFINITY);
+        conv = done ? 1 : (bad ? 2 : 0);
+        if (conv || i >= n_max) break;
+        gam_old = gm;
+        const unsigned tag = tag0 + (unsigned)(i + 1);
+        const S bs = (S)beta;
+        // q = A p
+#pragma unroll
+        for (int b = 0; b < kB; ++b) {
+            S* sb = s_p + b * PS + tid;
+            if constexpr (kLds) {
+                sb[0] = fma(bs, sb[0], z[b]);
+#pragma unroll
+                for (int k = 0; k < H; ++k)
+                    if (k * R < bc.stride) sb[(k + 1) * R] = fma(bs, sb[(k + 1) * R], hz[b][k]);
+            } else {
+                sb[0] = p1 = fma(bs, p1, z[b]);
+#pragma unroll
+                for (int k = 0; k < H; ++k)
+                    if (k * R < bc.stride) sb[(k + 1) * R] = hp1[k] = fma(bs, hp1[k], hz[b][k]);
+            }
+        }
+        __syncthreads();
+        S q[kB];
+        double v[2] = {0.0, 0.0};
+#pragma unroll
+        for (int b = 0; b < kB; ++b) {
+            const S* sb = s_p + b * PS;
+            q[b] = P[b].dot(bc, A, [&](unsigned c) { return sb[c]; });
+            if (row[b] < n_rows) {
+                mail.put(q_box + W * (unsigned)row[b], q[b], tag);
+                v[0] += (double)(kLds ? sb[tid] : p1) * (double)q[b];
+            }
+        }
+        give(v, 1, tag);
+        {
+            Inbox<double, 1> pin;
+            pin.expect(0, pq_at(my_copy, min(tid, nw - 1)), tid < nw);
+            Inbox<S, kB * E> qin;
+#pragma unroll
+            for (int k = 0; k < kB * E; ++k) {
+                const bool need = (k % E) * 256 + ht < ec[k / E];
+                int ek = 0;
+                if constexpr (kLds) {
+                    if (need) ek = s_e[(k / E * EU + k % E) * R + tid];
+                } else {
+                    ek = e1[k % E];
+                }
+                qin.expect(k, q_box + W * (unsigned)ek, need);
+            }
+            wait_boxes(mail, pin, qin, tag, nw, &s_fail);
+            v[0] = pin.value(0);
+            if (!sum(v, 1)) break;
+            const double alpha = gm / v[0];
+            if (!(alpha > 0.0 && alpha < INFINITY)) {
+                conv = 2;
+                break;
+            }
+            const S as = (S)alpha;
+#pragma unroll
+            for (int b = 0; b < kB; ++b) {
+                if constexpr (kLds)
+                    s_x[b * R + tid] = fma(as, s_p[b * PS + tid], s_x[b * R + tid]);
+                else
+                    x1 = fma(as, p1, x1);
+                r[b] = fma(-as, q[b], r[b]);
+            }
+#pragma unroll
+            for (int k = 0; k < kB * E; ++k) {
+                if constexpr (kLds) {
+                    if ((k % E) * 256 + ht < ec[k / E]) {
+                        S& re = s_re[(k / E * EU + k % E) * R + tid];
+                        re = fma(-as, qin.value(k), re);
+                    }
+                } else {
+                    re1[k % E] = fma(-as, qin.value(k), re1[k % E]);
+                }
+            }
+        }
+        // the slices' nodal sums
+#pragma unroll
+        for (int b = 0; b < kB; ++b) {
+            if (s0 + 2 * b >= s1) break;   // the whole workgroup
+            const int sl = s0 + 2 * b + half;
+            const bool mine = sl < s1;     // the whole wave
+            V4* rec4 = s_rec + half * (L.stride + 1);
+            if (mine) {
+#pragma unroll
+                for (int k = 0; k < E; ++k)
+                    if (k * 256 < L.stride) {
+                        S rk;
+                        EdgeVec tk;
+                        if constexpr (kLds) {
+                            const int at = (b * EU + k) * R + tid;
+                            rk = s_re[at];
+                            tk = unpack(s_te[at]);
+                        } else {
+                            rk = re1[k];
+                            tk = te1[k];
+                        }
+                        const auto tv = widen<S>(tk);
+                        rec4[k * 256 + ht] = Vec<S>::four(rk, tv.x * rk, tv.y * rk, tv.z * rk);
+                    }
+                if (ht == 0) rec4[L.stride] = Vec<S>::four(S(0), S(0), S(0), S(0));
+            }
+            __syncthreads();
+            S own = S(0), s8 = S(0);
+            if (mine) {
+                const S* rec = reinterpret_cast<const S*>(rec4);
+                S u[2] = {S(0), S(0)};
+                node_chunk<S>(u, rec, lc[b], comp);
+                for (int k = L.n_extra ? L.xsp[sl] : 0, k1 = L.n_extra ? L.xsp[sl + 1] : 0; k < k1; ++k)
+                    node_chunk<S>(u, rec, L.xlc[(int64_t)k * 256 + ht], comp);
+                own = s8 = u[0] + u[1];   // zero for the padding nodes of the last slice
+                s8 += __shfl_xor(s8, 4);
+                s8 += __shfl_xor(s8, 8);
+                s8 += __shfl_xor(s8, 16);
+                const S s16 = s8 + __shfl_xor(s8, 32);
+                if (lane < 4) s_sum[half][wave & 3][lane] = s16;
+            }
+            __syncthreads();
+            if (mine) {
+                S s64 = S(0);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) s64 += s_sum[half][k][comp];
+                const int64_t node = (int64_t)sl * 64 + nl;
+                const S y = own * d1[b] + s8 * d8[b] + s64 * d64[b];
+                if (node < g.n_aux) mail.put(y_box + W * (4 * (unsigned)node + comp), y, tag);
+                if (far && ht < 4) mail.put(f_box + W * (4 * (unsigned)sl + comp), s64, tag);
+            }
+        }
+        // Y with the far level at the blocks' nodes
+        {
+            Inbox<S, kB * NY> yin;
+            Inbox<S, kB> fin;
+#pragma unroll
+            for (int k = 0; k < kB * NY; ++k)
+                yin.expect(k, y_box + W * (4 * ((unsigned)yn[k / NY][k % NY] & 0xffffffu) + comp),
+                           ((tid + (k % NY) * R) >> 2) < n_node[k / NY]);
+#pragma unroll
+            for (int b = 0; b < kB; ++b) {
+                const bool need = f_slice[b] < L.n_slices;
+                fin.expect(b, f_box + W * (4 * (unsigned)(need ? f_slice[b] : 0) + comp), need);
+            }
+            wait_boxes(mail, yin, fin, tag, nw, &s_fail_y);
+            if (far) {
+#pragma unroll
+                for (int b = 0; b < kB; ++b) {
+                    double f = (double)fin.value(b);   // the aggregate's eight slices
+                    f += __shfl_xor(f, 4);
+                    f += __shfl_xor(f, 8);
+                    f += __shfl_xor(f, 16);
+                    if ((tid & 28) == 0) s_far[b][tid >> 5][comp] = f;
+                }
+                __syncthreads();
+            }
+#pragma unroll
+            for (int k = 0; k < kB * NY; ++k) {
+                const int b = k / NY, kk = k % NY;
+                S y = yin.value(k);
+                if (far) y += (S)s_far[b][(unsigned)yn[b][kk] >> 24][comp] * yf[b][kk];
+                s_y[b * 4 * (kSolveNodes + 1) + tid + kk * R] = y;
+            }
+            if (tid < 4 * kB) s_y[(tid >> 2) * 4 * (kSolveNodes + 1) + 4 * kSolveNodes + comp] = S(0);
+            __syncthreads();
+            if (s_fail_y) break;
+        }
+        // z and its dots
+        v[0] = v[1] = 0.0;
+#pragma unroll
+        for (int b = 0; b < kB; ++b) {
+            const V4* yb = reinterpret_cast<const V4*>(s_y) + b * (kSolveNodes + 1);
+            const V4 y0 = yb[en[b] & 0xffffu], y1 = yb[en[b] >> 16];
+            const auto tv = widen<S>(th[b]);
+            S di;
+            if constexpr (kLds)
+                di = s_di[b * R + tid];
+            else
+                di = di1;
+            z[b] = di * r[b] + (y1.x - y0.x) + tv.x * (y0.y + y1.y) + tv.y * (y0.z + y1.z) + tv.z * (y0.w + y1.w);
+            if (row[b] < n_rows) {
+                mail.put(z_box + W * (unsigned)row[b], z[b], tag);
+                v[0] += (double)r[b] * (double)z[b];
+                v[1] += (double)r[b] * (double)r[b];
+            }
+        }
+        give(v, 2, tag);
+        {
+            Inbox<double, 2> pin;
+            pin.expect(0, rz_at(my_copy, min(tid, nw - 1)), tid < nw);
+            pin.expect(1, rz_at(my_copy, min(tid, nw - 1)) + 16, tid < nw);
+            Inbox<S, kB * H> zin;
+#pragma unroll
+            for (int k = 0; k < kB * H; ++k)
+                zin.expect(k, z_box + W * (unsigned)((k % H) * R < bc.stride ? h[k / H][k % H] : 0),
+                           (k % H) * R + tid < cnt[k / H]);
+            wait_boxes(mail, pin, zin, tag, nw, &s_fail);
+            v[0] = pin.value(0);
+            v[1] = pin.value(1);
+            if (!sum(v, 2)) break;
+            gm = v[0];
+            rr = v[1];
+#pragma unroll
+            for (int k = 0; k < kB * H; ++k) hz[k / H][k % H] = zin.value(k);
+        }
+    }
+    if (s_fail || s_fail_y) {   // the same for the whole workgroup: a barrier follows every wait
+        if (tid == 0) sc->converged = 3;
+        return;
+    }
+#pragma unroll
+    for (int b = 0; b < kB; ++b)
+        if (row[b] < n_rows) x[row[b]] = kLds ? s_x[b * R + tid] : x1;
+    if (wg == 0 && tid == 0) {
         sc->rr = rr;
         sc->rr0 = rr0;
         sc->iters = i;
@@ -1874,7 +2381,7 @@ void launch_cg_iter(hipStream_t s, int i, int64_t n_rows, const int64_t* sp, con
                        col, bc, A, x, v[a], v[b], partial + SLOT_CG * kSlot, sc);
 }
 
-int64_t cg_solve_boxes(const BlockCols& bc) { return bc.nb * (4 * kBlockRows + 16 * kSolveCopies); }
+int64_t cg_solve_boxes(const BlockCols& bc) { return bc.nb * (4 * kBlockRows + 12 * kSolveCopies); }
 
 // One workgroup per CU: 197k rows on two per CU took 18.4 us per iteration, against 11.9 by
 // k_cg_iter (129k rows, one per CU: 5.2 against 7.4).  Every halo column has a register
@@ -1896,12 +2403,106 @@ hipError_t launch_cg_solve(hipStream_t s, int64_t n_rows, int n_max, const int64
     RowGrid rg = block_grid(bc);
     BlockCols g = bc;
     const double* slots = partial + SLOT_CG * kSlot;
-    void* args[] = {&n_rows, &rg, &n_max, &sp, &g, &A, &x, &V, &boxes, &tag0, &slots, &sc};
+    unsigned box_bytes = (unsigned)(8 * cg_solve_boxes(bc));
+    void* args[] = {&n_rows, &rg, &n_max, &sp, &g, &A, &x, &V, &boxes, &box_bytes, &tag0, &slots, &sc};
     const hipError_t e = hipLaunchCooperativeKernel((const void*)k_cg_solve, dim3(rg.grid), dim3(kBlockRows), args,
                                                     (unsigned)staged_bytes(bc, sizeof(double)), s);
     if (e != hipSuccess) (void)hipGetLastError();
     return e;
 }
+
+namespace {
+constexpr size_t kSolveLds = 152 * 1024;   // dynamic LDS of a workgroup alone on its CU
+
+inline RowGrid solve_grid(const BlockCols& bc, int blocks) {
+    RowGrid r;
+    r.nb = (bc.nb + blocks - 1) / blocks;
+    r.per = (r.nb + 7) / 8;
+    r.g = (int)std::max<int64_t>(1, r.per);
+    r.grid = 8u * (unsigned)r.g;
+    return r;
+}
+
+// Dynamic LDS: what the phases use one after the other, and the state kept there.
+inline size_t solve_shared(const BlockCols& bc, const SolveLists& l, int blocks, size_t value) {
+    return value * std::max({blocks > 1 ? (size_t)0 : (size_t)(kBlockRows + bc.stride), (size_t)(8 * (l.stride + 1)),
+                             (size_t)blocks * 4 * (kSolveNodes + 1)});
+}
+inline size_t solve_bytes(const BlockCols& bc, const SolveLists& l, int blocks, size_t value) {
+    const size_t edges = (size_t)blocks * 2 * l.stride, rows = (size_t)blocks * kBlockRows;
+    return solve_shared(bc, l, blocks, value) +
+           (blocks > 1 ? edges * (12 + value) + (3 * rows + (size_t)blocks * bc.stride) * value : 0);
+}
+
+template <typename S>
+const void* pcg_solve_kernel(int blocks) {
+    return blocks == 1 ? (const void*)k_pcg_solve<S, 1> : (const void*)k_pcg_solve<S, 2>;
+}
+
+// One workgroup per CU with one or two row blocks: with four (FP32, 463k rows) the matrix and
+// state spilled 740 bytes per lane and an iteration took 50 us, against 27 by the kernels;
+// with two they lose on no mesh that fits (figures at k_pcg_solve).
+template <typename S>
+bool pcg_solve_resident(const BlockCols& bc, const SolveLists& l, int blocks, int n_cu) {
+    const RowGrid rg = solve_grid(bc, blocks);
+    if (l.n_slices > 2 * blocks * rg.nb || rg.nb > kBlockRows || (int64_t)rg.grid > n_cu) return false;
+    int per_cu = 0;
+    const size_t lds = solve_bytes(bc, l, blocks, sizeof(S));
+    if (lds > kSolveLds || hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, pcg_solve_kernel<S>(blocks), kBlockRows,
+                                                                        lds) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return per_cu > 0;
+}
+}  // namespace
+
+template <typename S>
+int pcg_solve_blocks(const BlockCols& bc, const SolveLists& l, int n_cu) {
+    if (l.n_slices == 0 || bc.nb <= 0 || bc.wide || bc.stride > kHaloRegs * kBlockRows) return 0;
+    for (int blocks : {1, 2})
+        if (pcg_solve_resident<S>(bc, l, blocks, n_cu)) return blocks;
+    return 0;
+}
+
+template <typename S>
+int64_t pcg_solve_boxes(const BlockCols& bc, const SolveLists& l, int64_t n_rows, int64_t n_aux, int blocks) {
+    return (int64_t)(sizeof(S) / 4) * (2 * n_rows + 4 * n_aux + 4 * l.n_slices) +
+           6 * kSolveCopies * solve_grid(bc, blocks).nb;
+}
+
+template <typename S, typename S2>
+hipError_t launch_pcg_solve(hipStream_t s, int blocks, int64_t n_rows, int n_max, const int64_t* sp,
+                            const BlockCols& bc, const S* A, const S* dinv, S* x, const S2* zp0, const S* r,
+                            const AuxSpace& g, const SolveLists& l, unsigned long long* boxes, unsigned tag0,
+                            double* partial, CgScalars* sc) {
+    RowGrid rg = solve_grid(bc, blocks);
+    BlockCols b = bc;
+    AuxSpace a = g;
+    SolveLists ll = l;
+    const double* slots = partial + SLOT_CG * kSlot + (size_t)3 * 3 * kCgSlots;   // reduction -1: buffer 3 of 4
+    unsigned box_bytes = (unsigned)(8 * pcg_solve_boxes<S>(bc, l, n_rows, g.n_aux, blocks));
+    unsigned shared_bytes = (unsigned)solve_shared(bc, l, blocks, sizeof(S));
+    void* args[] = {&n_rows, &rg, &n_max, &sp,    &b,         &A,            &dinv, &x,     &zp0,
+                    &r,      &a,  &ll,    &boxes, &box_bytes, &shared_bytes, &tag0, &slots, &sc};
+    const hipError_t e = hipLaunchCooperativeKernel(pcg_solve_kernel<S>(blocks), dim3(rg.grid), dim3(kBlockRows), args,
+                                                    (unsigned)solve_bytes(bc, l, blocks, sizeof(S)), s);
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e;
+}
+
+template int pcg_solve_blocks<double>(const BlockCols&, const SolveLists&, int);
+template int pcg_solve_blocks<float>(const BlockCols&, const SolveLists&, int);
+template int64_t pcg_solve_boxes<double>(const BlockCols&, const SolveLists&, int64_t, int64_t, int);
+template int64_t pcg_solve_boxes<float>(const BlockCols&, const SolveLists&, int64_t, int64_t, int);
+template hipError_t launch_pcg_solve<double, double2>(hipStream_t, int, int64_t, int, const int64_t*, const BlockCols&,
+                                                      const double*, const double*, double*, const double2*,
+                                                      const double*, const AuxSpace&, const SolveLists&,
+                                                      unsigned long long*, unsigned, double*, CgScalars*);
+template hipError_t launch_pcg_solve<float, float2>(hipStream_t, int, int64_t, int, const int64_t*, const BlockCols&,
+                                                    const float*, const float*, float*, const float2*, const float*,
+                                                    const AuxSpace&, const SolveLists&, unsigned long long*, unsigned,
+                                                    double*, CgScalars*);
 
 // One workgroup per slice of 64 auxiliary nodes, consecutive slices on the same XCD.
 inline RowGrid node_grid(int64_t n_aux) {

@@ -1,7 +1,8 @@
-"""Jacobi solves in one launch (every row block a resident workgroup) where they can go
-wrong: one partial block, a few, the most that one workgroup per CU holds and the first mesh
-past it (iterations launched one by one), several solves through the same exchange words,
-the iteration budget, and two contexts solving at once.
+"""Solves in one launch (every row block a resident workgroup) where they can go wrong: one
+partial block, a few, the most that one workgroup per CU holds and the first mesh past it
+(Jacobi: iterations launched one by one; auxiliary space: two row blocks per workgroup, then
+one by one), nodes of more edges than one chunk of incidences, far levels, several solves
+through the same exchange words, the iteration budget, and two contexts solving at once.
 
 Held to the solver's stopping rule recomputed in numpy, like the row blocks' test.
 """
@@ -13,6 +14,7 @@ import scipy.sparse as sp
 
 from gpu_common import announce, have_gpu, jittered_kuhn, require_lib
 from paper_2102_06248_amd import inputs
+from test_gpu_row_blocks import fan
 
 pytestmark = pytest.mark.gpu
 TOL = 1e-10
@@ -52,7 +54,7 @@ def start(F, L, d):
     F.fepic_set_fields(L.ctx, *(np.where(d, inputs.random_field_dofs(n, 1.0, s), 0.0) for s in (3, 4)))
 
 
-# n = 26: 129,194 rows, 253 blocks of 512; n = 27: 144,225 rows, 282 blocks for 256 CUs
+# n = 26: 129,194 rows, 253 blocks of 512; n = 27: 144,423 rows, 283 blocks for 256 CUs
 @pytest.mark.parametrize("n,deterministic", [(2, 0), (7, 0), (7, 1), (26, 0), (27, 0)])
 def test_stopping_rule(F, n, deterministic):
     announce(f"one launch: n={n}, deterministic={deterministic}")
@@ -62,6 +64,23 @@ def test_stopping_rule(F, n, deterministic):
         M, S, d, dt = operators(F, L)
         start(F, L, d)
         for _ in range(3):
+            assert check_step(F, L, M, S, dt) > 0
+
+
+# n = 33: 261,459 rows, 511 blocks, two for each of 256 workgroups; n = 34: 558 blocks; the
+# fan's axis nodes have more than 80 edges
+@pytest.mark.parametrize("mesh,far", [(2, -1), (7, -1), (12, 0), (12, 1), (12, 2), (26, -1), (27, -1), (33, -1), (34, -1),
+                                      ("fan", 0)])
+@pytest.mark.parametrize("solve", ["fp64", "mixed"])
+def test_stopping_rule_auxiliary_space(F, mesh, far, solve):
+    announce(f"one launch, auxiliary space: {mesh}, far levels {far}, {solve}")
+    xyz, tets = fan(40) if mesh == "fan" else jittered_kuhn(mesh, seed=1)[:2]
+    precision = F.FEPIC_SOLVE_MIXED if solve == "mixed" else F.FEPIC_SOLVE_FP64
+    with F.Simulation(xyz, tets, device=0, cg_tol=TOL, preconditioner=F.FEPIC_PC_AUX, cg_max_iters=5000,
+                      solve_precision=precision, aux_far_levels=far) as L:
+        M, S, d, dt = operators(F, L)
+        start(F, L, d)
+        for _ in range(2):
             assert check_step(F, L, M, S, dt) > 0
 
 
