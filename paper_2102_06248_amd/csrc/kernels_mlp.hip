@@ -236,7 +236,9 @@ __global__ __launch_bounds__(kMlpBlock) void k_mlp_grad(BatchSrc src, float inv_
                     sHT[k * kTileStride + m] = a[kb][j];
                 }
             floatx4 z2[4];
-            float y = 0.f;
+            // the output in k_mlp_forward's order of sums (per unit mod 16, then pairwise), so that
+            // the loss is the forward pass's own
+            float part_y[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int nt = 0; nt < 4; ++nt) {
                 floatx4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -246,10 +248,11 @@ __global__ __launch_bounds__(kMlpBlock) void k_mlp_grad(BatchSrc src, float inv_
                 for (int q = 0; q < 4; ++q) {
                     const int n = 16 * nt + 4 * g + q;
                     acc[q] += sb2[n];
-                    y += fmaxf(acc[q], 0.0f) * sW3[n];
+                    part_y[q] += fmaxf(acc[q], 0.0f) * sW3[n];
                 }
                 z2[nt] = acc;
             }
+            float y = (part_y[0] + part_y[1]) + (part_y[2] + part_y[3]);
             y += __shfl_xor(y, 16);
             y += __shfl_xor(y, 32);
             const float e = i < src.n ? y + b3 - target : 0.f;
