@@ -118,6 +118,9 @@ struct fepic_ctx {
     int32_t *d_mf_col = nullptr, *d_ef_inc = nullptr;
     double *d_mf_val = nullptr, *d_h = nullptr;
     double *d_rhs = nullptr, *d_rt = nullptr, *d_Me = nullptr;
+    unsigned char* h_out = nullptr;                // pinned, read-outs pass through it
+    hipEvent_t out_ev[2] = {nullptr, nullptr};     // its halves are written
+    int32_t* d_eperm = nullptr;                    // canonical edge id -> device edge id
     unsigned long long* d_boxes = nullptr;         // values exchanged within a one-launch Jacobi solve
     int64_t n_boxes = 0;
     uint32_t box_tag = 0;                          // last tag in use there

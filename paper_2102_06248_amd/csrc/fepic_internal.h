@@ -317,6 +317,20 @@ void launch_fill_i32(hipStream_t s, int32_t* x, int64_t n, int32_t v);
 
 // Field kernels (kernels_fields.hip).
 void launch_fill(hipStream_t s, double* x, int64_t n, double v);
+// Pieces of device arrays into host-visible memory, in the caller's order.
+struct OutPiece {
+    const void* src = nullptr;
+    const int32_t* perm = nullptr;   // element i is src[perm[i]]; null: src[i]
+    void* to = nullptr;
+    int64_t first = 0, n = 0;
+    int kind = 0;                    // OUT_WORD, OUT_FLOAT or OUT_INT
+};
+enum { OUT_WORD = 0, OUT_FLOAT = 1, OUT_INT = 2 };   // 8 bytes as they are; FP32 widened to FP64; 4 bytes
+constexpr int kOutPieces = 8;
+struct OutPieces {
+    OutPiece p[kOutPieces];
+};
+void launch_read_out(hipStream_t s, const OutPieces& pieces, int n);
 void launch_axpby(hipStream_t s, double* y, const double* a, double alpha, const double* b, double beta, int64_t n);
 void launch_scale_A(hipStream_t s, const SellMatrix& shape, const int64_t* slice_ptr, const int32_t* col,
                     const double* M, const double* S, double* A, double* dinv, const uint8_t* bmask, double c,

@@ -301,73 +301,82 @@ HostSolveLists build_solve_lists(const HostMesh& m) {
     const int64_t ne = m.n_edges, na = m.n_aux, nsl = (na + kSell - 1) / kSell;
     const int64_t nb = (ne + kBlockRows - 1) / kBlockRows;
     if (na <= 0 || ne > kSolveRows) return out;
-    // the slices' distinct edges
-    std::vector<std::vector<int32_t>> uniq(nsl);
-    std::vector<int32_t>&cnt = out.cnt, &xsp = out.xsp;
-    cnt.resize(nsl);
-    xsp.assign(nsl + 1, 0);
-    size_t most = 1;
+    // the slices' distinct edges, ascending: an edge is listed when its stamp is another
+    // slice's (the one of the block, below), and its place found again in pos
+    std::vector<int32_t> stamp(std::max(ne, na), -1), pos(std::max(ne, na));
+    std::vector<int64_t> start(nsl + 1, 0);
+    std::vector<int32_t> uniq;
+    uniq.reserve(12 * na);
+    out.cnt.resize(nsl);
+    out.xsp.assign(nsl + 1, 0);
+    int64_t most = 1;
     for (int64_t s = 0; s < nsl; ++s) {
-        std::vector<int32_t>& u = uniq[s];
-        for (int64_t k = m.aux_sp[s]; k < m.aux_sp[s + 1]; ++k)
-            if (m.aux_inc[k] != kAuxPad) u.push_back(m.aux_inc[k] >= 0 ? m.aux_inc[k] : ~m.aux_inc[k]);
-        std::sort(u.begin(), u.end());
-        u.erase(std::unique(u.begin(), u.end()), u.end());
-        if (u.empty() || u.size() > (size_t)kSolveEdges) return out;
-        cnt[s] = (int32_t)u.size();
-        most = std::max(most, u.size());
-        const int64_t w = (m.aux_sp[s + 1] - m.aux_sp[s]) / kSell;
-        xsp[s + 1] = xsp[s] + (int32_t)(w > kNodeSlots ? (w - 1) / kNodeSlots : 0);
-    }
-    // the row blocks' end nodes and their finest far aggregates
-    std::vector<int32_t>&node = out.node, &n_node = out.n_node, &agg = out.agg;
-    node.assign(nb * kSolveNodes, 0);
-    n_node.resize(nb);
-    agg.assign(nb * kSolveAggs, -1);
-    out.node_agg.assign(nb * kSolveNodes, 0);
-    out.ends.assign(nb * kBlockRows, (uint32_t)kSolveNodes | (uint32_t)kSolveNodes << 16);
-    for (int64_t b = 0; b < nb; ++b) {
-        std::vector<int32_t> u;
-        const int64_t r0 = b * kBlockRows, r1 = std::min(ne, r0 + kBlockRows);
-        for (int64_t k = 2 * r0; k < 2 * r1; ++k)
-            if (m.aux_ends[k] < na) u.push_back(m.aux_ends[k]);
-        std::sort(u.begin(), u.end());
-        u.erase(std::unique(u.begin(), u.end()), u.end());
-        if (u.size() > (size_t)kSolveNodes) return out;
-        n_node[b] = (int32_t)u.size();
-        int n_agg = 0;
-        for (size_t j = 0; j < u.size(); ++j) {
-            const int32_t a = u[j] >> aux_far_log(0);
-            if (n_agg == 0 || agg[b * kSolveAggs + n_agg - 1] != a) {   // ascending, like the nodes
-                if (n_agg == kSolveAggs) return out;
-                agg[b * kSolveAggs + n_agg++] = a;
-            }
-            node[b * kSolveNodes + j] = u[j];
-            out.node_agg[b * kSolveNodes + j] = (uint8_t)(n_agg - 1);
+        for (int64_t k = m.aux_sp[s]; k < m.aux_sp[s + 1]; ++k) {
+            const int32_t c = m.aux_inc[k], e = c >= 0 ? c : ~c;
+            if (c == kAuxPad || stamp[e] == (int32_t)s) continue;
+            stamp[e] = (int32_t)s;
+            uniq.push_back(e);
         }
-        auto at = [&](int32_t v) {
-            return v < na ? (uint32_t)(std::lower_bound(u.begin(), u.end(), v) - u.begin()) : (uint32_t)kSolveNodes;
-        };
-        for (int64_t r = r0; r < r1; ++r) out.ends[r] = at(m.aux_ends[2 * r]) | at(m.aux_ends[2 * r + 1]) << 16;
+        start[s + 1] = (int64_t)uniq.size();
+        const int64_t n = start[s + 1] - start[s], w = (m.aux_sp[s + 1] - m.aux_sp[s]) / kSell;
+        if (n == 0 || n > kSolveEdges) return HostSolveLists{};
+        std::sort(uniq.begin() + start[s], uniq.end());
+        out.cnt[s] = (int32_t)n;
+        most = std::max(most, n);
+        out.xsp[s + 1] = out.xsp[s] + (int32_t)(w > kNodeSlots ? (w - 1) / kNodeSlots : 0);
     }
     const int stride = (int)((most + 255) / 256 * 256);
     out.edge.resize(nsl * stride);
     out.lc.assign(nsl * kSell * kNodeSlots, (uint16_t)stride);
-    out.xlc.assign((int64_t)xsp[nsl] * kSell * kNodeSlots, (uint16_t)stride);
+    out.xlc.assign((int64_t)out.xsp[nsl] * kSell * kNodeSlots, (uint16_t)stride);
     for (int64_t s = 0; s < nsl; ++s) {
-        const std::vector<int32_t>& u = uniq[s];
+        const int32_t* u = uniq.data() + start[s];
         int32_t* list = out.edge.data() + s * stride;
-        std::fill(list, list + stride, u[0]);
-        std::copy(u.begin(), u.end(), list);
+        for (int32_t k = 0; k < out.cnt[s]; ++k) {
+            list[k] = u[k];
+            pos[u[k]] = k;
+        }
+        std::fill(list + out.cnt[s], list + stride, u[0]);
         for (int64_t k = m.aux_sp[s]; k < m.aux_sp[s + 1]; ++k) {
             const int32_t c = m.aux_inc[k];
             if (c == kAuxPad) continue;
             const int64_t slot = (k - m.aux_sp[s]) / kSell, l = (k - m.aux_sp[s]) % kSell, chunk = slot / kNodeSlots;
-            const auto at = (uint16_t)(std::lower_bound(u.begin(), u.end(), c >= 0 ? c : ~c) - u.begin());
             uint16_t* to = chunk == 0 ? out.lc.data() + s * kSell * kNodeSlots
-                                      : out.xlc.data() + (xsp[s] + chunk - 1) * (int64_t)(kSell * kNodeSlots);
-            to[l * kNodeSlots + slot % kNodeSlots] = (uint16_t)(at | (c >= 0 ? 0 : 0x8000));
+                                      : out.xlc.data() + (out.xsp[s] + chunk - 1) * (int64_t)(kSell * kNodeSlots);
+            to[l * kNodeSlots + slot % kNodeSlots] = (uint16_t)(pos[c >= 0 ? c : ~c] | (c >= 0 ? 0 : 0x8000));
         }
+    }
+    // the row blocks' end nodes and their finest far aggregates
+    out.node.assign(nb * kSolveNodes, 0);
+    out.n_node.resize(nb);
+    out.agg.assign(nb * kSolveAggs, -1);
+    out.node_agg.assign(nb * kSolveNodes, 0);
+    out.ends.assign(nb * kBlockRows, (uint32_t)kSolveNodes | (uint32_t)kSolveNodes << 16);
+    std::fill(stamp.begin(), stamp.end(), -1);
+    for (int64_t b = 0; b < nb; ++b) {
+        int32_t *node = out.node.data() + b * kSolveNodes, *agg = out.agg.data() + b * kSolveAggs;
+        const int64_t r0 = b * kBlockRows, r1 = std::min(ne, r0 + kBlockRows);
+        int n = 0, n_agg = 0;
+        for (int64_t k = 2 * r0; k < 2 * r1; ++k) {
+            const int32_t v = m.aux_ends[k];
+            if (v >= na || stamp[v] == (int32_t)b) continue;
+            stamp[v] = (int32_t)b;
+            if (n == kSolveNodes) return HostSolveLists{};
+            node[n++] = v;
+        }
+        std::sort(node, node + n);
+        out.n_node[b] = n;
+        for (int j = 0; j < n; ++j) {
+            pos[node[j]] = j;
+            const int32_t a = node[j] >> aux_far_log(0);
+            if (n_agg == 0 || agg[n_agg - 1] != a) {   // ascending, like the nodes
+                if (n_agg == kSolveAggs) return HostSolveLists{};
+                agg[n_agg++] = a;
+            }
+            out.node_agg[b * kSolveNodes + j] = (uint8_t)(n_agg - 1);
+        }
+        auto at = [&](int32_t v) { return v < na ? (uint32_t)pos[v] : (uint32_t)kSolveNodes; };
+        for (int64_t r = r0; r < r1; ++r) out.ends[r] = at(m.aux_ends[2 * r]) | at(m.aux_ends[2 * r + 1]) << 16;
     }
     out.stride = stride;
     return out;

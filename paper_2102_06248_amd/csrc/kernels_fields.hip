@@ -138,6 +138,23 @@ __global__ __launch_bounds__(kBlock) void k_fill(double* x, int64_t n, double v)
     if (i < n) x[i] = v;
 }
 
+// Read-outs: the arrays' pieces (blockIdx.y) written in the caller's order straight into
+// pinned host memory, whole cache lines at a time, so that neither a copy into pageable
+// memory (16 GB/s here, against 55) nor the host's permutation is left.  Bound by the host's
+// copy alongside: fields of 998k tets (35 MB) 5.7 -> 1.65 ms, 384k tets 2.0 -> 0.6.
+__global__ __launch_bounds__(kBlock) void k_read_out(OutPieces pieces) {
+    const OutPiece p = pieces.p[blockIdx.y];
+    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < p.n; i += (int64_t)gridDim.x * kBlock) {
+        const int64_t j = p.perm ? p.perm[p.first + i] : p.first + i;
+        if (p.kind == OUT_WORD)
+            static_cast<unsigned long long*>(p.to)[i] = static_cast<const unsigned long long*>(p.src)[j];
+        else if (p.kind == OUT_FLOAT)
+            static_cast<double*>(p.to)[i] = (double)static_cast<const float*>(p.src)[j];
+        else
+            static_cast<int32_t*>(p.to)[i] = static_cast<const int32_t*>(p.src)[j];
+    }
+}
+
 __global__ __launch_bounds__(kBlock) void k_axpby(double* y, const double* a, double alpha, const double* b,
                                                    double beta, int64_t n) {
     int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -2279,6 +2296,13 @@ size_t partial_buffer_doubles() { return SLOT_COUNT * kSlot; }
 void launch_fill(hipStream_t s, double* x, int64_t n, double v) {
     if (n <= 0) return;
     hipLaunchKernelGGL(k_fill, dim3(grid_1d(n, kBlock)), dim3(kBlock), 0, s, x, n, v);
+}
+
+void launch_read_out(hipStream_t s, const OutPieces& pieces, int n) {
+    int64_t most = 1;
+    for (int k = 0; k < n; ++k) most = std::max(most, pieces.p[k].n);
+    hipLaunchKernelGGL(k_read_out, dim3((unsigned)std::min<int64_t>(grid_1d(most, kBlock), 256), (unsigned)n),
+                       dim3(kBlock), 0, s, pieces);
 }
 
 void launch_axpby(hipStream_t s, double* y, const double* a, double alpha, const double* b, double beta, int64_t n) {
