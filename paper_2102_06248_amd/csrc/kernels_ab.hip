@@ -33,7 +33,7 @@
 namespace fepic {
 namespace {
 
-constexpr int kBlock = 256;
+constexpr int kBlock = 128;
 constexpr int LE_A[6] = {0, 0, 0, 1, 1, 2};   // local edges (a, b), a < b
 constexpr int LE_B[6] = {1, 2, 3, 2, 3, 3};
 
@@ -43,7 +43,7 @@ constexpr int LE_B[6] = {1, 2, 3, 2, 3, 3};
 // kProbe probes goes straight to the global vector.  Particles arrive sorted by tet, so a
 // workgroup's pieces touch few edges and most adds stay in LDS; the table is flushed with
 // one FP64 atomic per occupied slot.
-constexpr int kTableBits = 10;
+constexpr int kTableBits = 9;
 constexpr int kTableSlots = 1 << kTableBits;
 constexpr int kProbe = 8;
 
@@ -85,15 +85,13 @@ __device__ __forceinline__ double min4(const double l[4]) { return fmin(fmin(l[0
 // The path of one step in Newton form on its nodes s_j = 1 - j (j = 0..M): r(s) =
 // sum_k c_k prod_{i<k} (s - s_i), with c_k the divided differences of the points P[j] at
 // s_j.  The nodes are unit-spaced, so each level of the table divides by -k.  Built once
-// per particle and step; every evaluation is then a nested product, without divisions.
+// per particle and step, and kept in LDS (a value per thread and coefficient): only a new
+// tet's LambdaPath reads them, and the 30 registers are the third wave of a SIMD.
 template <int M>
 struct NewtonPath {
-    double c[M + 1][3];
-    __device__ __forceinline__ explicit NewtonPath(const double P[M + 1][3]) {
-#pragma unroll
-        for (int j = 0; j <= M; ++j)
-#pragma unroll
-            for (int d = 0; d < 3; ++d) c[j][d] = P[j][d];
+    double* at;   // coefficient (j, d) at (3 j + d) kBlock
+    __device__ __forceinline__ double get(int j, int d) const { return at[(3 * j + d) * kBlock]; }
+    __device__ __forceinline__ NewtonPath(double c[M + 1][3], double* lds) : at(lds) {
 #pragma unroll
         for (int k = 1; k <= M; ++k) {
             const double inv = -1.0 / (double)k;
@@ -102,49 +100,65 @@ struct NewtonPath {
 #pragma unroll
                 for (int d = 0; d < 3; ++d) c[j][d] = (c[j][d] - c[j - 1][d]) * inv;
         }
-    }
-    __device__ __forceinline__ void at(double s, double r[3]) const {
 #pragma unroll
-        for (int d = 0; d < 3; ++d) r[d] = c[M][d];
+        for (int j = 0; j <= M; ++j)
 #pragma unroll
-        for (int k = M - 1; k >= 0; --k) {
-            const double f = s - (1.0 - k);
-#pragma unroll
-            for (int d = 0; d < 3; ++d) r[d] = r[d] * f + c[k][d];
-        }
-    }
-    __device__ __forceinline__ void at(double s, double r[3], double dr[3]) const {
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            r[d] = c[M][d];
-            dr[d] = 0.0;
-        }
-#pragma unroll
-        for (int k = M - 1; k >= 0; --k) {
-            const double f = s - (1.0 - k);
-#pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                dr[d] = dr[d] * f + r[d];
-                r[d] = r[d] * f + c[k][d];
-            }
-        }
+            for (int d = 0; d < 3; ++d) at[(3 * j + d) * kBlock] = c[j][d];
     }
 };
 
+// The path in one tet's barycentric coordinates lambda_1..3: the same Newton form, its
+// coefficients the gradients' products with the path's (lambda is affine in r).  Built once
+// per tet; an evaluation, of which a crossing's bisection takes about 50, is then a nested
+// product of three components: for order 4, 18 operations where r(s) and lambda(r) took 30.
 template <int M>
-__device__ __forceinline__ double min_lambda_at(const TetBlock<double>* bp, const double* r0, const NewtonPath<M>& path,
-                                                double s) {
-    double r[3], lam[4];
-    path.at(s, r);
-    lam_at(bp, r0, r, lam);
-    return min4(lam);
-}
-
-template <int M>
-__device__ __forceinline__ bool inside_at(const TetBlock<double>* bp, const double* r0, const NewtonPath<M>& path,
-                                          double s) {
-    return min_lambda_at(bp, r0, path, s) >= -kAbInsideEps;
-}
+struct LambdaPath {
+    double c[M + 1][3];
+    __device__ __forceinline__ LambdaPath(const TetBlock<double>* bp, const double* r0, const NewtonPath<M>& path) {
+#pragma unroll
+        for (int j = 0; j <= M; ++j) {
+            double p[3];
+#pragma unroll
+            for (int d = 0; d < 3; ++d) p[d] = path.get(j, d) - (j == 0 ? r0[d] : 0.0);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) c[j][k] = bp->gl[3 * k] * p[0] + bp->gl[3 * k + 1] * p[1] + bp->gl[3 * k + 2] * p[2];
+        }
+    }
+    __device__ __forceinline__ void at(double s, double lam[4]) const {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) lam[k + 1] = c[M][k];
+#pragma unroll
+        for (int j = M - 1; j >= 0; --j) {
+            const double f = s - (1.0 - j);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) lam[k + 1] = lam[k + 1] * f + c[j][k];
+        }
+        lam[0] = 1.0 - lam[1] - lam[2] - lam[3];
+    }
+    __device__ __forceinline__ void at(double s, double lam[4], double dl[4]) const {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            lam[k + 1] = c[M][k];
+            dl[k + 1] = 0.0;
+        }
+#pragma unroll
+        for (int j = M - 1; j >= 0; --j) {
+            const double f = s - (1.0 - j);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                dl[k + 1] = dl[k + 1] * f + lam[k + 1];
+                lam[k + 1] = lam[k + 1] * f + c[j][k];
+            }
+        }
+        lam[0] = 1.0 - lam[1] - lam[2] - lam[3];
+        dl[0] = -(dl[1] + dl[2] + dl[3]);
+    }
+    __device__ __forceinline__ bool inside(double s) const {
+        double lam[4];
+        at(s, lam);
+        return min4(lam) >= -kAbInsideEps;
+    }
+};
 
 // The straight segment from barycentric point A to B of one tet: its integrand W . dr is
 // constant, so q w (m_a d_b - m_b d_a) with m = (A + B) / 2, d = B - A is exact.
@@ -161,21 +175,16 @@ __device__ __forceinline__ void deposit_segment(const TetBlock<double>* bp, cons
 // The piece [sa, sb] of the path in tet t: q w int W . r' ds into the table, with M + 1
 // Gauss-Legendre points.
 template <int M>
-__device__ __forceinline__ void deposit_piece(const TetBlock<double>* bp, const double* r0,
-                                              const NewtonPath<M>& path, double sa, double sb, const AbParams& ap,
-                                              const EdgeTable& tab) {
+__device__ __forceinline__ void deposit_piece(const TetBlock<double>* bp, const LambdaPath<M>& lp, double sa, double sb,
+                                              const AbParams& ap, const EdgeTable& tab) {
     constexpr int ng = M + 1;
     const double half = 0.5 * (sb - sa);
     double acc[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
 #pragma unroll 1
     for (int q = 0; q < ng; ++q) {
         const double s = sa + half * (ap.gl_x[ng][q] + 1.0);
-        double r[3], dr[3], lam[4], dl[4];
-        path.at(s, r, dr);
-        lam_at(bp, r0, r, lam);
-#pragma unroll
-        for (int k = 0; k < 3; ++k) dl[k + 1] = bp->gl[3 * k] * dr[0] + bp->gl[3 * k + 1] * dr[1] + bp->gl[3 * k + 2] * dr[2];
-        dl[0] = -(dl[1] + dl[2] + dl[3]);
+        double lam[4], dl[4];
+        lp.at(s, lam, dl);
         const double w = ap.gl_w[ng][q];
 #pragma unroll
         for (int c = 0; c < 6; ++c) acc[c] += w * (lam[LE_A[c]] * dl[LE_B[c]] - lam[LE_B[c]] * dl[LE_A[c]]);
@@ -189,26 +198,26 @@ __device__ __forceinline__ void deposit_piece(const TetBlock<double>* bp, const 
 // or it passed the crossing cap (counted in na / ncap); nc counts the faces crossed.
 template <int M>
 __device__ __forceinline__ int walk_path(const TetBlock<double>* __restrict__ blk, const double* __restrict__ r0s, int t,
-                                      const double P[M + 1][3], const AbParams& ap, const EdgeTable& tab,
+                                      double P[M + 1][3], double* s_path, const AbParams& ap, const EdgeTable& tab,
                                       unsigned int& nc, unsigned int& na, unsigned int& ncap) {
     constexpr int ng = M + 1;
-    const NewtonPath<M> path(P);
+    const NewtonPath<M> path(P, s_path);
     const TetBlock<double>* bp = blk + t;
     double sa = 0.0;
     unsigned int crossed = 0;
+    LambdaPath<M> lp(bp, r0s + 3 * t, path);
     for (;;) {
-        const double* r0 = r0s + 3 * t;
         double out = -1.0;
 #pragma unroll 1
         for (int q = 0; q <= ng; ++q) {
             const double s = q < ng ? sa + (1.0 - sa) * 0.5 * (ap.gl_x[ng][q] + 1.0) : 1.0;
-            if (!inside_at(bp, r0, path, s)) {
+            if (!lp.inside(s)) {
                 out = s;
                 break;
             }
         }
         if (out < 0.0) {
-            deposit_piece(bp, r0, path, sa, 1.0, ap, tab);
+            deposit_piece(bp, lp, sa, 1.0, ap, tab);
             nc += crossed;
             return t;
         }
@@ -217,26 +226,22 @@ __device__ __forceinline__ int walk_path(const TetBlock<double>* __restrict__ bl
 #pragma unroll 1
         for (int it = 0; it < 64 && hi - lo > kAbRootTol; ++it) {
             const double mid = 0.5 * (lo + hi);
-            if (inside_at(bp, r0, path, mid)) lo = mid;
+            if (lp.inside(mid)) lo = mid;
             else hi = mid;
         }
         const double sx = 0.5 * (lo + hi);
-        deposit_piece(bp, r0, path, sa, sx, ap, tab);
+        deposit_piece(bp, lp, sa, sx, ap, tab);
         // exit face: the most negative coordinate at the bracket's outer end
-        double r[3], L[4];
-        path.at(hi, r);
-        lam_at(bp, r0, r, L);
-        int kf = 0;
-#pragma unroll
-        for (int k = 1; k < 4; ++k)
-            if (L[k] < L[kf]) kf = k;
+        double L[4];
+        lp.at(hi, L);
+        const double m01 = fmin(L[0], L[1]), m012 = fmin(m01, L[2]);   // ties: the smallest k
+        const int kf = L[3] < m012 ? 3 : (L[2] < m01 ? 2 : (L[1] < L[0] ? 1 : 0));
         // close the piece onto face kf from its end point r(sx)
-        path.at(sx, r);
-        lam_at(bp, r0, r, L);
+        lp.at(sx, L);
+        const double third = (kf == 0 ? L[0] : (kf == 1 ? L[1] : (kf == 2 ? L[2] : L[3]))) * (1.0 / 3.0);
         double Pf[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) Pf[k] = L[k] + L[kf] * (1.0 / 3.0);
-        Pf[kf] = 0.0;
+        for (int k = 0; k < 4; ++k) Pf[k] = k == kf ? 0.0 : L[k] + third;
         deposit_segment(bp, L, Pf, ap, tab);
         const int nb = bp->nbr[kf];
         if (nb < 0) {
@@ -249,29 +254,18 @@ __device__ __forceinline__ int walk_path(const TetBlock<double>* __restrict__ bl
             ++ncap;
             return -1;
         }
-        // the face point in the neighbour's local order (shared vertices keep their order,
-        // the far vertex gets 0), then the segment from it to the neighbour's coordinates of
-        // the piece's end point
+        // the face point in the neighbour's local order (shared vertices keep their order: the
+        // three others close up over kf and open again at the far vertex, which gets 0), then
+        // the segment from it to the neighbour's coordinates of the piece's end point
         const int far = nb & 3;
-        double Pn[4];
-        {
-            int jt = 0;
-#pragma unroll
-            for (int jn = 0; jn < 4; ++jn) {
-                if (jn == far) {
-                    Pn[jn] = 0.0;
-                    continue;
-                }
-                if (jt == kf) ++jt;
-                Pn[jn] = Pf[jt];
-                ++jt;
-            }
-        }
+        const double c0 = kf <= 0 ? Pf[1] : Pf[0], c1 = kf <= 1 ? Pf[2] : Pf[1], c2 = kf <= 2 ? Pf[3] : Pf[2];
+        const double Pn[4] = {far == 0 ? 0.0 : c0, far == 1 ? 0.0 : (far < 1 ? c0 : c1),
+                              far == 2 ? 0.0 : (far < 2 ? c1 : c2), far == 3 ? 0.0 : c2};
         t = nb >> 2;
         bp = blk + t;
-        path.at(sx, r);
+        lp = LambdaPath<M>(bp, r0s + 3 * t, path);
         double Ln[4];
-        lam_at(bp, r0s + 3 * t, r, Ln);
+        lp.at(sx, Ln);
         deposit_segment(bp, Pn, Ln, ap, tab);
         sa = sx;
     }
@@ -293,8 +287,8 @@ __device__ __forceinline__ int ring(int head, int j) {
 
 template <int M>
 __device__ __forceinline__ int walk_m(const TetBlock<double>* __restrict__ blk, const double* __restrict__ r0s, int t,
-                                      const double rn[3], const HistRef& H, int head, const AbParams& ap,
-                                      const EdgeTable& tab, unsigned int& nc, unsigned int& na, unsigned int& ncap) {
+                                      const double rn[3], const HistRef& H, int head, double* s_path,
+                                      const AbParams& ap, const EdgeTable& tab, unsigned int& nc, unsigned int& na, unsigned int& ncap) {
     double P[M + 1][3];
 #pragma unroll
     for (int d = 0; d < 3; ++d) P[0][d] = rn[d];
@@ -302,7 +296,7 @@ __device__ __forceinline__ int walk_m(const TetBlock<double>* __restrict__ blk, 
     for (int j = 1; j <= M; ++j)
 #pragma unroll
         for (int d = 0; d < 3; ++d) P[j][d] = H[3 * ring(head, j - 1) + d];
-    return walk_path<M>(blk, r0s, t, P, ap, tab, nc, na, ncap);
+    return walk_path<M>(blk, r0s, t, P, s_path, ap, tab, nc, na, ncap);
 }
 
 // Cartesian point of barycentric (l1, l2, l3) in a tet: r_0 + G^-1 (l1, l2, l3), G the rows
@@ -318,6 +312,12 @@ __device__ __forceinline__ void point_of(const double* G, const double* r0, doub
     for (int r = 0; r < 3; ++r) x[r] = r0[r] + inv[3 * r] * l1 + inv[3 * r + 1] * l2 + inv[3 * r + 2] * l3;
 }
 
+// Bound by the walks: a wave runs as long as its longest path, with a third of the lanes in
+// the bisections, at three waves per SIMD (167 registers).  300k particles of order 4, mean
+// of electrons and ions: 96.7 us with r(s) evaluated in Cartesian coordinates and arrays
+// indexed by the exit face (scratch memory), 88.4 in barycentric ones with the path in LDS,
+// 86.9 with selects, 85.6 in workgroups of 128 instead of 256 (a finer last round).  Loading
+// all levels of the history at once spilled and was slower (90.8).
 // History of one particle (kAbStride components): three rings of kAbRing levels that share
 // one head h: r^{n-j} at 3 ring(h, j), v^{n-j} at 18 + 3 ring(h, j) and a^{n-1-j} at
 // 36 + 3 ring(h, j); the levels held and h are in the slot's AbMeta.  A step reads at most
@@ -325,7 +325,7 @@ __device__ __forceinline__ void point_of(const double* G, const double* r0, doub
 // one no level of the current state uses), so a step that is not committed leaves the
 // history as it was.  A particle without history (AbMeta -1) takes r^n from its
 // barycentric position and v^n = u, and writes them at slot 0 first.
-__global__ __launch_bounds__(kBlock) void k_push_ab(PArrays<double> in, PArrays<double> out, int64_t n,
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) void k_push_ab(PArrays<double> in, PArrays<double> out, int64_t n,
                                                      const TetBlock<double>* __restrict__ blk,
                                                      const double* __restrict__ r0s, double* __restrict__ hist,
                                                      int64_t hstride, const int32_t* __restrict__ meta_in,
@@ -334,6 +334,7 @@ __global__ __launch_bounds__(kBlock) void k_push_ab(PArrays<double> in, PArrays<
                                                      const int32_t* __restrict__ n_live) {
     __shared__ int s_key[kTableSlots];
     __shared__ double s_val[kTableSlots];
+    __shared__ double s_path[3 * (kAbMax + 1) * kBlock];
     for (int k = threadIdx.x; k < kTableSlots; k += kBlock) {
         s_key[k] = -1;
         s_val[k] = 0.0;
@@ -402,11 +403,11 @@ __global__ __launch_bounds__(kBlock) void k_push_ab(PArrays<double> in, PArrays<
         }
         // the path through r^{n+1}, r^n, ..., r^{n+1-m}, walked with the order in use
         switch (m) {
-            case 1: t = walk_m<1>(blk, r0s, t, rn, H, head, ap, tab, nc, na, ncap); break;
-            case 2: t = walk_m<2>(blk, r0s, t, rn, H, head, ap, tab, nc, na, ncap); break;
-            case 3: t = walk_m<3>(blk, r0s, t, rn, H, head, ap, tab, nc, na, ncap); break;
-            case 4: t = walk_m<4>(blk, r0s, t, rn, H, head, ap, tab, nc, na, ncap); break;
-            default: t = walk_m<5>(blk, r0s, t, rn, H, head, ap, tab, nc, na, ncap); break;
+            case 1: t = walk_m<1>(blk, r0s, t, rn, H, head, s_path + threadIdx.x, ap, tab, nc, na, ncap); break;
+            case 2: t = walk_m<2>(blk, r0s, t, rn, H, head, s_path + threadIdx.x, ap, tab, nc, na, ncap); break;
+            case 3: t = walk_m<3>(blk, r0s, t, rn, H, head, s_path + threadIdx.x, ap, tab, nc, na, ncap); break;
+            case 4: t = walk_m<4>(blk, r0s, t, rn, H, head, s_path + threadIdx.x, ap, tab, nc, na, ncap); break;
+            default: t = walk_m<5>(blk, r0s, t, rn, H, head, s_path + threadIdx.x, ap, tab, nc, na, ncap); break;
         }
         if (t < 0) {
             out.tet[i] = -1;
