@@ -311,7 +311,7 @@ void sort_species(fepic_ctx* c, Species& s) {
         ab.mout = s.d_abm[1 - s.abm_cur];
     }
     launch_sort<T>(c->stream, parr<T>(s, s.cur), parr<T>(s, 1 - s.cur), s.n, c->mesh.n_tets, c->d_count, c->d_offset,
-                   c->d_bsums, s.d_nlive, ab);
+                   c->d_bsums, s.d_nlive, &c->h_stats[&s - c->species.data()].n_live, ab);
     if (ev) (void)hipEventRecord(ev[1], c->stream);
     s.cur = 1 - s.cur;
     s.idcur = 1 - s.idcur;
@@ -343,18 +343,14 @@ void sort_all(fepic_ctx* c) {
 void settle_counts(fepic_ctx* c) {
     for (auto& s : c->species)
         if (s.sorted_pending) {
-            s.n = *s.h_nlive;
+            s.n = c->h_stats[&s - c->species.data()].n_live;
             s.sorted_pending = false;
         }
 }
 
 int sync_counts(fepic_ctx* c) {
     bool any = false;
-    for (auto& s : c->species)
-        if (s.sorted_pending) {
-            HIPCHK(c, hipMemcpyAsync(s.h_nlive, s.d_nlive, sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
-            any = true;
-        }
+    for (const auto& s : c->species) any = any || s.sorted_pending;
     if (!any) return FEPIC_OK;
     HIPCHK(c, hipStreamSynchronize(c->stream));
     settle_counts(c);
@@ -394,16 +390,13 @@ int read_out_plain(fepic_ctx* c, const std::vector<OutArray>& arrays) {
 // into half of it, otherwise the device fills one half while the host empties the other.
 // Ends with everything copied.  Halves of 512 KiB stay in the host's caches: fields of 998k
 // tets (35 MB) took 1.65 ms, with a buffer of 256 KiB 3.5, of 512 KiB 2.2, of 2 to 8 MiB 1.9
-// to 2.0.  (Pinned buffers of less than a MiB also cost 350 us at their first use.)
+// to 2.0.
 constexpr size_t kOutBytes = 1u << 20;
+constexpr size_t kPinTail = 4096;   // behind it: the counters, and the stats of the first species
 
 // The buffer and, for edge vectors, the permutation; false if there is no room for them.
 bool reserve_read_out(fepic_ctx* c, bool edges) {
-    if (!c->h_out && hipHostMalloc((void**)&c->h_out, kOutBytes) != hipSuccess) {
-        (void)hipGetLastError();
-        c->h_out = nullptr;
-        return false;
-    }
+    if (!c->h_out) return false;
     if (edges && !c->d_eperm) {
         const std::string err = c->err;
         if (upload(c, &c->d_eperm, c->mesh.eperm) != FEPIC_OK) {
@@ -563,6 +556,36 @@ CrossQueue<T> cqueue(fepic_ctx* c) {
     return q;
 }
 
+// Room for the counter slots and stats of n species.
+int fit_species(fepic_ctx* c, int n) {
+    if (n > c->slot_species) {
+        const int cap = std::max(n, 2 * c->slot_species);
+        PushCounters* p = dalloc<PushCounters>(c, (int64_t)kCntSlots * cap);
+        if (!p) return fail(c, FEPIC_E_OOM, "allocation failed");
+        HIPCHK(c, hipMemsetAsync(p, 0, sizeof(PushCounters) * kCntSlots * cap, c->stream));
+        HIPCHK(c, hipStreamSynchronize(c->stream));   // a step's counters are folded before it returns
+        dfree(c, c->d_cnt_slots);
+        c->d_cnt_slots = p;
+        c->slot_species = cap;
+    }
+    if (n > c->stat_species) {
+        SpeciesStat* p = nullptr;
+        const int cap = 2 * n;
+        HIPCHK(c, hipStreamSynchronize(c->stream));
+        if (hipHostMalloc((void**)&p, sizeof(SpeciesStat) * cap) != hipSuccess) return fail(c, FEPIC_E_OOM, "allocation failed");
+        std::memset(p, 0, sizeof(SpeciesStat) * cap);
+        std::memcpy(p, c->h_stats, sizeof(SpeciesStat) * c->stat_species);
+        if (c->stats_own) (void)hipHostFree(c->h_stats);
+        c->h_stats = p;
+        c->stat_species = cap;
+        c->stats_own = true;
+    }
+    return FEPIC_OK;
+}
+
+// The species' set of counter slots.
+PushCounters* cnt_slots(fepic_ctx* c, const Species& s) { return c->d_cnt_slots + kCntSlots * (&s - c->species.data()); }
+
 // The injectors' particles of this step, drawn on the device and appended after the sort
 // (the push moves them with the rest, their charge joins rho^n when diagnostics run);
 // inject_undo drops them again when the step is not committed.
@@ -641,11 +664,10 @@ void particle_phase_T(fepic_ctx* c, double dt, bool do_sort) {
         hipEvent_t* ev = timer_pair(c, FAM_STAGE);
         if (ev) (void)hipEventRecord(ev[0], c->stream);
         launch_stage<T>(c->stream, c->mesh.n_tets, (TetBlock<T>*)c->d_blk, c->d_e, c->d_b, c->d_grad64,
-                        c->d_tet_edges, c->d_tet_faces);
+                        c->d_tet_edges, c->d_tet_faces, c->d_dgn, c->mesh.n_edges);
         if (ev) (void)hipEventRecord(ev[1], c->stream);
     }
     ev_mark(c, 2);
-    launch_fill(c->stream, c->d_dgn, c->mesh.n_edges, 0.0);
     if (ensure_queue(c) != FEPIC_OK) {
         c->deferred_err = FEPIC_E_OOM;
         return;
@@ -668,20 +690,13 @@ void particle_phase_T(fepic_ctx* c, double dt, bool do_sort) {
         hipEvent_t* ev = timer_pair(c, FAM_PUSH);
         if (ev) (void)hipEventRecord(ev[0], c->stream);
         launch_push<T>(c->stream, parr<T>(s, s.cur), parr<T>(s, 1 - s.cur), s.n, (const TetBlock<T>*)c->d_blk,
-                       c->d_dgn, pp, c->d_cnt_slots, s.sorted_pending ? s.d_nlive : nullptr, cqueue<T>(c),
+                       c->d_dgn, pp, cnt_slots(c, s), s.sorted_pending ? s.d_nlive : nullptr, cqueue<T>(c),
                        c->cross_share, s.own_share, c->opt.walk);
         if (ev) (void)hipEventRecord(ev[1], c->stream);
         s.n_pushed = s.n;
-        launch_cnt_crossings(c->stream, c->d_cnt_slots, s.d_xcum);
-        const hipError_t xe = hipMemcpyAsync(s.h_xcum, s.d_xcum, 2 * sizeof(unsigned long long),
-                                             hipMemcpyDeviceToHost, c->stream);
-        if (xe != hipSuccess) {
-            c->deferred_err = hip_fail(c, xe, "hipMemcpyAsync(crossing count)");
-            return;
-        }
     }
     if (fix) launch_fix_out(c->stream, fix, c->mesh.n_edges, scale, c->d_dgn);
-    launch_cnt_finish(c->stream, c->d_cnt_slots, c->d_cnt);
+    launch_cnt_finish(c->stream, c->d_cnt_slots, (int)c->species.size(), c->d_cnt, c->h_cnt, c->h_stats);
     ev_mark(c, 3);
 }
 
@@ -744,11 +759,10 @@ void particle_phase_ab(fepic_ctx* c, double dt, bool do_sort) {
         hipEvent_t* ev = timer_pair(c, FAM_STAGE);
         if (ev) (void)hipEventRecord(ev[0], c->stream);
         launch_stage<double>(c->stream, c->mesh.n_tets, (TetBlock<double>*)c->d_blk, c->d_e, c->d_b, c->d_grad64,
-                             c->d_tet_edges, c->d_tet_faces);
+                             c->d_tet_edges, c->d_tet_faces, c->d_dgn, c->mesh.n_edges);
         if (ev) (void)hipEventRecord(ev[1], c->stream);
     }
     ev_mark(c, 2);
-    launch_fill(c->stream, c->d_dgn, c->mesh.n_edges, 0.0);
     AbParams ap;
     ab_tables(ap);
     ap.dt = dt;
@@ -770,19 +784,12 @@ void particle_phase_ab(fepic_ctx* c, double dt, bool do_sort) {
         if (ev) (void)hipEventRecord(ev[0], c->stream);
         launch_push_ab(c->stream, parr<double>(s, s.cur), parr<double>(s, 1 - s.cur), s.n,
                        (const TetBlock<double>*)c->d_blk, c->d_r0, s.d_abh[s.abh_cur], s.abh_cap, s.d_abm[s.abm_cur],
-                       s.d_abm[1 - s.abm_cur], c->d_dgn, ap, c->d_cnt_slots, s.sorted_pending ? s.d_nlive : nullptr);
+                       s.d_abm[1 - s.abm_cur], c->d_dgn, ap, cnt_slots(c, s), s.sorted_pending ? s.d_nlive : nullptr);
         if (ev) (void)hipEventRecord(ev[1], c->stream);
         s.n_pushed = s.n;
-        launch_cnt_crossings(c->stream, c->d_cnt_slots, s.d_xcum);
-        const hipError_t xe = hipMemcpyAsync(s.h_xcum, s.d_xcum, 2 * sizeof(unsigned long long),
-                                             hipMemcpyDeviceToHost, c->stream);
-        if (xe != hipSuccess) {
-            c->deferred_err = hip_fail(c, xe, "hipMemcpyAsync(crossing count)");
-            return;
-        }
     }
     if (fix) launch_fix_out(c->stream, fix, c->mesh.n_edges, scale, c->d_dgn);
-    launch_cnt_finish(c->stream, c->d_cnt_slots, c->d_cnt);
+    launch_cnt_finish(c->stream, c->d_cnt_slots, (int)c->species.size(), c->d_cnt, c->h_cnt, c->h_stats);
     ev_mark(c, 3);
 }
 
@@ -1462,7 +1469,6 @@ int do_step(fepic_ctx* c, double dt, double beta, double gamma, fepic_step_stats
         int rc = field_phase(c, dt, beta, gamma);
         if (rc != FEPIC_OK) return rc;
     }
-    HIPCHK(c, hipMemcpyAsync(c->h_cnt, c->d_cnt, sizeof(PushCounters), hipMemcpyDeviceToHost, c->stream));
     int rc = sync_counts(c);
     if (rc != FEPIC_OK) return rc;
     HIPCHK(c, hipStreamSynchronize(c->stream));
@@ -1472,19 +1478,14 @@ int do_step(fepic_ctx* c, double dt, double beta, double gamma, fepic_step_stats
         int64_t n_all = 0;
         for (const auto& sp : c->species) n_all += sp.n;
         c->cross_share = n_all > 0 ? (double)st.n_crossings / (double)n_all : 1.0;
-        // each species' own crossings and losses: the running counts read after each
-        // species' kernels, differenced in push order (a species without particles keeps
-        // its last share); its crossings per particle choose its crossing-walk form at the
-        // next step, and crossings plus losses count towards its re-binning
-        unsigned long long prev = 0, prev_gone = 0;
+        // each species' own crossings and losses (a species without particles keeps its last
+        // share): its crossings per particle choose its crossing-walk form at the next step,
+        // and crossings plus losses count towards its re-binning
         for (auto& sp : c->species) {
             if (sp.n_pushed <= 0) continue;
-            const unsigned long long cum = sp.h_xcum[0], gone = sp.h_xcum[1];
-            const unsigned long long own = cum >= prev ? cum - prev : 0, own_gone = gone >= prev_gone ? gone - prev_gone : 0;
-            sp.own_share = (double)own / (double)sp.n_pushed;
-            sp.moved += (int64_t)(own + own_gone);
-            prev = cum;
-            prev_gone = gone;
+            const SpeciesStat& own = c->h_stats[&sp - c->species.data()];
+            sp.own_share = (double)own.crossings / (double)sp.n_pushed;
+            sp.moved += (int64_t)(own.crossings + own.gone);
             sp.n_pushed = 0;
         }
     }
@@ -1758,12 +1759,25 @@ int fepic_create(const fepic_options* opts, fepic_ctx** out) {
             return FEPIC_E_HIP;
         }
         c->stream = c->own_stream;
-        if (hipHostMalloc((void**)&c->h_sc, sizeof(CgScalars)) != hipSuccess ||
-            hipHostMalloc((void**)&c->h_cnt, sizeof(PushCounters)) != hipSuccess ||
+        // one pinned block that kernels write (blocks of less than a MiB cost 350 us at their
+        // first use); without room for the read-outs' part, the counters' alone
+        if (hipHostMalloc((void**)&c->h_pin, kOutBytes + kPinTail) == hipSuccess) {
+            c->h_out = c->h_pin;
+        } else {
+            (void)hipGetLastError();
+            c->h_pin = nullptr;
+        }
+        if ((!c->h_pin && hipHostMalloc((void**)&c->h_pin, kPinTail) != hipSuccess) ||
+            hipHostMalloc((void**)&c->h_sc, sizeof(CgScalars)) != hipSuccess ||
             hipHostMalloc((void**)&c->h_acc, sizeof(DiagAcc)) != hipSuccess) {
             delete c;
             return FEPIC_E_OOM;
         }
+        unsigned char* const tail = c->h_pin + (c->h_out ? kOutBytes : 0);
+        std::memset(tail, 0, kPinTail);
+        c->h_cnt = reinterpret_cast<PushCounters*>(tail);
+        c->h_stats = reinterpret_cast<SpeciesStat*>(tail + 128);
+        c->stat_species = (int)((kPinTail - 128) / sizeof(SpeciesStat));
         for (auto& e : c->phase_ev) (void)hipEventCreate(&e);
     }
     *out = c;
@@ -1776,17 +1790,13 @@ int fepic_destroy(fepic_ctx* c) {
         (void)hipSetDevice(c->opt.device);
         (void)hipStreamSynchronize(c->stream);
         for (void* p : c->allocs) release(c, p);
-        for (auto& s : c->species) {
-            if (s.h_nlive) (void)hipHostFree(s.h_nlive);
-            if (s.h_xcum) (void)hipHostFree(s.h_xcum);
-        }
+        if (c->stats_own) (void)hipHostFree(c->h_stats);
         for (auto& t : c->timers)
             for (auto e : t.ev) (void)hipEventDestroy(e);
         for (auto e : c->phase_ev) (void)hipEventDestroy(e);
         if (c->h_sc) (void)hipHostFree(c->h_sc);
-        if (c->h_cnt) (void)hipHostFree(c->h_cnt);
         if (c->h_acc) (void)hipHostFree(c->h_acc);
-        if (c->h_out) (void)hipHostFree(c->h_out);
+        if (c->h_pin) (void)hipHostFree(c->h_pin);
         for (hipEvent_t e : c->out_ev)
             if (e) (void)hipEventDestroy(e);
         if (c->h_stage) (void)hipHostFree(c->h_stage);
@@ -2059,15 +2069,15 @@ int fepic_upload_mesh(fepic_ctx* c, int64_t n_nodes, const double* xyz, int64_t 
     c->d_partial = dalloc<double>(c, (int64_t)partial_buffer_doubles());
     c->d_sc = dalloc<CgScalars>(c, 1);
     c->d_cnt = dalloc<PushCounters>(c, 1);
-    c->d_cnt_slots = dalloc<PushCounters>(c, kCntSlots);
-    if (c->d_cnt_slots) HIPCHK(c, hipMemset(c->d_cnt_slots, 0, sizeof(PushCounters) * kCntSlots));
+    if ((rc = fit_species(c, std::max<int>(4, (int)c->species.size())))) return rc;
     c->d_acc = dalloc<DiagAcc>(c, 1);
     c->d_dotc = dalloc<unsigned int>(c, 1);
     c->d_live = dalloc<double>(c, 1);
     c->d_count = dalloc<int32_t>(c, nt);
+    if (c->d_count) HIPCHK(c, hipMemset(c->d_count, 0, sizeof(int32_t) * nt));   // each sort leaves it zero
     c->d_offset = dalloc<int32_t>(c, nt);
     c->d_bsums = dalloc<int32_t>(c, nt / 1024 + 2);
-    if (!c->d_A || !c->d_dinv || !c->d_partial || !c->d_sc || !c->d_cnt || !c->d_cnt_slots || !c->d_acc || !c->d_count ||
+    if (!c->d_A || !c->d_dinv || !c->d_partial || !c->d_sc || !c->d_cnt || !c->d_acc || !c->d_count ||
         !c->d_offset || !c->d_bsums || !c->d_dotc || !c->d_live)
         return fail(c, FEPIC_E_OOM, "device allocation failed");
     HIPCHK(c, hipMemset(c->d_sc, 0, sizeof(CgScalars)));
@@ -2172,11 +2182,12 @@ int fepic_add_species(fepic_ctx* c, double q, double m, double w, int* out) {
     s.m = m;
     s.w = w;
     s.d_nlive = dalloc<int32_t>(c, 1);
-    s.d_xcum = dalloc<unsigned long long>(c, 2);
-    if (!s.d_nlive || !s.d_xcum || hipHostMalloc((void**)&s.h_nlive, sizeof(int32_t)) != hipSuccess ||
-        hipHostMalloc((void**)&s.h_xcum, 2 * sizeof(unsigned long long)) != hipSuccess)
-        return fail(c, FEPIC_E_OOM, "allocation failed");
-    s.h_xcum[0] = s.h_xcum[1] = 0;
+    if (!s.d_nlive) return fail(c, FEPIC_E_OOM, "allocation failed");
+    const int rc = fit_species(c, (int)c->species.size() + 1);
+    if (rc) {
+        dfree(c, s.d_nlive);
+        return rc;
+    }
     c->species.push_back(s);
     if (out) *out = (int)c->species.size() - 1;
     return FEPIC_OK;

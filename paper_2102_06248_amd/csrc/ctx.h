@@ -34,13 +34,8 @@ struct Species {
     // arrays have their own current index, flipped only by the sort.
     int idcur = 0;
     int32_t* d_nlive = nullptr;
-    int32_t* h_nlive = nullptr;
-    // face crossings of the step so far, counted after this species' particle kernels (its
-    // own crossings are the difference to the previous species'), and the species' own
-    // crossings per particle at its last committed step
-    unsigned long long* d_xcum = nullptr;   // [2]: crossings, and absorptions + paths cut at the cap
-    unsigned long long* h_xcum = nullptr;
     int64_t n_pushed = 0;
+    // the species' own crossings per particle at its last committed step
     double own_share = 1.0;
     // FEPIC_SORT_AUTO: particles that left their tet or the mesh since the species' last
     // re-binning (face crossings counted), and whether particles were added since
@@ -118,7 +113,8 @@ struct fepic_ctx {
     int32_t *d_mf_col = nullptr, *d_ef_inc = nullptr;
     double *d_mf_val = nullptr, *d_h = nullptr;
     double *d_rhs = nullptr, *d_rt = nullptr, *d_Me = nullptr;
-    unsigned char* h_out = nullptr;                // pinned, read-outs pass through it
+    unsigned char* h_pin = nullptr;                // pinned: h_out if there was room, h_cnt, h_stats
+    unsigned char* h_out = nullptr;                // read-outs pass through it (null: plain copies)
     hipEvent_t out_ev[2] = {nullptr, nullptr};     // its halves are written
     int32_t* d_eperm = nullptr;                    // canonical edge id -> device edge id
     unsigned long long* d_boxes = nullptr;         // values exchanged within a one-launch Jacobi solve
@@ -144,7 +140,11 @@ struct fepic_ctx {
     fepic::CgScalars* d_sc = nullptr;
     fepic::CgScalars* h_sc = nullptr;
     fepic::PushCounters* d_cnt = nullptr;
-    fepic::PushCounters* d_cnt_slots = nullptr;   // [kCntSlots], zero between steps
+    fepic::PushCounters* d_cnt_slots = nullptr;   // [slot_species][kCntSlots], zero between steps
+    int slot_species = 0;
+    fepic::SpeciesStat* h_stats = nullptr;        // [stat_species], pinned: in h_pin or of their own
+    int stat_species = 0;
+    bool stats_own = false;
     unsigned char* d_cq = nullptr;                 // crossing queue storage (CrossQueue arrays)
     int64_t cq_cap = 0;                            // its capacity in slots (multiple of 256)
     double cross_share = 1.0;                      // face crossings per particle, last step

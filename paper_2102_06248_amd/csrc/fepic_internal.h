@@ -75,7 +75,7 @@ struct PushParams {
 };
 
 // The particle kernel adds its per-workgroup counts into kCntSlots copies of the counters
-// (workgroup b -> slot b mod kCntSlots); launch_cnt_finish folds them into one.
+// (workgroup b -> slot b mod kCntSlots), a set per species; launch_cnt_finish folds them into one.
 constexpr int kCntSlots = 256;
 
 // Adams-Bashforth pusher (all-FP64): orders 1..kAbMax, a history of kAbStride doubles per
@@ -108,6 +108,14 @@ struct PushCounters {
     unsigned int n_cap;
     unsigned int n_rejected;
     unsigned int pad[2];
+};
+
+// What the device reports of each species, in pinned host memory that the kernels write:
+// the face crossings of a step, its absorptions and paths stopped at the crossing cap, and
+// the live particles counted by the last sort.
+struct SpeciesStat {
+    unsigned long long crossings, gone;
+    int32_t n_live, pad[3];
 };
 
 // Scalars of the PCG recurrence, kept on the device between kernels.
@@ -258,15 +266,16 @@ struct SellMatrix {
 // Particle kernels (kernels_particles.hip).
 template <typename T>
 void launch_stage(hipStream_t s, int64_t n_tets, TetBlock<T>* blk, const double* e, const double* b,
-                  const double* grad64, const int32_t* tet_edges, const int32_t* tet_faces);
+                  const double* grad64, const int32_t* tet_edges, const int32_t* tet_faces, double* zero,
+                  int64_t n_zero);
 template <typename T>
 void launch_push(hipStream_t s, PArrays<T> in, PArrays<T> out, int64_t n, const TetBlock<T>* blk, double* dg,
                  PushParams pp, PushCounters* cnt, const int32_t* n_live, CrossQueue<T> cq, double cross_share,
                  double own_share, int walk);
-void launch_cnt_finish(hipStream_t s, PushCounters* slots, PushCounters* out);
-// The face crossings the slots hold so far (summed over the slots) into out[0], the
-// absorptions and paths stopped at the crossing cap into out[1].
-void launch_cnt_crossings(hipStream_t s, const PushCounters* slots, unsigned long long* out);
+// The species' sets of slots into stats (host-visible) and, summed, into out and host (the
+// same, host-visible); the slots are cleared.
+void launch_cnt_finish(hipStream_t s, PushCounters* slots, int n_species, PushCounters* out, PushCounters* host,
+                       SpeciesStat* stats);
 template <typename T>
 void launch_locate(hipStream_t s, int64_t n, const double* x, const double* u, const int64_t* id, int64_t id_base,
                    PArrays<T> out, int64_t out_off, const double* grad64, const double* r0, const int32_t* cell_start,
@@ -294,7 +303,8 @@ struct AbHistIo {
 };
 template <typename T>
 void launch_sort(hipStream_t s, PArrays<T> in, PArrays<T> out, int64_t n, int64_t n_tets, int32_t* count,
-                 int32_t* offset, int32_t* block_sums, int32_t* n_live_dev, AbHistIo ab = AbHistIo());
+                 int32_t* offset, int32_t* block_sums, int32_t* n_live_dev, int32_t* n_live_host,
+                 AbHistIo ab = AbHistIo());
 // rho += q w lambda per particle (FP64 atomics), or with fix into fixed-point accumulators
 // in units of 1 / fix_inv (deterministic mode; rho untouched).
 template <typename T>

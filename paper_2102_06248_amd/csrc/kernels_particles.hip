@@ -50,8 +50,10 @@ __global__ __launch_bounds__(kBlock) void k_stage(int64_t n_tets, TetBlock<T>* _
                                                    const double* __restrict__ e, const double* __restrict__ b,
                                                    const double* __restrict__ grad64,
                                                    const int32_t* __restrict__ tet_edges,
-                                                   const int32_t* __restrict__ tet_faces) {
+                                                   const int32_t* __restrict__ tet_faces,
+                                                   double* __restrict__ zero, int64_t n_zero) {
     int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    for (int64_t i = t; i < n_zero; i += (int64_t)gridDim.x * kBlock) zero[i] = 0.0;   // the step's currents
     if (t >= n_tets) return;
     TetBlock<T>* B = blk + t;
 #pragma unroll
@@ -708,57 +710,57 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(walk_waves<T
 template <typename T>
 constexpr unsigned sparse_grid() { return 256u * 4u * (unsigned)walk_waves<T>(); }
 
-// Face crossings counted so far in this step (the slots' running sum) into out[0], and the
-// absorptions plus paths stopped at the crossing cap into out[1].
-__global__ __launch_bounds__(kCntSlots) void k_cnt_crossings(const PushCounters* __restrict__ slots,
-                                                             unsigned long long* __restrict__ out) {
-    __shared__ unsigned long long s_c[kCntSlots], s_a[kCntSlots];
-    const int t = threadIdx.x;
-    s_c[t] = slots[t].n_crossings;
-    s_a[t] = (unsigned long long)slots[t].n_absorbed + slots[t].n_cap;
-    __syncthreads();
-    for (int h = kCntSlots / 2; h > 0; h >>= 1) {
-        if (t < h) {
-            s_c[t] += s_c[t + h];
-            s_a[t] += s_a[t + h];
+// Each species' slots into its stats and, summed over the species, into *out; the slots are
+// cleared for the next step.  stats and host are pinned host memory, so that no copies
+// follow: as a kernel and a copy per species, a kernel and a copy for the sums, the counters
+// took 28 us of a push of two species (now 6).
+__global__ __launch_bounds__(kCntSlots) void k_cnt_finish(PushCounters* __restrict__ slots, int n_species,
+                                                          PushCounters* __restrict__ out,
+                                                          PushCounters* __restrict__ host,
+                                                          SpeciesStat* __restrict__ stats) {
+    constexpr int NW = kCntSlots / 64;
+    __shared__ unsigned long long s_c[NW];
+    __shared__ unsigned int s_m[NW], s_a[NW], s_p[NW];
+    const int t = threadIdx.x, w = t >> 6;
+    PushCounters r{};
+    for (int k = 0; k < n_species; ++k) {
+        const PushCounters v = slots[k * kCntSlots + t];
+        slots[k * kCntSlots + t] = PushCounters{};
+        unsigned long long c = v.n_crossings;
+        unsigned int m = v.max_crossings, a = v.n_absorbed, p = v.n_cap;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            c += __shfl_xor(c, off);
+            m = max(m, (unsigned int)__shfl_xor(m, off));
+            a += __shfl_xor(a, off);
+            p += __shfl_xor(p, off);
+        }
+        if ((t & 63) == 0) {
+            s_c[w] = c;
+            s_m[w] = m;
+            s_a[w] = a;
+            s_p[w] = p;
+        }
+        __syncthreads();
+        if (t == 0) {
+            unsigned long long own = 0, gone = 0;
+#pragma unroll
+            for (int q = 0; q < NW; ++q) {
+                own += s_c[q];
+                gone += (unsigned long long)s_a[q] + s_p[q];
+                r.max_crossings = max(r.max_crossings, s_m[q]);
+                r.n_absorbed += s_a[q];
+                r.n_cap += s_p[q];
+            }
+            r.n_crossings += own;
+            stats[k].crossings = own;
+            stats[k].gone = gone;
         }
         __syncthreads();
     }
     if (t == 0) {
-        out[0] = s_c[0];
-        out[1] = s_a[0];
-    }
-}
-
-// Folds the per-slot push counters into *out and clears the slots for the next step.
-__global__ __launch_bounds__(kCntSlots) void k_cnt_finish(PushCounters* __restrict__ slots,
-                                                          PushCounters* __restrict__ out) {
-    __shared__ unsigned long long s_c[kCntSlots];
-    __shared__ unsigned int s_m[kCntSlots], s_a[kCntSlots], s_p[kCntSlots];
-    const int t = threadIdx.x;
-    PushCounters v = slots[t];
-    s_c[t] = v.n_crossings;
-    s_m[t] = v.max_crossings;
-    s_a[t] = v.n_absorbed;
-    s_p[t] = v.n_cap;
-    slots[t] = PushCounters{};
-    __syncthreads();
-    for (int h = kCntSlots / 2; h > 0; h >>= 1) {
-        if (t < h) {
-            s_c[t] += s_c[t + h];
-            s_m[t] = max(s_m[t], s_m[t + h]);
-            s_a[t] += s_a[t + h];
-            s_p[t] += s_p[t + h];
-        }
-        __syncthreads();
-    }
-    if (t == 0) {
-        PushCounters r{};
-        r.n_crossings = s_c[0];
-        r.max_crossings = s_m[0];
-        r.n_absorbed = s_a[0];
-        r.n_cap = s_p[0];
         *out = r;
+        *host = r;
     }
 }
 
@@ -826,11 +828,6 @@ __global__ __launch_bounds__(kBlock) void k_locate(int64_t n, const double* __re
 }
 
 // ------------------------------------------------------------------------- counting sort
-__global__ __launch_bounds__(kBlock) void k_zero_i32(int32_t* p, int64_t n) {
-    int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i < n) p[i] = 0;
-}
-
 // Lanes of a wave grouped by key, in any order: for each lane with key >= 0 its group's
 // leader (lowest lane), its rank among the group's lanes and the group's size; one pass
 // per distinct key.  Between sorts the particles stay nearly sorted, but those that
@@ -885,7 +882,8 @@ __device__ __forceinline__ int block_excl_scan(int v, int* s_w, int& total) {
 
 constexpr int kScanItems = 4;  // per thread; 1024 per block
 
-__global__ __launch_bounds__(kBlock) void k_scan_blocks(const int32_t* __restrict__ in, int32_t* __restrict__ out,
+// Per-block exclusive scan of the counts, which are left zero for the next sort.
+__global__ __launch_bounds__(kBlock) void k_scan_blocks(int32_t* __restrict__ in, int32_t* __restrict__ out,
                                                          int64_t n, int32_t* __restrict__ block_sums) {
     __shared__ int s_w[4];
     const int64_t base = ((int64_t)blockIdx.x * kBlock + threadIdx.x) * kScanItems;
@@ -895,6 +893,7 @@ __global__ __launch_bounds__(kBlock) void k_scan_blocks(const int32_t* __restric
     for (int k = 0; k < kScanItems; ++k) {
         v[k] = (base + k < n) ? in[base + k] : 0;
         sum += v[k];
+        if (base + k < n) in[base + k] = 0;
     }
     int total;
     int run = block_excl_scan(sum, s_w, total);
@@ -906,30 +905,19 @@ __global__ __launch_bounds__(kBlock) void k_scan_blocks(const int32_t* __restric
     if (threadIdx.x == 0) block_sums[blockIdx.x] = total;
 }
 
-// Single block: exclusive scan of the block sums in place; total -> *n_total.
-__global__ __launch_bounds__(kBlock) void k_scan_top(int32_t* block_sums, int64_t nb, int32_t* n_total) {
-    __shared__ int s_w[4];
-    const int64_t per = (nb + kBlock - 1) / kBlock;
-    const int64_t b0 = threadIdx.x * per;
-    int sum = 0;
-    for (int64_t k = 0; k < per; ++k)
-        if (b0 + k < nb) sum += block_sums[b0 + k];
-    int total;
-    int run = block_excl_scan(sum, s_w, total);
-    for (int64_t k = 0; k < per; ++k) {
-        if (b0 + k < nb) {
-            const int v = block_sums[b0 + k];
-            block_sums[b0 + k] = run;
-            run += v;
-        }
-    }
-    if (threadIdx.x == 0) *n_total = total;
-}
-
+// The sums of the blocks before it added to each block's scan; the last one reports the
+// total.  Every block sums the up to a thousand sums itself: a scan of them by one block,
+// between the two kernels, was a launch and 2.3 us more.
 __global__ __launch_bounds__(kBlock) void k_scan_add(int32_t* __restrict__ out, int64_t n,
-                                                      const int32_t* __restrict__ block_sums) {
+                                                      const int32_t* __restrict__ block_sums,
+                                                      int32_t* __restrict__ n_total, int32_t* __restrict__ n_total_host) {
+    __shared__ int s_w[4];
+    int before = 0;
+    for (unsigned k = threadIdx.x; k < blockIdx.x; k += kBlock) before += block_sums[k];
+    int add;
+    block_excl_scan(before, s_w, add);
+    if (threadIdx.x == 0 && blockIdx.x == gridDim.x - 1) *n_total = *n_total_host = add + block_sums[blockIdx.x];
     const int64_t base = ((int64_t)blockIdx.x * kBlock + threadIdx.x) * kScanItems;
-    const int add = block_sums[blockIdx.x];
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k)
         if (base + k < n) out[base + k] += add;
@@ -1165,20 +1153,18 @@ void launch_kinetic(hipStream_t s, PArrays<T> p, int64_t n, double wmc2, double*
                        p, n, wmc2, out);
 }
 
-void launch_cnt_finish(hipStream_t s, PushCounters* slots, PushCounters* out) {
-    hipLaunchKernelGGL(k_cnt_finish, dim3(1), dim3(kCntSlots), 0, s, slots, out);
-}
-
-void launch_cnt_crossings(hipStream_t s, const PushCounters* slots, unsigned long long* out) {
-    hipLaunchKernelGGL(k_cnt_crossings, dim3(1), dim3(kCntSlots), 0, s, slots, out);
+void launch_cnt_finish(hipStream_t s, PushCounters* slots, int n_species, PushCounters* out, PushCounters* host,
+                       SpeciesStat* stats) {
+    hipLaunchKernelGGL(k_cnt_finish, dim3(1), dim3(kCntSlots), 0, s, slots, n_species, out, host, stats);
 }
 
 template <typename T>
 void launch_stage(hipStream_t s, int64_t n_tets, TetBlock<T>* blk, const double* e, const double* b,
-                  const double* grad64, const int32_t* tet_edges, const int32_t* tet_faces) {
+                  const double* grad64, const int32_t* tet_edges, const int32_t* tet_faces, double* zero,
+                  int64_t n_zero) {
     if (n_tets <= 0) return;
     hipLaunchKernelGGL(k_stage<T>, dim3(grid_1d(n_tets, kBlock)), dim3(kBlock), 0, s, n_tets, blk, e, b, grad64,
-                       tet_edges, tet_faces);
+                       tet_edges, tet_faces, zero, n_zero);
 }
 
 // Crossings per particle (last step) above which the particle step is one kernel, and that
@@ -1238,15 +1224,14 @@ void launch_locate(hipStream_t s, int64_t n, const double* x, const double* u, c
 
 template <typename T>
 void launch_sort(hipStream_t s, PArrays<T> in, PArrays<T> out, int64_t n, int64_t n_tets, int32_t* count,
-                 int32_t* offset, int32_t* block_sums, int32_t* n_live_dev, AbHistIo ab) {
-    hipLaunchKernelGGL(k_zero_i32, dim3(grid_1d(n_tets, kBlock)), dim3(kBlock), 0, s, count, n_tets);
+                 int32_t* offset, int32_t* block_sums, int32_t* n_live_dev, int32_t* n_live_host, AbHistIo ab) {
     if (n > 0)
         hipLaunchKernelGGL(k_hist, dim3(grid_1d(n, kBlock)), dim3(kBlock), 0, s, in.tet, n, count);
     const int64_t per_block = (int64_t)kBlock * kScanItems;
     const int64_t nb = (n_tets + per_block - 1) / per_block;
     hipLaunchKernelGGL(k_scan_blocks, dim3((unsigned)nb), dim3(kBlock), 0, s, count, offset, n_tets, block_sums);
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kBlock), 0, s, block_sums, nb, n_live_dev);
-    hipLaunchKernelGGL(k_scan_add, dim3((unsigned)nb), dim3(kBlock), 0, s, offset, n_tets, block_sums);
+    hipLaunchKernelGGL(k_scan_add, dim3((unsigned)nb), dim3(kBlock), 0, s, offset, n_tets, block_sums, n_live_dev,
+                       n_live_host);
     if (n > 0)
         hipLaunchKernelGGL(k_scatter<T>, dim3(grid_1d(n, kBlock)), dim3(kBlock), 0, s, in, out, n, offset, ab);
 }
@@ -1268,14 +1253,14 @@ void launch_fix_out(hipStream_t s, unsigned long long* acc, int64_t n, double sc
 
 #define FEPIC_INSTANTIATE(T)                                                                                      \
     template void launch_stage<T>(hipStream_t, int64_t, TetBlock<T>*, const double*, const double*,             \
-                                  const double*, const int32_t*, const int32_t*);                                \
+                                  const double*, const int32_t*, const int32_t*, double*, int64_t);                                \
     template void launch_push<T>(hipStream_t, PArrays<T>, PArrays<T>, int64_t, const TetBlock<T>*, double*,      \
                                  PushParams, PushCounters*, const int32_t*, CrossQueue<T>, double, double, int); \
     template void launch_locate<T>(hipStream_t, int64_t, const double*, const double*, const int64_t*, int64_t,  \
                                    PArrays<T>, int64_t, const double*, const double*, const int32_t*,            \
                                    const int32_t*, const double*, const double*, const int32_t*, PushCounters*); \
     template void launch_sort<T>(hipStream_t, PArrays<T>, PArrays<T>, int64_t, int64_t, int32_t*, int32_t*,      \
-                                 int32_t*, int32_t*, AbHistIo);                                                  \
+                                 int32_t*, int32_t*, int32_t*, AbHistIo);                                                  \
     template void launch_rho<T>(hipStream_t, PArrays<T>, int64_t, const int32_t*, double, double*,                 \
                                 unsigned long long*, double);                                                     \
     template void launch_kinetic<T>(hipStream_t, PArrays<T>, int64_t, double, double*);
