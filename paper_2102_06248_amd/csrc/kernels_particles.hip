@@ -1217,16 +1217,17 @@ void launch_push(hipStream_t s, PArrays<T> in, PArrays<T> out, int64_t n, const 
                        cq);
     // a species whose paths rarely cross: resident one-wave workgroups visit the few
     // non-empty queue regions; otherwise one k_cross workgroup per k_push workgroup, sized
-    // for its expected queue length: a width for the species' own crossings, so that a
-    // region's paths take one turn (4M electrons on 998k tets, 0.3 crossings each, or 77
-    // paths a region: 64 threads 207 us, 128 threads 197 us).  The share of all species
+    // for its expected queue length, by the species' own crossings, so that a region's paths
+    // take about one turn (4M electrons on 998k tets, 0.3 crossings each, or 77 paths a
+    // region: 64 threads 207 us, 128 threads 197 us; 32M on 8M tets, 0.6 each: 128 threads
+    // 5.3 ms of particle kernels per step, 256 threads 5.7).  The share of all species
     // together would halve the width where one of two species stands still
     if (own_share < kSparseShare)
         hipLaunchKernelGGL((k_cross_sparse<T>), dim3(std::min<unsigned>(n_wg, sparse_grid<T>())), dim3(64), 0, s, out,
                            cq, (int64_t)n_wg, blk, dg, pp, cnt);
     else if (own_share <= 0.25)
         hipLaunchKernelGGL((k_cross<T, 64>), dim3(n_wg), dim3(64), 0, s, out, cq, blk, dg, pp, cnt);
-    else if (own_share <= 0.5)
+    else if (own_share <= 0.75)
         hipLaunchKernelGGL((k_cross<T, 128>), dim3(n_wg), dim3(128), 0, s, out, cq, blk, dg, pp, cnt);
     else
         hipLaunchKernelGGL((k_cross<T, 256>), dim3(n_wg), dim3(256), 0, s, out, cq, blk, dg, pp, cnt);
