@@ -39,6 +39,8 @@ KERNEL_NAMES = {"push": "k_push+k_cross|k_cross_sparse", "stage": "k_stage", "so
                 "faraday": "k_faraday"}
 MIXED_ITER_KERNEL = "k_pcg_q<float>+k_pcg_nodes<float>+k_pcg_fold<float>+k_pcg_update<float, 2>"
 JACOBI_ITER_KERNEL = "k_cg_iter"
+ONE_LAUNCH_KERNEL = "k_pcg_solve"   # a whole solve; figures per iteration
+ONE_LAUNCH_ROWS = 2 * 256 * 512     # two row blocks for each CU
 KERNEL_SOURCES = {"push": "kernels_particles.hip", "stage": "kernels_particles.hip", "sort": "kernels_particles.hip",
                   "rhs": "kernels_fields.hip", "cg_iter": "kernels_fields.hip", "faraday": "kernels_fields.hip"}
 EXTRA_DEFAULT = "c1_single_electron,c2_beam,c3_plasma"
@@ -68,7 +70,8 @@ def push_bytes(n_particles, occupied, crossings, precision=0):
 def algorithmic_bytes(fam, geo, st, pc="aux", solve="fp64", precision=0):
     """Bytes the method must move per launch (each HBM word once), by kernel family.  A
     "cg_iter" launch is one PCG iteration: one kernel with Jacobi, four with the nodal
-    auxiliary-space preconditioner (in FP32 for the inner solves of the mixed form)."""
+    auxiliary-space preconditioner (in FP32 for the inner solves of the mixed form).  Columns
+    count 4 bytes each, as in the matrix's own format; the row blocks' 16-bit ones move 2."""
     n_rows, nnz, ne, nf, nt = geo["n_rows"], geo["nnz"], geo["n_edges"], geo["n_faces"], geo["n_tets"]
     fold = 1 if geo.get("far_levels", 0) > 0 else 0   # the far levels' per-node fold runs
     npart, occ, cross = st["particles"], st["occupied_tets"], st["crossings"]
@@ -507,13 +510,22 @@ def run_workload(args, F, torch, name, steps, warmup, with_cpu, with_fp64_solve)
     traffic = traffic_from_profile(dominant, name, pc, solve)
     if traffic is not None:
         traffic = int(traffic * work_share)   # counters are per working launch (median)
+    # a one-launch solve keeps the matrix in registers: the bytes are the method's per
+    # iteration, not HBM's, and what bounds it is the exchange between workgroups
+    one_launch = pc == "aux" and geo["n_edges"] <= ONE_LAUNCH_ROWS
+    if one_launch and dominant == "cg_iter":
+        traffic = None
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
-                "kernel": (JACOBI_ITER_KERNEL if pc == "jacobi" else MIXED_ITER_KERNEL if solve == "mixed"
+                "kernel": (JACOBI_ITER_KERNEL if pc == "jacobi" else ONE_LAUNCH_KERNEL if one_launch
+                           else MIXED_ITER_KERNEL if solve == "mixed"
                            else KERNEL_NAMES[dominant]) if dominant == "cg_iter" else KERNEL_NAMES[dominant],
                 "avg_launch_us": round(avg_s * 1e6, 3), "launches": nl,
                 "working_launch_share": round(work_share, 4),
                 "algorithmic_bytes_per_launch": int(per_launch * work_share)}
+    if one_launch and dominant == "cg_iter":
+        roofline["note"] = ("one launch per solve, the matrix in registers: achieved counts the bytes that a "
+                            "streaming iteration would move; three exchanges between workgroups set the pace")
 
     # the particle kernels' own roofline: one launch = one species' k_push (+ k_cross)
     pms, pn = fam_time["push"]

@@ -152,7 +152,8 @@ typedef struct {
                           FEPIC_ALL_FP64: everything FP64                               */
     double cg_tol;     /* stop when ||b - A x||_2 <= cg_tol ||b||_2 (default 1e-10)      */
     int cg_max_iters;  /* default 10000                                                  */
-    int cg_check_every;/* iterations between convergence reads on the host (default 8)   */
+    int cg_check_every;/* iterations between convergence reads on the host (default 8),
+                          where a solve is not one launch                                */
     int sort_period;   /* re-bin particles by tet every this many steps (default 1; 0:
                           never); FEPIC_SORT_AUTO: each species when its particles that
                           left their tet or the mesh since its last re-binning reach 1/64
@@ -399,9 +400,10 @@ int fepic_diagnostics(fepic_ctx* ctx, fepic_step_stats* out);
  * "cg_iter", "faraday", "mlp_fwd") with HIP events on the context's stream while
  * enabled: one pair per launch, except "cg_iter", whose pair spans each batch of
  * back-to-back iteration launches (so its per-launch average includes the dispatch gap
- * between iterations, and events do not separate them) and whose launch count is the
- * number of PCG iterations launched (one kernel each with Jacobi, three with the
- * auxiliary-space preconditioner).  fepic_kernel_time returns the summed duration and
+ * between iterations, and events do not separate them), or the one launch of a whole solve
+ * on meshes small enough for it, and whose launch count is the number of PCG iterations
+ * launched or made (one kernel each with Jacobi, three with the auxiliary-space
+ * preconditioner).  fepic_kernel_time returns the summed duration and
  * the launch count since enabling (synchronizes the stream). */
 int fepic_kernel_timing(fepic_ctx* ctx, const char* family, int enable);
 int fepic_kernel_time(fepic_ctx* ctx, const char* family, double* total_ms, int64_t* launches);

@@ -433,6 +433,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_init_b(int64_t n_rows, RowGrid rg
 //                    scales (once per node, not at both ends of every edge)
 //   k_pcg_update(i): p again (same operands, same bits);  x += alpha p;  r = r';
 //                    z = D^-1 r + G y + Pi v (all levels);  dots (r, z), (r, r)
+// (Meshes of up to 262k rows do all of this in one launch per solve, k_pcg_solve.)
 // Every kernel issues its loads before it sums the previous kernel's slots.  Reductions
 // use the iteration slots in four rotating buffers: reduction k goes to buffer k mod 4;
 // iteration i adds (p, q) as reduction 2i and (r, z), (r, r) as reduction 2i + 1; the
@@ -881,8 +882,9 @@ __global__ __launch_bounds__(kBlock) void k_pack_f32(int64_t n_slices, const int
     if (k < w) A32[k0 + 64 * k + lane] = (float)A[k0 + 64 * k + lane];
 }
 
-// One Jacobi-PCG iteration per row block (in the deterministic mode a workgroup takes every
-// rg.g-th block, so that each dot slot takes a single add).  The neighbours'
+// One Jacobi-PCG iteration, for meshes past k_cg_solve's limits (more row blocks than CUs, or
+// a halo too long for its registers), per row block (in the deterministic mode a workgroup
+// takes every rg.g-th block, so that each dot slot takes a single add).  The neighbours'
 // u' = R - alpha (W + beta S) are staged in LDS like the auxiliary-space product's p, one
 // value per column instead of three gathered values per stored slot; a row's diagonal is its
 // slot 0.  Bound by HBM on large meshes (998k tets: 92.8 -> 55.4 us), by the chain of
