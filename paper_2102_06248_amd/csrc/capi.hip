@@ -28,16 +28,21 @@ int fail(fepic_ctx* c, int code, const std::string& msg) {
     return code;
 }
 
+// Null if there is no memory.  The runtime keeps an allocation's error until it is asked for
+// it, so it is taken here: a caller that does without the memory would otherwise meet it at
+// its next hipGetLastError.
 void* dmalloc(fepic_ctx* c, size_t bytes) {
     if (bytes == 0) bytes = 8;
     void* p = nullptr;
     if (c->ualloc) {
         p = c->ualloc(bytes, c->uarg);
-        if (!p) return nullptr;
     } else if (hipMalloc(&p, bytes) != hipSuccess) {
-        return nullptr;
+        p = nullptr;
     }
-    c->allocs.push_back(p);
+    if (p)
+        c->allocs.push_back(p);
+    else
+        (void)hipGetLastError();
     return p;
 }
 
@@ -572,7 +577,10 @@ int fit_species(fepic_ctx* c, int n) {
         SpeciesStat* p = nullptr;
         const int cap = 2 * n;
         HIPCHK(c, hipStreamSynchronize(c->stream));
-        if (hipHostMalloc((void**)&p, sizeof(SpeciesStat) * cap) != hipSuccess) return fail(c, FEPIC_E_OOM, "allocation failed");
+        if (hipHostMalloc((void**)&p, sizeof(SpeciesStat) * cap) != hipSuccess) {
+            (void)hipGetLastError();
+            return fail(c, FEPIC_E_OOM, "allocation failed");
+        }
         std::memset(p, 0, sizeof(SpeciesStat) * cap);
         std::memcpy(p, c->h_stats, sizeof(SpeciesStat) * c->stat_species);
         if (c->stats_own) (void)hipHostFree(c->h_stats);
