@@ -242,6 +242,18 @@ int fepic_set_preconditioner(fepic_ctx* ctx, int pc);
 /* Selects the arithmetic of later Newmark solves (FEPIC_SOLVE_*; FEPIC_E_ARG for any other
  * value, and for FEPIC_SOLVE_MIXED with the Jacobi preconditioner). */
 int fepic_set_solve_precision(fepic_ctx* ctx, int solve_precision);
+/* A solve on a mesh small enough for it is one launch, whose workgroups wait for each other's
+ * values.  Every wait is bounded, by `polls` rounds of looking for them (default
+ * FEPIC_SOLVE_POLLS, about a tenth of a second; a round trip takes a few): where other work
+ * on the GPU keeps some workgroups from starting for that long, the solve is given up and
+ * made by a launch per iteration and kernel, as on larger meshes.  0 gives up at the first
+ * wait; -1 makes no one-launch solves (FEPIC_E_ARG below that). */
+#define FEPIC_SOLVE_POLLS (1 << 17)
+int fepic_set_solve_polls(fepic_ctx* ctx, int polls);
+/* How the last solve (with FEPIC_SOLVE_MIXED: its last pass) was made, FEPIC_SOLVE_FORM_*,
+ * and the one-launch solves given up so far; either may be NULL. */
+enum { FEPIC_SOLVE_FORM_NONE = -1, FEPIC_SOLVE_FORM_KERNELS = 0, FEPIC_SOLVE_FORM_ONE_LAUNCH = 1 };
+int fepic_get_solve_form(fepic_ctx* ctx, int* form, int64_t* n_given_up);
 /* Selects the field update of later steps (FEPIC_FIELD_*; FEPIC_E_ARG otherwise). */
 int fepic_set_field_solver(fepic_ctx* ctx, int solver);
 /* Selects the pusher (FEPIC_PUSHER_*) and Adams-Bashforth order (1..5) of later steps;

@@ -999,7 +999,7 @@ template <typename F>
 int solve_one_launch(fepic_ctx* c, int64_t n, int n_max, bool* again, bool* solved, F&& launch) {
     *solved = false;
     c->h_sc->converged = 0;
-    if (n_max <= 0) return FEPIC_OK;
+    if (n_max <= 0 || c->solve_polls < 0) return FEPIC_OK;
     bool fresh = (uint64_t)c->box_tag + (uint64_t)n_max > 0xffffffffull;
     if (c->n_boxes < n) {
         dfree(c, c->d_boxes);
@@ -1026,9 +1026,11 @@ int solve_one_launch(fepic_ctx* c, int64_t n, int n_max, bool* again, bool* solv
     *solved = c->h_sc->converged != 3;
     if (!*solved) {
         *again = false;
+        c->solves_given_up++;
         c->box_tag += (uint32_t)n_max;
         return FEPIC_OK;
     }
+    c->solve_form = FEPIC_SOLVE_FORM_ONE_LAUNCH;
     c->box_tag += (uint32_t)c->h_sc->iters + 1;   // a breakdown leaves words of the iteration it stopped in
     if (ev) c->timers[FAM_CG_ITER].launches += c->h_sc->iters + 1;   // counted as the iterations it stands for
     return FEPIC_OK;
@@ -1124,6 +1126,7 @@ int field_phase(fepic_ctx* c, double dt, double beta, double gamma) {
     // launches after convergence return at once, which costs less than another round trip
     // to the host.  iter(i) launches iteration i.
     auto iterate = [&](int first, auto&& iter) -> int {
+        c->solve_form = FEPIC_SOLVE_FORM_KERNELS;
         int launched = 0, last_done = -1;
         double last_rr = 0.0;
         const int budget = maxit - total;
@@ -1199,7 +1202,8 @@ int field_phase(fepic_ctx* c, double dt, double beta, double gamma) {
                     [&](unsigned long long* boxes, uint32_t tag) {
                         return launch_pcg_solve<float, float2>(c->stream, blocks, ne, n_max, c->d_sp, c->bc, c->d_A32,
                                                                c->d_dinv32, c->d_x32, ZP32[0], c->d_rq32, c->aux,
-                                                               c->solve_lists, boxes, tag, c->d_partial, c->d_sc);
+                                                               c->solve_lists, boxes, tag, c->solve_polls, c->d_partial,
+                                                               c->d_sc);
                     });
                 if (rc != FEPIC_OK) return rc;
                 if (!again) c->one_launch_pcg[1] = 0;
@@ -1250,14 +1254,15 @@ int field_phase(fepic_ctx* c, double dt, double beta, double gamma) {
                         const double* R = reinterpret_cast<const double*>(c->d_rq);
                         return launch_pcg_solve<double, double2>(c->stream, blocks, ne, n_max, c->d_sp, c->bc, c->d_A,
                                                                  c->d_dinv, c->d_x, ZP[0], R, c->aux, c->solve_lists,
-                                                                 boxes, tag, c->d_partial, c->d_sc);
+                                                                 boxes, tag, c->solve_polls, c->d_partial, c->d_sc);
                     });
                 if (!again) c->one_launch_pcg[0] = 0;
             } else if (!aux && c->one_launch) {
                 rs = solve_one_launch(c, cg_solve_boxes(c->bc), n_max, &c->one_launch, &solved,
                                       [&](unsigned long long* boxes, uint32_t tag) {
                                           return launch_cg_solve(c->stream, ne, n_max, c->d_sp, c->bc, c->d_A, c->d_x,
-                                                                 V[0], boxes, tag, c->d_partial, c->d_sc);
+                                                                 V[0], boxes, tag, c->solve_polls, c->d_partial,
+                                                                 c->d_sc);
                                       });
             }
             if (rs != FEPIC_OK) return rs;
@@ -1850,6 +1855,20 @@ int fepic_set_solve_precision(fepic_ctx* c, int sp) {
         for (int& n : c->last_pass_iters) n = 0;
     }
     c->opt.solve_precision = sp;
+    return FEPIC_OK;
+}
+
+int fepic_set_solve_polls(fepic_ctx* c, int polls) {
+    if (!c) return FEPIC_E_ARG;
+    if (polls < -1) return fail(c, FEPIC_E_ARG, "polls must be -1 or more");
+    c->solve_polls = polls;
+    return FEPIC_OK;
+}
+
+int fepic_get_solve_form(fepic_ctx* c, int* form, int64_t* n_given_up) {
+    if (!c) return FEPIC_E_ARG;
+    if (form) *form = c->solve_form;
+    if (n_given_up) *n_given_up = c->solves_given_up;
     return FEPIC_OK;
 }
 

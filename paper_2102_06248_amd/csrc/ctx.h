@@ -124,6 +124,9 @@ struct fepic_ctx {
     fepic::SolveLists solve_lists;
     bool solve_lists_tried = false;
     int one_launch_pcg[2] = {0, 0};                // FP64, FP32: row blocks per workgroup (0: not in one launch)
+    int solve_polls = FEPIC_SOLVE_POLLS;           // of one wait inside a one-launch solve; below zero: none is made
+    int solve_form = FEPIC_SOLVE_FORM_NONE;        // of the last solve
+    int64_t solves_given_up = 0;
     fepic::CgVec* d_cgv[2] = {nullptr, nullptr};   // Jacobi-PCG state, double buffered
     // auxiliary-space PCG: (z, p) pairs double buffered, r and q (n_edges each), nodal arrays
     double2* d_zp[2] = {nullptr, nullptr};

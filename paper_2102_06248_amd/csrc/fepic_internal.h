@@ -371,15 +371,15 @@ template <typename S, typename S2>
 hipError_t launch_pcg_solve(hipStream_t s, int blocks, int64_t n_rows, int n_max, const int64_t* sp,
                             const BlockCols& bc, const S* A, const S* dinv, S* x, const S2* zp0, const S* r,
                             const AuxSpace& g, const SolveLists& l, unsigned long long* boxes, unsigned tag0,
-                            double* partial, CgScalars* sc);
+                            int polls, double* partial, CgScalars* sc);
 // A whole Jacobi solve in one launch: whether every row block has a resident workgroup, the
 // 64-bit words that the workgroups exchange values through, and the launch (from launch_cg_init's
-// state; tags tag0 + 1 .. tag0 + n_max must not be in the words yet).
+// state; tags tag0 + 1 .. tag0 + n_max must not be in the words yet; polls bounds each wait).
 bool cg_solve_fits(const BlockCols& bc, int n_cu);
 int64_t cg_solve_boxes(const BlockCols& bc);
 hipError_t launch_cg_solve(hipStream_t s, int64_t n_rows, int n_max, const int64_t* sp, const BlockCols& bc,
                            const double* A, double* x, const CgVec* V, unsigned long long* boxes, unsigned tag0,
-                           double* partial, CgScalars* sc);
+                           int polls, double* partial, CgScalars* sc);
 void launch_cg_rr0(hipStream_t s, int64_t n_rows, double* partial, CgScalars* sc);
 // Halo sizes of the row blocks into cnt (count), then halo lists and 16-bit columns (fill).
 void launch_block_count(hipStream_t s, const BlockCols& g, const int64_t* slice_ptr, const int32_t* col, int32_t* cnt);

@@ -1012,8 +1012,6 @@ struct Mail {
     }
 };
 
-// Polls of one wait before the solve gives up (a tenth of a second; a wait takes a few).
-constexpr int kSolvePolls = 1 << 17;
 // Copies of the workgroups' partials: every workgroup reads all of one, its XCD's.
 constexpr int kSolveCopies = 8;
 
@@ -1075,24 +1073,21 @@ struct Inbox {
 // cycles first (half a microsecond, nearly what a store and a load past the L2s take), 90k
 // rows took 3.5 us per Jacobi iteration and 7.9 per FP64 PCG one; without 4.1 and 11.1, with
 // 32 x 64 3.7 and 8.5.  Up to 64 workgroups poll so little that 8 are enough (13k rows 2.98
-// us, with 16 3.09).  Gives up after kSolvePolls rounds (*fail).
+// us, with 16 3.09).  Gives up after `polls` rounds (*fail; at once if there are none).
 template <typename A, typename B>
-__device__ __forceinline__ void wait_boxes(const Mail& m, A& a, B& b, unsigned tag, int n_wg, int* fail) {
+__device__ __forceinline__ void wait_boxes(const Mail& m, A& a, B& b, unsigned tag, int n_wg, int polls, int* fail) {
     if (n_wg > 64)
         __builtin_amdgcn_s_sleep(17);
     else
         __builtin_amdgcn_s_sleep(8);
-    for (int n = 0;; ++n) {
+    for (int n = 0; n < polls; ++n) {
         asm volatile("" ::: "memory");   // the words are read anew in every round
         a.load(m);
         b.load(m);
         const bool ok = a.check(tag) & b.check(tag);
-        if (__all(ok)) break;
-        if (n >= kSolvePolls) {
-            if ((threadIdx.x & 63) == 0) *fail = 1;
-            break;
-        }
+        if (__all(ok)) return;
     }
+    if ((threadIdx.x & 63) == 0) *fail = 1;
 }
 
 // A whole Jacobi-PCG solve in one launch, for matrices of which every row block has a
@@ -1108,14 +1103,14 @@ __device__ __forceinline__ void wait_boxes(const Mail& m, A& a, B& b, unsigned t
 // of the product (0.75 us); what grows with the mesh is the polling, so the partials lie in a
 // copy per XCD.  Per iteration against a launch of k_cg_iter: 1.1k rows 5.2 -> 2.7 us, 13k 6.5
 // -> 3.0, 90k 7.0 -> 3.5 (registers capped for two workgroups per CU: 0.8 us more, by spills).
-// Every wait is bounded: a workgroup that polls kSolvePolls times in vain sets converged to
+// Every wait is bounded: a workgroup that polls `polls` times in vain sets converged to
 // 3 and leaves with x as it found it, the others follow in the same way, and the host solves
 // by k_cg_iter.
 // n_max: the iterate at which the solve stops unconverged.
 __global__ __launch_bounds__(kBlockRows) __attribute__((amdgpu_waves_per_eu(2))) void k_cg_solve(
     int64_t n_rows, RowGrid rg, int n_max, const int64_t* __restrict__ sp, BlockCols bc, const double* __restrict__ A,
     double* __restrict__ x, const CgVec* __restrict__ V, unsigned long long* boxes, unsigned box_bytes, unsigned tag0,
-    const double* __restrict__ cg_slots, CgScalars* sc) {
+    int polls, const double* __restrict__ cg_slots, CgScalars* sc) {
     extern __shared__ double s_u[];
     constexpr int R = kBlockRows, H = kHaloRegs, NW = R / 64;
     __shared__ double s_dot[3][NW], s_own[3][NW];
@@ -1206,7 +1201,7 @@ __global__ __launch_bounds__(kBlockRows) __attribute__((amdgpu_waves_per_eu(2)))
         for (int j = 0; j < 3; ++j) pin.expect(j, p_box(buf, blockIdx.x % kSolveCopies, min(tid, nb - 1)) + 16 * j, tid < nb);
 #pragma unroll
         for (int k = 0; k < H; ++k) win.expect(k, w_box(buf, k * R < bc.stride ? h[k] : 0), k * R + tid < cnt);
-        wait_boxes(mail, pin, win, tag, nb, &s_fail);
+        wait_boxes(mail, pin, win, tag, nb, polls, &s_fail);
 #pragma unroll
         for (int j = 0; j < 3; ++j) v[j] = pin.value(j);
 #pragma unroll
@@ -1301,8 +1296,7 @@ __global__ __launch_bounds__(kBlockRows) __attribute__((amdgpu_waves_per_eu(2)))
     int64_t n_rows, RowGrid rg, int n_max, const int64_t* __restrict__ sp, BlockCols bc, const S* __restrict__ A,
     const S* __restrict__ dinv, S* __restrict__ x, const typename Vec<S>::t2* __restrict__ ZP, const S* __restrict__ R0,
     AuxSpace g, SolveLists L, unsigned long long* boxes, unsigned box_bytes, unsigned shared_bytes, unsigned tag0,
-    const double* __restrict__ slots,
-    CgScalars* sc) {
+    int polls, const double* __restrict__ slots, CgScalars* sc) {
     using V4 = typename Vec<S>::t4;
     extern __shared__ __attribute__((aligned(32))) double lds_solve[];
     constexpr int R = kBlockRows, H = kHaloRegs, NW = R / 64, W = 2 * sizeof(S);
@@ -1525,7 +1519,7 @@ __global__ __launch_bounds__(kBlockRows) __attribute__((amdgpu_waves_per_eu(2)))
                 }
                 qin.expect(k, q_box + W * (unsigned)ek, need);
             }
-            wait_boxes(mail, pin, qin, tag, nw, &s_fail);
+            wait_boxes(mail, pin, qin, tag, nw, polls, &s_fail);
             v[0] = pin.value(0);
             if (!sum(v, 1)) break;
             const double alpha = gm / v[0];
@@ -1619,7 +1613,7 @@ __global__ __launch_bounds__(kBlockRows) __attribute__((amdgpu_waves_per_eu(2)))
                 const bool need = f_slice[b] < L.n_slices;
                 fin.expect(b, f_box + W * (4 * (unsigned)(need ? f_slice[b] : 0) + comp), need);
             }
-            wait_boxes(mail, yin, fin, tag, nw, &s_fail_y);
+            wait_boxes(mail, yin, fin, tag, nw, polls, &s_fail_y);
             if (far) {
 #pragma unroll
                 for (int b = 0; b < kB; ++b) {
@@ -1671,7 +1665,7 @@ __global__ __launch_bounds__(kBlockRows) __attribute__((amdgpu_waves_per_eu(2)))
             for (int k = 0; k < kB * H; ++k)
                 zin.expect(k, z_box + W * (unsigned)((k % H) * R < bc.stride ? h[k / H][k % H] : 0),
                            (k % H) * R + tid < cnt[k / H]);
-            wait_boxes(mail, pin, zin, tag, nw, &s_fail);
+            wait_boxes(mail, pin, zin, tag, nw, polls, &s_fail);
             v[0] = pin.value(0);
             v[1] = pin.value(1);
             if (!sum(v, 2)) break;
@@ -2425,12 +2419,12 @@ bool cg_solve_fits(const BlockCols& bc, int n_cu) {
 
 hipError_t launch_cg_solve(hipStream_t s, int64_t n_rows, int n_max, const int64_t* sp, const BlockCols& bc,
                            const double* A, double* x, const CgVec* V, unsigned long long* boxes, unsigned tag0,
-                           double* partial, CgScalars* sc) {
+                           int polls, double* partial, CgScalars* sc) {
     RowGrid rg = block_grid(bc);
     BlockCols g = bc;
     const double* slots = partial + SLOT_CG * kSlot;
     unsigned box_bytes = (unsigned)(8 * cg_solve_boxes(bc));
-    void* args[] = {&n_rows, &rg, &n_max, &sp, &g, &A, &x, &V, &boxes, &box_bytes, &tag0, &slots, &sc};
+    void* args[] = {&n_rows, &rg, &n_max, &sp, &g, &A, &x, &V, &boxes, &box_bytes, &tag0, &polls, &slots, &sc};
     const hipError_t e = hipLaunchCooperativeKernel((const void*)k_cg_solve, dim3(rg.grid), dim3(kBlockRows), args,
                                                     (unsigned)staged_bytes(bc, sizeof(double)), s);
     if (e != hipSuccess) (void)hipGetLastError();
@@ -2501,7 +2495,7 @@ template <typename S, typename S2>
 hipError_t launch_pcg_solve(hipStream_t s, int blocks, int64_t n_rows, int n_max, const int64_t* sp,
                             const BlockCols& bc, const S* A, const S* dinv, S* x, const S2* zp0, const S* r,
                             const AuxSpace& g, const SolveLists& l, unsigned long long* boxes, unsigned tag0,
-                            double* partial, CgScalars* sc) {
+                            int polls, double* partial, CgScalars* sc) {
     RowGrid rg = solve_grid(bc, blocks);
     BlockCols b = bc;
     AuxSpace a = g;
@@ -2510,7 +2504,7 @@ hipError_t launch_pcg_solve(hipStream_t s, int blocks, int64_t n_rows, int n_max
     unsigned box_bytes = (unsigned)(8 * pcg_solve_boxes<S>(bc, l, n_rows, g.n_aux, blocks));
     unsigned shared_bytes = (unsigned)solve_shared(bc, l, blocks, sizeof(S));
     void* args[] = {&n_rows, &rg, &n_max, &sp,    &b,         &A,            &dinv, &x,     &zp0,
-                    &r,      &a,  &ll,    &boxes, &box_bytes, &shared_bytes, &tag0, &slots, &sc};
+                    &r,      &a,  &ll,    &boxes, &box_bytes, &shared_bytes, &tag0, &polls, &slots, &sc};
     const hipError_t e = hipLaunchCooperativeKernel(pcg_solve_kernel<S>(blocks), dim3(rg.grid), dim3(kBlockRows), args,
                                                     (unsigned)solve_bytes(bc, l, blocks, sizeof(S)), s);
     if (e != hipSuccess) (void)hipGetLastError();
@@ -2524,10 +2518,10 @@ template int64_t pcg_solve_boxes<float>(const BlockCols&, const SolveLists&, int
 template hipError_t launch_pcg_solve<double, double2>(hipStream_t, int, int64_t, int, const int64_t*, const BlockCols&,
                                                       const double*, const double*, double*, const double2*,
                                                       const double*, const AuxSpace&, const SolveLists&,
-                                                      unsigned long long*, unsigned, double*, CgScalars*);
+                                                      unsigned long long*, unsigned, int, double*, CgScalars*);
 template hipError_t launch_pcg_solve<float, float2>(hipStream_t, int, int64_t, int, const int64_t*, const BlockCols&,
                                                     const float*, const float*, float*, const float2*, const float*,
-                                                    const AuxSpace&, const SolveLists&, unsigned long long*, unsigned,
+                                                    const AuxSpace&, const SolveLists&, unsigned long long*, unsigned, int,
                                                     double*, CgScalars*);
 
 // One workgroup per slice of 64 auxiliary nodes, consecutive slices on the same XCD.

@@ -23,6 +23,8 @@ FEPIC_PC_JACOBI, FEPIC_PC_AUX = 0, 1
 FEPIC_WALK_AUTO, FEPIC_WALK_QUEUE, FEPIC_WALK_FUSED = 0, 1, 2
 FEPIC_SORT_AUTO = -1
 FEPIC_SOLVE_FP64, FEPIC_SOLVE_MIXED = 0, 1
+FEPIC_SOLVE_POLLS = 1 << 17
+FEPIC_SOLVE_FORM_NONE, FEPIC_SOLVE_FORM_KERNELS, FEPIC_SOLVE_FORM_ONE_LAUNCH = -1, 0, 1
 FEPIC_PUSHER_BORIS, FEPIC_PUSHER_AB = 0, 1
 FEPIC_FIELD_WAVE, FEPIC_FIELD_NM_MFEM, FEPIC_FIELD_BD_MFEM = 0, 1, 2
 FEPIC_E_CG_NOT_CONVERGED = -6
@@ -128,6 +130,8 @@ _SIGS = {
     "fepic_set_warm_start": [_P, _INT],
     "fepic_set_preconditioner": [_P, _INT],
     "fepic_set_solve_precision": [_P, _INT],
+    "fepic_set_solve_polls": [_P, _INT],
+    "fepic_get_solve_form": [_P, ctypes.POINTER(_INT), _PI64],
     "fepic_set_pusher": [_P, _INT, _INT],
     "fepic_set_field_solver": [_P, _INT],
     "fepic_set_absorbing_faces": [_P, _I64, _P],
@@ -493,6 +497,17 @@ def fepic_set_preconditioner(ctx, pc):
 
 def fepic_set_solve_precision(ctx, solve_precision):
     _check(ctx, lib().fepic_set_solve_precision(ctx, int(solve_precision)))
+
+
+def fepic_set_solve_polls(ctx, polls):
+    _check(ctx, lib().fepic_set_solve_polls(ctx, int(polls)))
+
+
+def fepic_get_solve_form(ctx):
+    """(FEPIC_SOLVE_FORM_* of the last solve, one-launch solves given up so far)."""
+    form, n = ctypes.c_int(), ctypes.c_int64()
+    _check(ctx, lib().fepic_get_solve_form(ctx, ctypes.byref(form), ctypes.byref(n)))
+    return form.value, n.value
 
 
 def fepic_set_field_solver(ctx, solver):

@@ -1,0 +1,58 @@
+"""One-launch solves whose workgroups give up waiting for each other: with a bound of no polls
+every workgroup leaves at the first wait, and the solve is made by kernels.  All forms of the
+solve (one and two row blocks per workgroup, FP64 and FP32), held to the stopping rule
+recomputed in numpy.
+"""
+import pytest
+
+from gpu_common import announce, have_gpu, jittered_kuhn, require_lib
+from test_gpu_one_launch import TOL, check_step, operators, start
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def F():
+    if not have_gpu():
+        pytest.fail("GPU tests need an MI355X")
+    return require_lib()
+
+
+def options(F, solve):
+    return {"jacobi": dict(preconditioner=F.FEPIC_PC_JACOBI, cg_max_iters=20000),
+            "deterministic": dict(preconditioner=F.FEPIC_PC_JACOBI, cg_max_iters=20000, deterministic=1),
+            "fp64": dict(preconditioner=F.FEPIC_PC_AUX, cg_max_iters=5000),
+            "mixed": dict(preconditioner=F.FEPIC_PC_AUX, cg_max_iters=5000, solve_precision=F.FEPIC_SOLVE_MIXED)}[solve]
+
+
+# n = 27: 283 row blocks, two per workgroup with the auxiliary space (Jacobi: by kernels)
+@pytest.mark.parametrize("n,solve", [(2, "jacobi"), (7, "jacobi"), (7, "deterministic"), (7, "fp64"), (7, "mixed"),
+                                     (27, "fp64"), (27, "mixed")])
+def test_solve_given_up(F, n, solve):
+    announce(f"one-launch solve given up: n={n}, {solve}")
+    xyz, tets = jittered_kuhn(n, seed=1)[:2]
+    with F.Simulation(xyz, tets, device=0, cg_tol=TOL, **options(F, solve)) as L:
+        M, S, d, dt = operators(F, L)
+        start(F, L, d)
+        assert F.fepic_get_solve_form(L.ctx) == (F.FEPIC_SOLVE_FORM_NONE, 0)
+        assert check_step(F, L, M, S, dt) > 0
+        assert F.fepic_get_solve_form(L.ctx) == (F.FEPIC_SOLVE_FORM_ONE_LAUNCH, 0)
+        F.fepic_set_solve_polls(L.ctx, 0)
+        for _ in range(2):
+            assert check_step(F, L, M, S, dt) > 0
+            form, given_up = F.fepic_get_solve_form(L.ctx)
+            assert form == F.FEPIC_SOLVE_FORM_KERNELS and given_up > 0
+
+
+def test_one_launch_switched_off(F):
+    announce("one-launch solves switched off")
+    xyz, tets = jittered_kuhn(5, seed=1)[:2]
+    with F.Simulation(xyz, tets, device=0, cg_tol=TOL, **options(F, "jacobi")) as L:
+        M, S, d, dt = operators(F, L)
+        start(F, L, d)
+        with pytest.raises(F.FepicError):
+            F.fepic_set_solve_polls(L.ctx, -2)
+        for polls, form in ((-1, F.FEPIC_SOLVE_FORM_KERNELS), (F.FEPIC_SOLVE_POLLS, F.FEPIC_SOLVE_FORM_ONE_LAUNCH)):
+            F.fepic_set_solve_polls(L.ctx, polls)
+            assert check_step(F, L, M, S, dt) > 0
+            assert F.fepic_get_solve_form(L.ctx) == (form, 0)
