@@ -992,13 +992,13 @@ bool mlp_start_rejected(int mode, double rr0, double bb) {
 
 // A solve in one launch, by launch(boxes, tag) with n words to exchange values through:
 // *solved, with the scalars on the host.  Not solved, the iterations are launched one by one:
-// there is no memory for the words or the launch was refused, the solve's state as it was; or
-// the workgroups gave up waiting for each other (h_sc->converged is 3 then), x some iterate.
+// there is no memory for the words, the launch was refused, or some workgroup gave up waiting
+// (h_sc->gave_up: the device's scalars have to be set up again, the start is as it was).
 // *again: whether the context may try the next time (not after either of the last two).
 template <typename F>
 int solve_one_launch(fepic_ctx* c, int64_t n, int n_max, bool* again, bool* solved, F&& launch) {
     *solved = false;
-    c->h_sc->converged = 0;
+    c->h_sc->gave_up = 0;
     if (n_max <= 0 || c->solve_polls < 0) return FEPIC_OK;
     bool fresh = (uint64_t)c->box_tag + (uint64_t)n_max > 0xffffffffull;
     if (c->n_boxes < n) {
@@ -1023,7 +1023,7 @@ int solve_one_launch(fepic_ctx* c, int64_t n, int n_max, bool* again, bool* solv
     }
     HIPCHK(c, hipMemcpyAsync(c->h_sc, c->d_sc, sizeof(CgScalars), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    *solved = c->h_sc->converged != 3;
+    *solved = !c->h_sc->gave_up;
     if (!*solved) {
         *again = false;
         c->solves_given_up++;
@@ -1201,13 +1201,13 @@ int field_phase(fepic_ctx* c, double dt, double beta, double gamma) {
                     c, pcg_solve_boxes<float>(c->bc, c->solve_lists, ne, c->aux.n_aux, blocks), n_max, &again, &solved,
                     [&](unsigned long long* boxes, uint32_t tag) {
                         return launch_pcg_solve<float, float2>(c->stream, blocks, ne, n_max, c->d_sp, c->bc, c->d_A32,
-                                                               c->d_dinv32, c->d_x32, ZP32[0], c->d_rq32, c->aux,
-                                                               c->solve_lists, boxes, tag, c->solve_polls, c->d_partial,
-                                                               c->d_sc);
+                                                               c->d_dinv32, c->d_x32, c->d_x32, ZP32[0], c->d_rq32,
+                                                               c->aux, c->solve_lists, boxes, tag, c->solve_polls,
+                                                               c->d_partial, c->d_sc);
                     });
                 if (rc != FEPIC_OK) return rc;
                 if (!again) c->one_launch_pcg[1] = 0;
-                if (!solved && c->h_sc->converged == 3)
+                if (c->h_sc->gave_up)   // from zero again
                     launch_pcg_init_f32(c->stream, ne, c->d_sp, c->d_col, c->d_dinv32, c->d_rt, c->d_x32, c->aux,
                                         ZP32[0], c->d_rq32, c->d_partial, c->d_sc, tol_in);
             }
@@ -1245,6 +1245,7 @@ int field_phase(fepic_ctx* c, double dt, double beta, double gamma) {
             const int first = (restart == 0 && c->last_cg_iters > 0) ? std::max(batch, c->last_cg_iters + 2) : batch;
             bool solved = false;
             int rs = FEPIC_OK;
+            c->h_sc->gave_up = 0;
             const int n_max = maxit - total, blocks = c->aux.n_far <= 1 ? c->one_launch_pcg[0] : 0;
             if (aux && blocks) {
                 bool again = true;
@@ -1253,20 +1254,22 @@ int field_phase(fepic_ctx* c, double dt, double beta, double gamma) {
                     [&](unsigned long long* boxes, uint32_t tag) {
                         const double* R = reinterpret_cast<const double*>(c->d_rq);
                         return launch_pcg_solve<double, double2>(c->stream, blocks, ne, n_max, c->d_sp, c->bc, c->d_A,
-                                                                 c->d_dinv, c->d_x, ZP[0], R, c->aux, c->solve_lists,
-                                                                 boxes, tag, c->solve_polls, c->d_partial, c->d_sc);
+                                                                 c->d_dinv, c->d_x, c->d_rt, ZP[0], R, c->aux,
+                                                                 c->solve_lists, boxes, tag, c->solve_polls,
+                                                                 c->d_partial, c->d_sc);
                     });
                 if (!again) c->one_launch_pcg[0] = 0;
             } else if (!aux && c->one_launch) {
                 rs = solve_one_launch(c, cg_solve_boxes(c->bc), n_max, &c->one_launch, &solved,
                                       [&](unsigned long long* boxes, uint32_t tag) {
                                           return launch_cg_solve(c->stream, ne, n_max, c->d_sp, c->bc, c->d_A, c->d_x,
-                                                                 V[0], boxes, tag, c->solve_polls, c->d_partial,
+                                                                 c->d_rt, V[0], boxes, tag, c->solve_polls, c->d_partial,
                                                                  c->d_sc);
                                       });
             }
             if (rs != FEPIC_OK) return rs;
-            if (!solved && c->h_sc->converged == 3) cg_init();   // it gave up: x is a start like another
+            if (solved) std::swap(c->d_x, c->d_rt);
+            else if (c->h_sc->gave_up) cg_init();
             int rc = solved ? FEPIC_OK : iterate(first, [&](int i) {
                 if (aux)
                     launch_pcg_iter(c->stream, i, ne, c->d_sp, c->d_col, c->bc, c->d_A, c->d_dinv, c->d_x, c->aux, ZP,

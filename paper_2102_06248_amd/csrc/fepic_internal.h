@@ -129,6 +129,7 @@ struct CgScalars {
     double rr_true;   // ||b - A x||^2 at exit
     int converged;    // 1 = tolerance met, 2 = breakdown
     int iters;
+    int gave_up;      // some workgroup of a one-launch solve waited in vain: its outputs are void
 };
 
 // Per-row state of the PCG iteration, interleaved so that a neighbour's three gathered
@@ -362,24 +363,26 @@ void launch_cg_iter(hipStream_t s, int i, int64_t n_rows, const int64_t* slice_p
                     CgScalars* sc, bool det = false);
 // A whole solve with the auxiliary space in one launch: the row blocks per workgroup with
 // which all workgroups are resident (0: none), the exchange words, and the launch from the
-// state of launch_pcg_init (launch_pcg_init_f32), otherwise like launch_cg_solve.
+// state of launch_pcg_init (launch_pcg_init_f32), otherwise like launch_cg_solve (x_out may be
+// x where a solve given up starts from zero anyway).
 template <typename S>
 int pcg_solve_blocks(const BlockCols& bc, const SolveLists& l, int n_cu);
 template <typename S>
 int64_t pcg_solve_boxes(const BlockCols& bc, const SolveLists& l, int64_t n_rows, int64_t n_aux, int blocks);
 template <typename S, typename S2>
 hipError_t launch_pcg_solve(hipStream_t s, int blocks, int64_t n_rows, int n_max, const int64_t* sp,
-                            const BlockCols& bc, const S* A, const S* dinv, S* x, const S2* zp0, const S* r,
-                            const AuxSpace& g, const SolveLists& l, unsigned long long* boxes, unsigned tag0,
+                            const BlockCols& bc, const S* A, const S* dinv, const S* x, S* x_out, const S2* zp0,
+                            const S* r, const AuxSpace& g, const SolveLists& l, unsigned long long* boxes, unsigned tag0,
                             int polls, double* partial, CgScalars* sc);
 // A whole Jacobi solve in one launch: whether every row block has a resident workgroup, the
 // 64-bit words that the workgroups exchange values through, and the launch (from launch_cg_init's
-// state; tags tag0 + 1 .. tag0 + n_max must not be in the words yet; polls bounds each wait).
+// state; tags tag0 + 1 .. tag0 + n_max must not be in the words yet; polls bounds each wait; x
+// into x_out, which holds the solution unless CgScalars::gave_up is set).
 bool cg_solve_fits(const BlockCols& bc, int n_cu);
 int64_t cg_solve_boxes(const BlockCols& bc);
 hipError_t launch_cg_solve(hipStream_t s, int64_t n_rows, int n_max, const int64_t* sp, const BlockCols& bc,
-                           const double* A, double* x, const CgVec* V, unsigned long long* boxes, unsigned tag0,
-                           int polls, double* partial, CgScalars* sc);
+                           const double* A, const double* x, double* x_out, const CgVec* V,
+                           unsigned long long* boxes, unsigned tag0, int polls, double* partial, CgScalars* sc);
 void launch_cg_rr0(hipStream_t s, int64_t n_rows, double* partial, CgScalars* sc);
 // Halo sizes of the row blocks into cnt (count), then halo lists and 16-bit columns (fill).
 void launch_block_count(hipStream_t s, const BlockCols& g, const int64_t* slice_ptr, const int32_t* col, int32_t* cnt);

@@ -374,6 +374,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_init_a(int64_t n_rows, RowGrid rg
             sc->bb = bb[0];
             sc->tol2_bb = tol * tol * bb[0];
             sc->converged = 0;
+            sc->gave_up = 0;
         }
         for (int k = threadIdx.x; k < 2 * 3 * kCgSlots; k += kBlock) cg_slots[k] = 0.0;
     }
@@ -1103,13 +1104,15 @@ __device__ __forceinline__ void wait_boxes(const Mail& m, A& a, B& b, unsigned t
 // of the product (0.75 us); what grows with the mesh is the polling, so the partials lie in a
 // copy per XCD.  Per iteration against a launch of k_cg_iter: 1.1k rows 5.2 -> 2.7 us, 13k 6.5
 // -> 3.0, 90k 7.0 -> 3.5 (registers capped for two workgroups per CU: 0.8 us more, by spills).
-// Every wait is bounded: a workgroup that polls `polls` times in vain sets converged to
-// 3 and leaves with x as it found it, the others follow in the same way, and the host solves
-// by k_cg_iter.
+// Every wait is bounded: a workgroup that polls `polls` times in vain sets gave_up and
+// leaves, those that wait for its next values follow in the same way, and the host solves by
+// k_cg_iter.  If it was the last exchange the others finish and report, which is why gave_up
+// is a field that only a workgroup giving up writes, and why the iterate goes into an array
+// of its own: x, V and the slots are left as they were.
 // n_max: the iterate at which the solve stops unconverged.
 __global__ __launch_bounds__(kBlockRows) __attribute__((amdgpu_waves_per_eu(2))) void k_cg_solve(
     int64_t n_rows, RowGrid rg, int n_max, const int64_t* __restrict__ sp, BlockCols bc, const double* __restrict__ A,
-    double* __restrict__ x, const CgVec* __restrict__ V, unsigned long long* boxes, unsigned box_bytes, unsigned tag0,
+    const double* __restrict__ x, double* __restrict__ x_out, const CgVec* __restrict__ V, unsigned long long* boxes, unsigned box_bytes, unsigned tag0,
     int polls, const double* __restrict__ cg_slots, CgScalars* sc) {
     extern __shared__ double s_u[];
     constexpr int R = kBlockRows, H = kHaloRegs, NW = R / 64;
@@ -1213,7 +1216,7 @@ __global__ __launch_bounds__(kBlockRows) __attribute__((amdgpu_waves_per_eu(2)))
         }
         __syncthreads();
         if (s_fail) {
-            if (tid == 0) sc->converged = 3;
+            if (tid == 0) sc->gave_up = 1;
             return;
         }
         g = d = rr = 0.0;
@@ -1224,7 +1227,7 @@ __global__ __launch_bounds__(kBlockRows) __attribute__((amdgpu_waves_per_eu(2)))
             rr += s_dot[2][q];
         }
     }
-    if (row < n_rows) x[row] = xr;
+    if (row < n_rows) x_out[row] = xr;
     if (b == 0 && tid == 0) {
         sc->rr = rr;
         sc->rr0 = rr0;
@@ -1294,8 +1297,8 @@ __device__ __forceinline__ typename Vec<S>::t3 widen(const EdgeVec& t) {
 template <typename S, int kB>
 __global__ __launch_bounds__(kBlockRows) __attribute__((amdgpu_waves_per_eu(2))) void k_pcg_solve(
     int64_t n_rows, RowGrid rg, int n_max, const int64_t* __restrict__ sp, BlockCols bc, const S* __restrict__ A,
-    const S* __restrict__ dinv, S* __restrict__ x, const typename Vec<S>::t2* __restrict__ ZP, const S* __restrict__ R0,
-    AuxSpace g, SolveLists L, unsigned long long* boxes, unsigned box_bytes, unsigned shared_bytes, unsigned tag0,
+    const S* __restrict__ dinv, const S* x, S* x_out, const typename Vec<S>::t2* __restrict__ ZP,
+    const S* __restrict__ R0, AuxSpace g, SolveLists L, unsigned long long* boxes, unsigned box_bytes, unsigned shared_bytes, unsigned tag0,
     int polls, const double* __restrict__ slots, CgScalars* sc) {
     using V4 = typename Vec<S>::t4;
     extern __shared__ __attribute__((aligned(32))) double lds_solve[];
@@ -1676,12 +1679,12 @@ __global__ __launch_bounds__(kBlockRows) __attribute__((amdgpu_waves_per_eu(2)))
         }
     }
     if (s_fail || s_fail_y) {   // the same for the whole workgroup: a barrier follows every wait
-        if (tid == 0) sc->converged = 3;
+        if (tid == 0) sc->gave_up = 1;
         return;
     }
 #pragma unroll
     for (int b = 0; b < kB; ++b)
-        if (row[b] < n_rows) x[row[b]] = kLds ? s_x[b * R + tid] : x1;
+        if (row[b] < n_rows) x_out[row[b]] = kLds ? s_x[b * R + tid] : x1;
     if (wg == 0 && tid == 0) {
         sc->rr = rr;
         sc->rr0 = rr0;
@@ -1708,6 +1711,7 @@ __global__ __launch_bounds__(kBlock) void k_pcg_init(int64_t n_rows, RowGrid rg,
             sc->bb = bb[0];
             sc->tol2_bb = tol * tol * bb[0];
             sc->converged = 0;
+            sc->gave_up = 0;
         }
         for (int k = threadIdx.x; k < 4 * 3 * kCgSlots; k += kBlock) cg_slots[k] = 0.0;
         clear_far(g);
@@ -2418,13 +2422,13 @@ bool cg_solve_fits(const BlockCols& bc, int n_cu) {
 }
 
 hipError_t launch_cg_solve(hipStream_t s, int64_t n_rows, int n_max, const int64_t* sp, const BlockCols& bc,
-                           const double* A, double* x, const CgVec* V, unsigned long long* boxes, unsigned tag0,
-                           int polls, double* partial, CgScalars* sc) {
+                           const double* A, const double* x, double* x_out, const CgVec* V,
+                           unsigned long long* boxes, unsigned tag0, int polls, double* partial, CgScalars* sc) {
     RowGrid rg = block_grid(bc);
     BlockCols g = bc;
     const double* slots = partial + SLOT_CG * kSlot;
     unsigned box_bytes = (unsigned)(8 * cg_solve_boxes(bc));
-    void* args[] = {&n_rows, &rg, &n_max, &sp, &g, &A, &x, &V, &boxes, &box_bytes, &tag0, &polls, &slots, &sc};
+    void* args[] = {&n_rows, &rg, &n_max, &sp, &g, &A, &x, &x_out, &V, &boxes, &box_bytes, &tag0, &polls, &slots, &sc};
     const hipError_t e = hipLaunchCooperativeKernel((const void*)k_cg_solve, dim3(rg.grid), dim3(kBlockRows), args,
                                                     (unsigned)staged_bytes(bc, sizeof(double)), s);
     if (e != hipSuccess) (void)hipGetLastError();
@@ -2493,8 +2497,8 @@ int64_t pcg_solve_boxes(const BlockCols& bc, const SolveLists& l, int64_t n_rows
 
 template <typename S, typename S2>
 hipError_t launch_pcg_solve(hipStream_t s, int blocks, int64_t n_rows, int n_max, const int64_t* sp,
-                            const BlockCols& bc, const S* A, const S* dinv, S* x, const S2* zp0, const S* r,
-                            const AuxSpace& g, const SolveLists& l, unsigned long long* boxes, unsigned tag0,
+                            const BlockCols& bc, const S* A, const S* dinv, const S* x, S* x_out, const S2* zp0,
+                            const S* r, const AuxSpace& g, const SolveLists& l, unsigned long long* boxes, unsigned tag0,
                             int polls, double* partial, CgScalars* sc) {
     RowGrid rg = solve_grid(bc, blocks);
     BlockCols b = bc;
@@ -2503,7 +2507,7 @@ hipError_t launch_pcg_solve(hipStream_t s, int blocks, int64_t n_rows, int n_max
     const double* slots = partial + SLOT_CG * kSlot + (size_t)3 * 3 * kCgSlots;   // reduction -1: buffer 3 of 4
     unsigned box_bytes = (unsigned)(8 * pcg_solve_boxes<S>(bc, l, n_rows, g.n_aux, blocks));
     unsigned shared_bytes = (unsigned)solve_shared(bc, l, blocks, sizeof(S));
-    void* args[] = {&n_rows, &rg, &n_max, &sp,    &b,         &A,            &dinv, &x,     &zp0,
+    void* args[] = {&n_rows, &rg, &n_max, &sp,    &b,         &A,            &dinv, &x,     &x_out, &zp0,
                     &r,      &a,  &ll,    &boxes, &box_bytes, &shared_bytes, &tag0, &polls, &slots, &sc};
     const hipError_t e = hipLaunchCooperativeKernel(pcg_solve_kernel<S>(blocks), dim3(rg.grid), dim3(kBlockRows), args,
                                                     (unsigned)solve_bytes(bc, l, blocks, sizeof(S)), s);
@@ -2516,12 +2520,12 @@ template int pcg_solve_blocks<float>(const BlockCols&, const SolveLists&, int);
 template int64_t pcg_solve_boxes<double>(const BlockCols&, const SolveLists&, int64_t, int64_t, int);
 template int64_t pcg_solve_boxes<float>(const BlockCols&, const SolveLists&, int64_t, int64_t, int);
 template hipError_t launch_pcg_solve<double, double2>(hipStream_t, int, int64_t, int, const int64_t*, const BlockCols&,
-                                                      const double*, const double*, double*, const double2*,
-                                                      const double*, const AuxSpace&, const SolveLists&,
+                                                      const double*, const double*, const double*, double*,
+                                                      const double2*, const double*, const AuxSpace&, const SolveLists&,
                                                       unsigned long long*, unsigned, int, double*, CgScalars*);
 template hipError_t launch_pcg_solve<float, float2>(hipStream_t, int, int64_t, int, const int64_t*, const BlockCols&,
-                                                    const float*, const float*, float*, const float2*, const float*,
-                                                    const AuxSpace&, const SolveLists&, unsigned long long*, unsigned, int,
+                                                    const float*, const float*, const float*, float*, const float2*,
+                                                    const float*, const AuxSpace&, const SolveLists&, unsigned long long*, unsigned, int,
                                                     double*, CgScalars*);
 
 // One workgroup per slice of 64 auxiliary nodes, consecutive slices on the same XCD.
