@@ -180,7 +180,8 @@ typedef struct {
                               as 128-bit fixed-point integers (order-independent; each term
                               truncated to 2^-64 of the power of two above the largest
                               |q w|), the particle step always walks in place, and the PCG
-                              dots use one workgroup per partial slot.  Needs
+                              sums its dots in an order that the mesh and the device alone
+                              decide, also where a one-launch solve was given up.  Needs
                               FEPIC_PC_JACOBI, FEPIC_SOLVE_FP64 and a warm start other than
                               the learned ones (FEPIC_E_ARG at create; the setters refuse to
                               leave them with FEPIC_E_STATE).  The state after a step

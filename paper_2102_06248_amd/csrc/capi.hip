@@ -1259,8 +1259,8 @@ int field_phase(fepic_ctx* c, double dt, double beta, double gamma) {
                                                                  c->d_partial, c->d_sc);
                     });
                 if (!again) c->one_launch_pcg[0] = 0;
-            } else if (!aux && c->one_launch) {
-                rs = solve_one_launch(c, cg_solve_boxes(c->bc), n_max, &c->one_launch, &solved,
+            } else if (!aux && c->one_launch && c->try_one_launch) {
+                rs = solve_one_launch(c, cg_solve_boxes(c->bc), n_max, &c->try_one_launch, &solved,
                                       [&](unsigned long long* boxes, uint32_t tag) {
                                           return launch_cg_solve(c->stream, ne, n_max, c->d_sp, c->bc, c->d_A, c->d_x,
                                                                  c->d_rt, V[0], boxes, tag, c->solve_polls, c->d_partial,
@@ -1275,8 +1275,8 @@ int field_phase(fepic_ctx* c, double dt, double beta, double gamma) {
                     launch_pcg_iter(c->stream, i, ne, c->d_sp, c->d_col, c->bc, c->d_A, c->d_dinv, c->d_x, c->aux, ZP,
                                     c->d_rq, c->d_partial, c->d_sc);
                 else
-                    launch_cg_iter(c->stream, i, ne, c->d_sp, c->d_col, c->bc, c->d_A, c->d_x, V, c->d_partial, c->d_sc,
-                                   c->opt.deterministic != 0);
+                    launch_cg_iter(c->stream, i, ne, n_max, c->d_sp, c->d_col, c->bc, c->d_A, c->d_x, V, c->d_partial,
+                                   c->d_sc, c->opt.deterministic != 0, c->one_launch);
             });
             if (rc != FEPIC_OK) return rc;
             if (restart == 0) rr0_first = c->h_sc->rr0;

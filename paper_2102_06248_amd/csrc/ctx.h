@@ -121,6 +121,7 @@ struct fepic_ctx {
     int64_t n_boxes = 0;
     uint32_t box_tag = 0;                          // last tag in use there
     bool one_launch = false;                       // Jacobi: the row blocks are all resident at once
+    bool try_one_launch = true;                    // not yet given up
     fepic::SolveLists solve_lists;
     bool solve_lists_tried = false;
     int one_launch_pcg[2] = {0, 0};                // FP64, FP32: row blocks per workgroup (0: not in one launch)

@@ -358,9 +358,10 @@ void launch_cg_init(hipStream_t s, int64_t n_rows, const int64_t* slice_ptr, con
                     double tol, bool det = false);
 // det: at most one workgroup per dot slot, so every slot takes a single add and the dots
 // do not depend on the order of the workgroups (deterministic mode).
-void launch_cg_iter(hipStream_t s, int i, int64_t n_rows, const int64_t* slice_ptr, const int32_t* col,
+// twin (a mesh that cg_solve_fits): that solve's arithmetic to the bit, stopping at n_max.
+void launch_cg_iter(hipStream_t s, int i, int64_t n_rows, int n_max, const int64_t* slice_ptr, const int32_t* col,
                     const BlockCols& bc, const double* A, double* x, CgVec* const v[2], double* partial,
-                    CgScalars* sc, bool det = false);
+                    CgScalars* sc, bool det, bool twin);
 // A whole solve with the auxiliary space in one launch: the row blocks per workgroup with
 // which all workgroups are resident (0: none), the exchange words, and the launch from the
 // state of launch_pcg_init (launch_pcg_init_f32), otherwise like launch_cg_solve (x_out may be

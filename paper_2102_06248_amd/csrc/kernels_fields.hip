@@ -646,6 +646,7 @@ __device__ __forceinline__ typename Vec<S>::t3 edge_vec_t(const AuxSpace& g, int
 // same bits in every lane: VALU moves, where shuffles would be LDS permutes.
 template <int kCtrl, int kRowMask>
 __device__ __forceinline__ double dpp_add(double v) {
+#pragma clang fp contract(off)
     const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), kCtrl, kRowMask, 0xf, true);
     const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), kCtrl, kRowMask, 0xf, true);
     return v + __hiloint2double(hi, lo);
@@ -742,15 +743,15 @@ struct BlockRow {
 #pragma unroll
         for (int j = 0; j < kPairs; ++j)
             if (2 * j < w) {
-                s0 += a[2 * j] * f(c[j] & 0xffffu);
-                s1 += a[2 * j + 1] * f(c[j] >> 16);
+                s0 = fma(a[2 * j], f(c[j] & 0xffffu), s0);
+                s1 = fma(a[2 * j + 1], f(c[j] >> 16), s1);
             }
         for (int j = kPairs; 2 * j < w; ++j) {
             S a0, a1;
             uint32_t cc;
             pair(bc, A, j, a0, a1, cc);
-            s0 += a0 * f(cc & 0xffffu);
-            s1 += a1 * f(cc >> 16);
+            s0 = fma(a0, f(cc & 0xffffu), s0);
+            s1 = fma(a1, f(cc >> 16), s1);
         }
         return s0 + s1;
     }
@@ -883,30 +884,85 @@ __global__ __launch_bounds__(kBlock) void k_pack_f32(int64_t n_slices, const int
     if (k < w) A32[k0 + 64 * k + lane] = (float)A[k0 + 64 * k + lane];
 }
 
-// One Jacobi-PCG iteration, for meshes past k_cg_solve's limits (more row blocks than CUs, or
-// a halo too long for its registers), per row block (in the deterministic mode a workgroup
-// takes every rg.g-th block, so that each dot slot takes a single add).  The neighbours'
+// What the Jacobi-PCG kernels compute alike.  Products and sums are kept apart, and the
+// multiply-adds of the recurrences written out, because which of them a compiler fuses is its
+// choice in each kernel, and k_cg_iter<true> has to give k_cg_solve's bits.
+struct CgStep {
+    double alpha, beta;
+    int conv;   // 1: done, 2: breakdown
+};
+__device__ __forceinline__ CgStep cg_step(int i, double g, double d, double rr, double gam_old, double alpha_old,
+                                          double tol2_bb, double bb) {
+#pragma clang fp contract(off)
+    const bool done = !(rr > tol2_bb) || bb == 0.0;
+    const double beta = (i == 0) ? 0.0 : g / gam_old;
+    const double alpha = (i == 0) ? g / d : g / (d - beta * g / alpha_old);
+    const bool bad = !done && !(alpha > 0.0 && alpha < INFINITY && beta >= 0.0 && beta < INFINITY);
+    return {alpha, beta, done ? 1 : (bad ? 2 : 0)};
+}
+// (r, u), (u, w) and (r, r) of a row, D^-1 r = u.
+__device__ __forceinline__ void cg_dots(double u, double acc, double diag, double v[3]) {
+#pragma clang fp contract(off)
+    const double rn = u * diag;
+    v[0] = rn * u;
+    v[1] = u * acc;
+    v[2] = rn * rn;
+}
+// The waves' sums of v, and their sum.
+template <int NV, int NW>
+__device__ __forceinline__ void sum_waves(const double v[NV], double (*s)[NW]) {
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+        const double a = wave_total(v[j]);
+        if ((threadIdx.x & 63) == 0) s[j][threadIdx.x >> 6] = a;
+    }
+}
+template <int NW>
+__device__ __forceinline__ double over_waves(const double* s) {
+    double a = 0.0;
+#pragma unroll
+    for (int q = 0; q < NW; ++q) a += s[q];
+    return a;
+}
+
+// One Jacobi-PCG iteration per row block.  The neighbours'
 // u' = R - alpha (W + beta S) are staged in LDS like the auxiliary-space product's p, one
 // value per column instead of three gathered values per stored slot; a row's diagonal is its
 // slot 0.  Bound by HBM on large meshes (998k tets: 92.8 -> 55.4 us), by the chain of
 // dependent loads on small ones, where the six-at-a-time gathers took up to twelve round
 // trips: beam 19.7 -> 13.1 us, 29k tets 8.2 -> 6.9, 1.3k tets 7.6 -> 5.1; deterministic, 13k
 // tets, 10.6 -> 6.0.
-__global__ __launch_bounds__(kBlockRows) void k_cg_iter(int64_t n_rows, RowGrid rg, int i,
+// kTwin false: meshes past k_cg_solve's limits (more row blocks than CUs, or a halo too long
+// for its registers); the dots go into slots, and in the deterministic mode a workgroup takes
+// every rg.g-th block, so that each slot takes a single add.
+// kTwin true: meshes within them, where that solve was given up, refused or switched off.  Its
+// arithmetic to the bit, so that a deterministic step is the same whichever of the two made
+// it: the workgroups' partials one per thread, summed in its order (part: two buffers of
+// [3][kBlockRows]), and no update past n_max.
+template <bool kTwin>
+__global__ __launch_bounds__(kBlockRows) void k_cg_iter(int64_t n_rows, RowGrid rg, int i, int n_max,
                                                          const int64_t* __restrict__ sp,
                                                          const int32_t* __restrict__ col, BlockCols bc,
                                                          const double* __restrict__ A, double* __restrict__ x,
                                                          const CgVec* __restrict__ V, CgVec* __restrict__ V_new,
-                                                         double* __restrict__ cg_slots, CgScalars* sc) {
+                                                         double* __restrict__ cg_slots, double* __restrict__ part,
+                                                         CgScalars* sc) {
     extern __shared__ double s_u[];
-    constexpr int R = kBlockRows, H = kHaloRegs;
+    constexpr int R = kBlockRows, H = kHaloRegs, NW = R / 64;
+    __shared__ double s_dot[kTwin ? 3 : 1][NW];
     // The converged flag, the previous kernel's dot slots and this workgroup's first block
     // are all in flight together; the flag (the same for every thread) is checked before
     // any write, so a launch after convergence changes nothing.
     const int conv = sc->converged;
     const double tol2_bb = sc->tol2_bb, bb = sc->bb, gam_old = sc->gam[(i + 1) & 1], alpha_old = sc->alpha[(i + 1) & 1];
     double t[3];
-    slot_load_wave<3>(cg_buf(cg_slots, i), t);
+    if (!kTwin || i == 0) {
+        slot_load_wave<3>(kTwin ? cg_slots : cg_buf(cg_slots, i), t);
+    } else {
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            t[j] = threadIdx.x < bc.nb ? part[(3 * (i & 1) + j) * R + threadIdx.x] : 0.0;
+    }
     int64_t b = rg_first(rg);
     const int64_t le = rg_end(rg);
     if (b >= le) return;   // the whole workgroup
@@ -932,30 +988,39 @@ __global__ __launch_bounds__(kBlockRows) void k_cg_iter(int64_t n_rows, RowGrid 
             }
     };
     load();
+    double g, d, rr;
+    if (!kTwin || i == 0) {
+        g = wave_total(t[0]);
+        d = wave_total(t[1]);
+        rr = wave_total(t[2]);
+    } else {
+        // by all waves, also one that has already seen the flag that workgroup 0 sets below
+        sum_waves<3, NW>(t, s_dot);
+        __syncthreads();
+        g = over_waves<NW>(s_dot[0]);
+        d = over_waves<NW>(s_dot[1]);
+        rr = over_waves<NW>(s_dot[2]);
+    }
     if (conv) return;
-    const double g = wave_total(t[0]), d = wave_total(t[1]), rr = wave_total(t[2]);
-    const bool done = !(rr > tol2_bb) || bb == 0.0;
-    const double beta = (i == 0) ? 0.0 : g / gam_old;
-    const double alpha = (i == 0) ? g / d : g / (d - beta * g / alpha_old);
-    const bool bad = !done && !(alpha > 0.0 && alpha < INFINITY && beta >= 0.0 && beta < INFINITY);
+    const CgStep st = cg_step(i, g, d, rr, gam_old, alpha_old, tol2_bb, bb);
+    const double alpha = st.alpha, beta = st.beta;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         sc->gam[i & 1] = g;
         sc->alpha[i & 1] = alpha;
         sc->rr = rr;
         sc->iters = i;
         if (i == 0) sc->rr0 = rr;
-        if (done) sc->converged = 1;
-        if (bad) sc->converged = 2;
+        if (st.conv) sc->converged = st.conv;
     }
-    if (done || bad) return;
-    if (blockIdx.x == 0)   // read by the previous kernel; the next one adds into it
+    if (st.conv || i >= n_max) return;
+    if (!kTwin && blockIdx.x == 0)   // read by the previous kernel; the next one adds into it
         for (int k = threadIdx.x; k < 3 * kCgSlots; k += R) cg_buf(cg_slots, i + 2)[k] = 0.0;
     double v[3] = {0.0, 0.0, 0.0};
-    auto u_new = [&](double2 w, double s) { return w.x - alpha * (w.y + beta * s); };
+    auto u_new = [&](double2 w, double s) { return fma(-alpha, fma(beta, s, w.y), w.x); };
     for (;;) {
         const int64_t row = b * R + threadIdx.x;
-        const double sj = own_rw.y + beta * own_sp.x;   // D^-1 s
-        const double un = own_rw.x - alpha * sj;        // D^-1 r' = u'
+        const double sj = fma(beta, own_sp.x, own_rw.y);   // D^-1 s
+        const double un = fma(-alpha, sj, own_rw.x);       // D^-1 r' = u'
         s_u[threadIdx.x] = un;
 #pragma unroll
         for (int k = 0; k < H; ++k)
@@ -972,15 +1037,21 @@ __global__ __launch_bounds__(kBlockRows) void k_cg_iter(int64_t n_rows, RowGrid 
             acc = P.dot_wide(col, A, [&](int c) { return u_new(*reinterpret_cast<const double2*>(V + c), V[c].S); });
         if (row < n_rows) {
             const double diag = P.a[0];
-            const double pj = own_rw.x + beta * own_sp.y;
-            x[row] = own_x + alpha * pj;
-            const double rn = un * diag;
+            const double pj = fma(beta, own_sp.y, own_rw.x);
+            x[row] = fma(alpha, pj, own_x);
             double2* o = reinterpret_cast<double2*>(V_new + row);
             o[0] = make_double2(un, acc / diag);
             o[1] = make_double2(sj, pj);
-            v[0] += rn * un;
-            v[1] += un * acc;
-            v[2] += rn * rn;
+            double dots[3];
+            cg_dots(un, acc, diag, dots);
+#pragma unroll
+            for (int j = 0; j < 3; ++j) v[j] += dots[j];
+        }
+        if (kTwin) {   // one block per workgroup; s_dot has been read before the barrier above
+            sum_waves<3, NW>(v, s_dot);
+            __syncthreads();
+            if (threadIdx.x < 3) part[(3 * ((i + 1) & 1) + threadIdx.x) * R + b] = over_waves<NW>(s_dot[threadIdx.x]);
+            return;
         }
         b += rg.g;
         if (b >= le) break;
@@ -1106,7 +1177,7 @@ __device__ __forceinline__ void wait_boxes(const Mail& m, A& a, B& b, unsigned t
 // -> 3.0, 90k 7.0 -> 3.5 (registers capped for two workgroups per CU: 0.8 us more, by spills).
 // Every wait is bounded: a workgroup that polls `polls` times in vain sets gave_up and
 // leaves, those that wait for its next values follow in the same way, and the host solves by
-// k_cg_iter.  If it was the last exchange the others finish and report, which is why gave_up
+// k_cg_iter<true>, to the same bits.  If it was the last exchange the others finish and report, which is why gave_up
 // is a field that only a workgroup giving up writes, and why the iterate goes into an array
 // of its own: x, V and the slots are left as they were.
 // n_max: the iterate at which the solve stops unconverged.
@@ -1151,11 +1222,9 @@ __global__ __launch_bounds__(kBlockRows) __attribute__((amdgpu_waves_per_eu(2)))
     double gam_old = 0.0, alpha_old = 0.0;
     int conv = 0, i = 0;
     for (;; ++i) {
-        const bool done = !(rr > tol2_bb) || bb == 0.0;
-        const double beta = (i == 0) ? 0.0 : g / gam_old;
-        const double alpha = (i == 0) ? g / d : g / (d - beta * g / alpha_old);
-        const bool bad = !done && !(alpha > 0.0 && alpha < INFINITY && beta >= 0.0 && beta < INFINITY);
-        conv = done ? 1 : (bad ? 2 : 0);
+        const CgStep st = cg_step(i, g, d, rr, gam_old, alpha_old, tol2_bb, bb);
+        const double alpha = st.alpha, beta = st.beta;
+        conv = st.conv;
         if (conv || i >= n_max) break;
         gam_old = g;
         alpha_old = alpha;
@@ -1177,25 +1246,16 @@ __global__ __launch_bounds__(kBlockRows) __attribute__((amdgpu_waves_per_eu(2)))
         const int buf = (i + 1) & 1;
         double v[3] = {0.0, 0.0, 0.0};
         if (row < n_rows) {
-            const double diag = P.a[0], rn = u * diag;
+            const double diag = P.a[0];
             w = acc / diag;
             mail.put(w_box(buf, row), w, tag);
-            v[0] = rn * u;
-            v[1] = u * acc;
-            v[2] = rn * rn;
+            cg_dots(u, acc, diag, v);
         }
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            const double a = wave_total(v[j]);
-            if ((tid & 63) == 0) s_own[j][wave] = a;
-        }
+        sum_waves<3, NW>(v, s_own);
         __syncthreads();
         if ((tid & 3) < 3 && tid < 4 * kSolveCopies) {
             const int j = tid & 3, copy = tid >> 2;
-            double a = 0.0;
-#pragma unroll
-            for (int q = 0; q < NW; ++q) a += s_own[j][q];
-            mail.put(p_box(buf, copy, (int)b) + 16 * j, a, tag);
+            mail.put(p_box(buf, copy, (int)b) + 16 * j, over_waves<NW>(s_own[j]), tag);
         }
         // the partials of all workgroups, one per thread, and the halo's values
         Inbox<double, 3> pin;
@@ -1209,23 +1269,15 @@ __global__ __launch_bounds__(kBlockRows) __attribute__((amdgpu_waves_per_eu(2)))
         for (int j = 0; j < 3; ++j) v[j] = pin.value(j);
 #pragma unroll
         for (int k = 0; k < H; ++k) hw[k] = win.value(k);
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            const double a = wave_total(v[j]);
-            if ((tid & 63) == 0) s_dot[j][wave] = a;
-        }
+        sum_waves<3, NW>(v, s_dot);
         __syncthreads();
         if (s_fail) {
             if (tid == 0) sc->gave_up = 1;
             return;
         }
-        g = d = rr = 0.0;
-#pragma unroll
-        for (int q = 0; q < NW; ++q) {
-            g += s_dot[0][q];
-            d += s_dot[1][q];
-            rr += s_dot[2][q];
-        }
+        g = over_waves<NW>(s_dot[0]);
+        d = over_waves<NW>(s_dot[1]);
+        rr = over_waves<NW>(s_dot[2]);
     }
     if (row < n_rows) x_out[row] = xr;
     if (b == 0 && tid == 0) {
@@ -2287,6 +2339,7 @@ __global__ __launch_bounds__(kBlock) void k_line_apply(int64_t n, const double* 
 constexpr size_t kSlot = 4 * kMaxGrid;
 enum { SLOT_RHS = 0, SLOT_CG, SLOT_RESID, SLOT_DOT, SLOT_COUNT };
 static_assert(4 * 3 * kCgSlots <= kSlot, "iteration slots fit one partial region");
+static_assert(3 * 3 * kCgSlots + 2 * 3 * kBlockRows <= kSlot, "so do k_cg_iter<true>'s partials, behind them");
 
 }  // namespace
 
@@ -2397,12 +2450,15 @@ inline RowGrid block_grid(const BlockCols& bc, int max_grid = 0) {
 inline size_t staged_bytes(const BlockCols& bc, size_t value) { return value * (size_t)(kBlockRows + bc.stride); }
 
 // Iteration i reads the interleaved state from buffer i & 1 and writes buffer (i + 1) & 1.
-void launch_cg_iter(hipStream_t s, int i, int64_t n_rows, const int64_t* sp, const int32_t* col, const BlockCols& bc,
-                    const double* A, double* x, CgVec* const v[2], double* partial, CgScalars* sc, bool det) {
-    const RowGrid rg = block_grid(bc, det ? kCgSlots : 0);
+void launch_cg_iter(hipStream_t s, int i, int64_t n_rows, int n_max, const int64_t* sp, const int32_t* col,
+                    const BlockCols& bc, const double* A, double* x, CgVec* const v[2], double* partial, CgScalars* sc,
+                    bool det, bool twin) {
+    const RowGrid rg = block_grid(bc, det && !twin ? kCgSlots : 0);
     const int a = i & 1, b = 1 - a;
-    hipLaunchKernelGGL(k_cg_iter, dim3(rg.grid), dim3(kBlockRows), staged_bytes(bc, sizeof(double)), s, n_rows, rg, i, sp,
-                       col, bc, A, x, v[a], v[b], partial + SLOT_CG * kSlot, sc);
+    double* const slots = partial + SLOT_CG * kSlot;
+    hipLaunchKernelGGL(twin ? k_cg_iter<true> : k_cg_iter<false>, dim3(rg.grid), dim3(kBlockRows),
+                       staged_bytes(bc, sizeof(double)), s, n_rows, rg, i, twin ? n_max : INT32_MAX, sp, col, bc, A, x,
+                       v[a], v[b], slots, slots + 3 * 3 * kCgSlots, sc);
 }
 
 int64_t cg_solve_boxes(const BlockCols& bc) { return bc.nb * (4 * kBlockRows + 12 * kSolveCopies); }

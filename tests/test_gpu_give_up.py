@@ -3,6 +3,7 @@ every workgroup leaves at the first wait, and the solve is made by kernels.  All
 solve (one and two row blocks per workgroup, FP64 and FP32), held to the stopping rule
 recomputed in numpy.  With a bound of a few polls some workgroups leave and some do not.
 """
+import numpy as np
 import pytest
 
 from gpu_common import announce, have_gpu, jittered_kuhn, require_lib
@@ -79,3 +80,41 @@ def test_given_up_by_some(F, solve):
         got = step(polls)
         # by kernels the dots' order varies; a restart from a torn iterate takes several more
         assert got == whole or (got[1:] == (F.FEPIC_SOLVE_FORM_KERNELS, 1) and abs(got[0] - kernels[0]) <= 1), polls
+
+
+# the deterministic mode's bits do not depend on whether, or where, a solve was given up
+@pytest.mark.parametrize("n", [2, 7, 26])   # 1, 5 and 253 row blocks
+def test_deterministic_whatever_the_form(F, n):
+    announce(f"deterministic, one-launch solves given up: n={n}")
+    xyz, tets = jittered_kuhn(n, seed=1)[:2]
+
+    def run(polls):
+        with F.Simulation(xyz, tets, device=0, cg_tol=TOL, **options(F, "deterministic")) as L:
+            _, _, d, dt = operators(F, L)
+            start(F, L, d)
+            F.fepic_set_solve_polls(L.ctx, polls)
+            stats = [F.fepic_step(L.ctx, dt) for _ in range(3)]
+            return ([(s.cg_iters, s.cg_rel_resid, s.cg_rel_resid0) for s in stats],) + F.fepic_get_fields(L.ctx)
+
+    ref = run(F.FEPIC_SOLVE_POLLS)
+    assert ref[0][0][0] > 0
+    for polls in (-1, 0, 1, 2, 4):
+        got = run(polls)
+        assert got[0] == ref[0], polls
+        for a, b in zip(got[1:], ref[1:]):
+            assert np.array_equal(a.view(np.uint64), b.view(np.uint64)), polls
+
+
+def test_deterministic_budget_whatever_the_form(F):
+    announce("deterministic, iteration budget, one-launch solves off")
+    xyz, tets = jittered_kuhn(7, seed=1)[:2]
+    with F.Simulation(xyz, tets, device=0, cg_tol=TOL, preconditioner=F.FEPIC_PC_JACOBI, deterministic=1,
+                      cg_max_iters=3) as L:
+        _, _, d, dt = operators(F, L)
+        start(F, L, d)
+        before = F.fepic_get_fields(L.ctx)
+        for polls in (F.FEPIC_SOLVE_POLLS, -1):
+            F.fepic_set_solve_polls(L.ctx, polls)
+            with pytest.raises(F.FepicError):
+                F.fepic_step(L.ctx, dt)
+            assert all(np.array_equal(a, b) for a, b in zip(F.fepic_get_fields(L.ctx), before))
