@@ -247,8 +247,10 @@ int fepic_set_solve_precision(fepic_ctx* ctx, int solve_precision);
  * values.  Every wait is bounded, by `polls` rounds of looking for them (default
  * FEPIC_SOLVE_POLLS, about a tenth of a second; a round trip takes a few): where other work
  * on the GPU keeps some workgroups from starting for that long, the solve is given up and
- * made by a launch per iteration and kernel, as on larger meshes.  0 gives up at the first
- * wait; -1 makes no one-launch solves (FEPIC_E_ARG below that). */
+ * made by a launch per iteration and kernel, as on larger meshes; so are the next solves, one,
+ * or twice as many as the last time if none succeeded since (up to 1024), before another is
+ * tried in one launch.  0 gives up at the first wait; -1 makes no one-launch solves
+ * (FEPIC_E_ARG below that). */
 #define FEPIC_SOLVE_POLLS (1 << 17)
 int fepic_set_solve_polls(fepic_ctx* ctx, int polls);
 /* How the last solve (with FEPIC_SOLVE_MIXED: its last pass) was made, FEPIC_SOLVE_FORM_*,

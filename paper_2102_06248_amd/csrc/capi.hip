@@ -994,12 +994,23 @@ bool mlp_start_rejected(int mode, double rr0, double bb) {
 // *solved, with the scalars on the host.  Not solved, the iterations are launched one by one:
 // there is no memory for the words, the launch was refused, or some workgroup gave up waiting
 // (h_sc->gave_up: the device's scalars have to be set up again, the start is as it was).
-// *again: whether the context may try the next time (not after either of the last two).
+// After either of the last two the next solves are by kernels, for as long as the pauses
+// have grown to (a wait in vain costs a tenth of a second, and other work on the GPU may
+// last, or be gone by the next solve).
+constexpr int kMaxPause = 1024;
 template <typename F>
-int solve_one_launch(fepic_ctx* c, int64_t n, int n_max, bool* again, bool* solved, F&& launch) {
+int solve_one_launch(fepic_ctx* c, int64_t n, int n_max, bool* solved, F&& launch) {
     *solved = false;
     c->h_sc->gave_up = 0;
     if (n_max <= 0 || c->solve_polls < 0) return FEPIC_OK;
+    if (c->one_launch_skip > 0) {
+        --c->one_launch_skip;
+        return FEPIC_OK;
+    }
+    auto pause = [&]() {
+        c->one_launch_pause = std::min(std::max(1, 2 * c->one_launch_pause), kMaxPause);
+        c->one_launch_skip = c->one_launch_pause;
+    };
     bool fresh = (uint64_t)c->box_tag + (uint64_t)n_max > 0xffffffffull;
     if (c->n_boxes < n) {
         dfree(c, c->d_boxes);
@@ -1018,18 +1029,19 @@ int solve_one_launch(fepic_ctx* c, int64_t n, int n_max, bool* again, bool* solv
     const hipError_t e = launch(c->d_boxes, c->box_tag);
     if (ev) (void)hipEventRecord(ev[1], c->stream);
     if (e != hipSuccess) {
-        *again = false;
+        pause();
         return FEPIC_OK;
     }
     HIPCHK(c, hipMemcpyAsync(c->h_sc, c->d_sc, sizeof(CgScalars), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     *solved = !c->h_sc->gave_up;
     if (!*solved) {
-        *again = false;
+        pause();
         c->solves_given_up++;
         c->box_tag += (uint32_t)n_max;
         return FEPIC_OK;
     }
+    c->one_launch_pause = 0;
     c->solve_form = FEPIC_SOLVE_FORM_ONE_LAUNCH;
     c->box_tag += (uint32_t)c->h_sc->iters + 1;   // a breakdown leaves words of the iteration it stopped in
     if (ev) c->timers[FAM_CG_ITER].launches += c->h_sc->iters + 1;   // counted as the iterations it stands for
@@ -1196,9 +1208,8 @@ int field_phase(fepic_ctx* c, double dt, double beta, double gamma) {
             bool solved = false;
             const int n_max = maxit - total, blocks = c->aux.n_far <= 1 ? c->one_launch_pcg[1] : 0;
             if (blocks) {
-                bool again = true;
                 rc = solve_one_launch(
-                    c, pcg_solve_boxes<float>(c->bc, c->solve_lists, ne, c->aux.n_aux, blocks), n_max, &again, &solved,
+                    c, pcg_solve_boxes<float>(c->bc, c->solve_lists, ne, c->aux.n_aux, blocks), n_max, &solved,
                     [&](unsigned long long* boxes, uint32_t tag) {
                         return launch_pcg_solve<float, float2>(c->stream, blocks, ne, n_max, c->d_sp, c->bc, c->d_A32,
                                                                c->d_dinv32, c->d_x32, c->d_x32, ZP32[0], c->d_rq32,
@@ -1206,7 +1217,6 @@ int field_phase(fepic_ctx* c, double dt, double beta, double gamma) {
                                                                c->d_partial, c->d_sc);
                     });
                 if (rc != FEPIC_OK) return rc;
-                if (!again) c->one_launch_pcg[1] = 0;
                 if (c->h_sc->gave_up)   // from zero again
                     launch_pcg_init_f32(c->stream, ne, c->d_sp, c->d_col, c->d_dinv32, c->d_rt, c->d_x32, c->aux,
                                         ZP32[0], c->d_rq32, c->d_partial, c->d_sc, tol_in);
@@ -1248,9 +1258,8 @@ int field_phase(fepic_ctx* c, double dt, double beta, double gamma) {
             c->h_sc->gave_up = 0;
             const int n_max = maxit - total, blocks = c->aux.n_far <= 1 ? c->one_launch_pcg[0] : 0;
             if (aux && blocks) {
-                bool again = true;
                 rs = solve_one_launch(
-                    c, pcg_solve_boxes<double>(c->bc, c->solve_lists, ne, c->aux.n_aux, blocks), n_max, &again, &solved,
+                    c, pcg_solve_boxes<double>(c->bc, c->solve_lists, ne, c->aux.n_aux, blocks), n_max, &solved,
                     [&](unsigned long long* boxes, uint32_t tag) {
                         const double* R = reinterpret_cast<const double*>(c->d_rq);
                         return launch_pcg_solve<double, double2>(c->stream, blocks, ne, n_max, c->d_sp, c->bc, c->d_A,
@@ -1258,9 +1267,8 @@ int field_phase(fepic_ctx* c, double dt, double beta, double gamma) {
                                                                  c->solve_lists, boxes, tag, c->solve_polls,
                                                                  c->d_partial, c->d_sc);
                     });
-                if (!again) c->one_launch_pcg[0] = 0;
-            } else if (!aux && c->one_launch && c->try_one_launch) {
-                rs = solve_one_launch(c, cg_solve_boxes(c->bc), n_max, &c->try_one_launch, &solved,
+            } else if (!aux && c->one_launch) {
+                rs = solve_one_launch(c, cg_solve_boxes(c->bc), n_max, &solved,
                                       [&](unsigned long long* boxes, uint32_t tag) {
                                           return launch_cg_solve(c->stream, ne, n_max, c->d_sp, c->bc, c->d_A, c->d_x,
                                                                  c->d_rt, V[0], boxes, tag, c->solve_polls, c->d_partial,

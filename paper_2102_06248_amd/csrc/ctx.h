@@ -121,13 +121,15 @@ struct fepic_ctx {
     int64_t n_boxes = 0;
     uint32_t box_tag = 0;                          // last tag in use there
     bool one_launch = false;                       // Jacobi: the row blocks are all resident at once
-    bool try_one_launch = true;                    // not yet given up
     fepic::SolveLists solve_lists;
     bool solve_lists_tried = false;
     int one_launch_pcg[2] = {0, 0};                // FP64, FP32: row blocks per workgroup (0: not in one launch)
     int solve_polls = FEPIC_SOLVE_POLLS;           // of one wait inside a one-launch solve; below zero: none is made
     int solve_form = FEPIC_SOLVE_FORM_NONE;        // of the last solve
     int64_t solves_given_up = 0;
+    // after a solve given up or refused, this many are made by kernels before the next try:
+    // one, and twice as many each time it happens again without a success between
+    int one_launch_skip = 0, one_launch_pause = 0;
     fepic::CgVec* d_cgv[2] = {nullptr, nullptr};   // Jacobi-PCG state, double buffered
     // auxiliary-space PCG: (z, p) pairs double buffered, r and q (n_edges each), nodal arrays
     double2* d_zp[2] = {nullptr, nullptr};

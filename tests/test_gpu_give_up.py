@@ -59,6 +59,22 @@ def test_one_launch_switched_off(F):
             assert F.fepic_get_solve_form(L.ctx) == (form, 0)
 
 
+# pauses of 1 and 2 solves by kernels after the first and the second in a row given up; a
+# success starts them afresh
+def test_tried_again(F):
+    announce("one-launch solves tried again")
+    xyz, tets = jittered_kuhn(5, seed=1)[:2]
+    with F.Simulation(xyz, tets, device=0, cg_tol=TOL, **options(F, "jacobi")) as L:
+        M, S, d, dt = operators(F, L)
+        start(F, L, d)
+        n_max = F.FEPIC_SOLVE_POLLS
+        for polls, in_one, given_up in ((0, 0, 1), (0, 0, 1), (0, 0, 2), (n_max, 0, 2), (n_max, 0, 2), (n_max, 1, 2),
+                                        (n_max, 1, 2), (0, 0, 3), (n_max, 0, 3), (n_max, 1, 3)):
+            F.fepic_set_solve_polls(L.ctx, polls)
+            assert check_step(F, L, M, S, dt) > 0
+            assert F.fepic_get_solve_form(L.ctx) == (in_one, given_up)
+
+
 # the last exchange's words may reach some workgroups and not others: a solve given up by any
 # of them is not taken, and the kernels start where it started
 @pytest.mark.parametrize("solve", ["jacobi", "fp64"])
