@@ -1043,7 +1043,9 @@ int solve_one_launch(fepic_ctx* c, int64_t n, int n_max, bool* solved, F&& launc
     }
     c->one_launch_pause = 0;
     c->solve_form = FEPIC_SOLVE_FORM_ONE_LAUNCH;
-    c->box_tag += (uint32_t)c->h_sc->iters + 1;   // a breakdown leaves words of the iteration it stopped in
+    // a breakdown leaves words of the iteration it stopped in; no tag is past the last one
+    // allowed, so that the check above sees every wrap
+    c->box_tag += (uint32_t)std::min(c->h_sc->iters + 1, n_max);
     if (ev) c->timers[FAM_CG_ITER].launches += c->h_sc->iters + 1;   // counted as the iterations it stands for
     return FEPIC_OK;
 }
