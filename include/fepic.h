@@ -477,7 +477,7 @@ int fepic_mlp_adam_step(fepic_ctx* ctx, const float* grad, double lr, double bet
  * loss [1] FP64 (the mean squared error) written, all in device memory of the context's
  * device; the kernels are enqueued on the context's stream and the call returns without
  * waiting (the caller synchronizes before reading the outputs).  The result is that of
- * fepic_mlp_grad on the same rows, summed in the same order.  The per-workgroup partial
+ * fepic_mlp_grad on the same rows, gradient and loss, bit for bit.  The per-workgroup partial
  * sums live in the context (4.7 MB, there since its weights were set or trained): calls on
  * contexts of their own may overlap, calls on one context run one after another on its
  * stream.  Errors: FEPIC_E_ARG for n <= 0, a NULL pointer or n above

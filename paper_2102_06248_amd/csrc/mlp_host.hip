@@ -61,7 +61,7 @@ static int ensure_mlp(fepic_ctx* c) {
     s->v = (float*)dmalloc(c, sizeof(float) * kNP);
     s->grad = (float*)dmalloc(c, sizeof(float) * kNP);
     s->part = (float*)dmalloc(c, sizeof(float) * kNP * kMaxGradBlocks);
-    s->loss_part = (double*)dmalloc(c, sizeof(double) * std::max(kMaxGradBlocks, 3 * 256));   // also the RMS partials
+    s->loss_part = (double*)dmalloc(c, sizeof(double) * std::max(kMaxGradBlocks + 1, 3 * 256));   // also the RMS partials
     s->na_part = (float*)dmalloc(c, sizeof(float) * kNP * kMaxGradBlocks);
     s->na_loss_part = (double*)dmalloc(c, sizeof(double) * kMaxGradBlocks);
     s->scales = (double*)dmalloc(c, sizeof(double) * 5);  // s_d, s_g, line step, target RMS, s_e
@@ -435,17 +435,13 @@ int fepic_mlp_grad(fepic_ctx* c, int64_t n, const float* X, const float* t, floa
     if ((rc = host_batch(c, n, X, t))) return rc;
     MlpState* s = c->mlp;
     const int blocks = mlp_grad_blocks(n);
+    double* const d_loss = s->loss_part + kMaxGradBlocks;   // behind the partial sums
     mlp_launch_grad(c->stream, s->Xh, s->Th, n, 0, 0, s->P, s->part, s->loss_part, blocks);
-    mlp_launch_reduce_adam(c->stream, s->part, blocks, s->grad, s->P, s->m, s->v, 0, 0.f, 0.f, 0.f, 0.f, 1.f, 1.f);
-    std::vector<double> lp(blocks);
+    mlp_launch_reduce_adam(c->stream, s->part, blocks, s->grad, s->P, s->m, s->v, 0, 0.f, 0.f, 0.f, 0.f, 1.f, 1.f,
+                           s->loss_part, 1.0 / (double)n, d_loss);
     HIPCHK_RET(c, hipStreamSynchronize(c->stream));
     HIPCHK_RET(c, hipMemcpy(grad, s->grad, sizeof(float) * kNP, hipMemcpyDeviceToHost));
-    HIPCHK_RET(c, hipMemcpy(lp.data(), s->loss_part, sizeof(double) * blocks, hipMemcpyDeviceToHost));
-    if (loss) {
-        double a = 0.0;
-        for (double v : lp) a += v;
-        *loss = a / (double)n;
-    }
+    if (loss) HIPCHK_RET(c, hipMemcpy(loss, d_loss, sizeof(double), hipMemcpyDeviceToHost));
     return FEPIC_OK;
 }
 
