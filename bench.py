@@ -39,8 +39,7 @@ KERNEL_NAMES = {"push": "k_push+k_cross|k_cross_sparse", "stage": "k_stage", "so
                 "faraday": "k_faraday"}
 MIXED_ITER_KERNEL = "k_pcg_q<float>+k_pcg_nodes<float>+k_pcg_fold<float>+k_pcg_update<float, 2>"
 JACOBI_ITER_KERNEL = "k_cg_iter"
-ONE_LAUNCH_KERNEL = "k_pcg_solve"   # a whole solve; figures per iteration
-ONE_LAUNCH_ROWS = 2 * 256 * 512     # two row blocks for each CU
+ONE_LAUNCH_KERNELS = {"jacobi": "k_cg_solve", "aux": "k_pcg_solve"}   # a whole solve; figures per iteration
 KERNEL_SOURCES = {"push": "kernels_particles.hip", "stage": "kernels_particles.hip", "sort": "kernels_particles.hip",
                   "rhs": "kernels_fields.hip", "cg_iter": "kernels_fields.hip", "faraday": "kernels_fields.hip"}
 EXTRA_DEFAULT = "c1_single_electron,c2_beam,c3_plasma"
@@ -102,6 +101,21 @@ def algorithmic_bytes(fam, geo, st, pc="aux", solve="fp64", precision=0):
     if fam == "sort":         # histogram read of tet; scatter read + write of 36 B payload
         return npart * (4 + 72) + 12 * nt
     return 0
+
+
+def iteration_roofline(pc, solve, one_launch, gbs, traffic):
+    """Name and bound of the PCG iteration: the kernels of an iteration stream the matrix and
+    are held against HBM; a one-launch solve has it in registers and is paced by the exchanges
+    between its workgroups, so the method's bytes per second are no measure of it."""
+    if one_launch:
+        waits = "one exchange" if pc == "jacobi" else "three exchanges"
+        return {"bound": "exchange", "achieved": None, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": None,
+                "traffic": None, "kernel": ONE_LAUNCH_KERNELS[pc],
+                "note": f"one launch per solve, the matrix in registers; {waits} between workgroups per iteration"}
+    kernel = (JACOBI_ITER_KERNEL if pc == "jacobi" else MIXED_ITER_KERNEL if solve == "mixed"
+              else KERNEL_NAMES["cg_iter"])
+    return {"bound": "hbm", "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+            "frac": round(gbs / HBM_PEAK_GBS, 4), "traffic": traffic, "kernel": kernel}
 
 
 def source_hash(fam):
@@ -510,22 +524,20 @@ def run_workload(args, F, torch, name, steps, warmup, with_cpu, with_fp64_solve)
     traffic = traffic_from_profile(dominant, name, pc, solve)
     if traffic is not None:
         traffic = int(traffic * work_share)   # counters are per working launch (median)
-    # a one-launch solve keeps the matrix in registers: the bytes are the method's per
-    # iteration, not HBM's, and what bounds it is the exchange between workgroups
-    one_launch = pc == "aux" and geo["n_edges"] <= ONE_LAUNCH_ROWS
-    if one_launch and dominant == "cg_iter":
-        traffic = None
-    roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
-                "kernel": (JACOBI_ITER_KERNEL if pc == "jacobi" else ONE_LAUNCH_KERNEL if one_launch
-                           else MIXED_ITER_KERNEL if solve == "mixed"
-                           else KERNEL_NAMES[dominant]) if dominant == "cg_iter" else KERNEL_NAMES[dominant],
-                "avg_launch_us": round(avg_s * 1e6, 3), "launches": nl,
-                "working_launch_share": round(work_share, 4),
-                "algorithmic_bytes_per_launch": int(per_launch * work_share)}
-    if one_launch and dominant == "cg_iter":
-        roofline["note"] = ("one launch per solve, the matrix in registers: achieved counts the bytes that a "
-                            "streaming iteration would move; three exchanges between workgroups set the pace")
+    # how the solves were made, as the library reports it (solves given up in the timed steps
+    # were by kernels after all)
+    form, given_up = F.fepic_get_solve_form(ctx)
+    one_launch = form == F.FEPIC_SOLVE_FORM_ONE_LAUNCH
+    if dominant == "cg_iter":
+        roofline = iteration_roofline(pc, solve, one_launch, achieved, traffic)
+    else:
+        roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                    "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic, "kernel": KERNEL_NAMES[dominant]}
+    roofline.update({"avg_launch_us": round(avg_s * 1e6, 3), "launches": nl,
+                     "working_launch_share": round(work_share, 4),
+                     "algorithmic_bytes_per_launch": int(per_launch * work_share)})
+    if given_up:
+        roofline["solves_given_up"] = given_up
 
     # the particle kernels' own roofline: one launch = one species' k_push (+ k_cross)
     pms, pn = fam_time["push"]
