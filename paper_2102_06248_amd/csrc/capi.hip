@@ -399,20 +399,43 @@ int read_out_plain(fepic_ctx* c, const std::vector<OutArray>& arrays) {
 constexpr size_t kOutBytes = 1u << 20;
 constexpr size_t kPinTail = 4096;   // behind it: the counters, and the stats of the first species
 
-// The buffer and, for edge vectors, the permutation; false if there is no room for them.
-bool reserve_read_out(fepic_ctx* c, bool edges) {
-    if (!c->h_out) return false;
-    if (edges && !c->d_eperm) {
-        const std::string err = c->err;
-        if (upload(c, &c->d_eperm, c->mesh.eperm) != FEPIC_OK) {
+// The pinned block that kernels write (blocks of less than a MiB cost 350 us at their first
+// use); without room for the read-outs' part, the counters' alone.  Allocated by the first
+// call that belongs to a simulation (its fields, a species, a step or a read-out): a context
+// for the network's gradients has no use for it (its creation took 90 us with it, 68 without,
+// or 295 and 230 where the runtime has no such block left from another).
+int reserve_pinned(fepic_ctx* c) {
+    if (c->h_pin) return FEPIC_OK;
+    size_t tail_at = kOutBytes;
+    if (hipHostMalloc((void**)&c->h_pin, kOutBytes + kPinTail) != hipSuccess) {
+        tail_at = 0;
+        (void)hipGetLastError();
+        c->h_pin = nullptr;
+        if (hipHostMalloc((void**)&c->h_pin, kPinTail) != hipSuccess) {
             (void)hipGetLastError();
-            dfree(c, c->d_eperm);
-            c->d_eperm = nullptr;
-            c->err = err;
-            return false;
+            c->h_pin = nullptr;
+            return fail(c, FEPIC_E_OOM, "pinned allocation");
         }
     }
-    return true;
+    unsigned char* const tail = c->h_pin + tail_at;
+    std::memset(tail, 0, kPinTail);
+    c->h_out = tail_at ? c->h_pin : nullptr;
+    c->h_cnt = reinterpret_cast<PushCounters*>(tail);
+    c->h_stats = reinterpret_cast<SpeciesStat*>(tail + 128);
+    c->stat_species = (int)((kPinTail - 128) / sizeof(SpeciesStat));
+    return FEPIC_OK;
+}
+
+// The permutation of edge vectors on the device; false if there is no room for it.
+bool reserve_edge_order(fepic_ctx* c) {
+    if (c->d_eperm) return true;
+    const std::string err = c->err;
+    if (upload(c, &c->d_eperm, c->mesh.eperm) == FEPIC_OK) return true;
+    (void)hipGetLastError();
+    dfree(c, c->d_eperm);
+    c->d_eperm = nullptr;
+    c->err = err;
+    return false;
 }
 
 int read_out(fepic_ctx* c, std::initializer_list<OutArray> list) {
@@ -427,7 +450,9 @@ int read_out(fepic_ctx* c, std::initializer_list<OutArray> list) {
         HIPCHK(c, hipStreamSynchronize(c->stream));
         return FEPIC_OK;
     }
-    if (!reserve_read_out(c, edges)) return read_out_plain(c, arrays);
+    const std::string err = c->err;
+    if (reserve_pinned(c) != FEPIC_OK) c->err = err;   // without it: plain copies
+    if (!c->h_out || (edges && !reserve_edge_order(c))) return read_out_plain(c, arrays);
     struct Copy {
         void* to;
         const void* from;
@@ -561,8 +586,8 @@ CrossQueue<T> cqueue(fepic_ctx* c) {
     return q;
 }
 
-// Room for the counter slots and stats of n species.
-int fit_species(fepic_ctx* c, int n) {
+// Room for the counter slots of n species.
+int fit_slots(fepic_ctx* c, int n) {
     if (n > c->slot_species) {
         const int cap = std::max(n, 2 * c->slot_species);
         PushCounters* p = dalloc<PushCounters>(c, (int64_t)kCntSlots * cap);
@@ -573,6 +598,13 @@ int fit_species(fepic_ctx* c, int n) {
         c->d_cnt_slots = p;
         c->slot_species = cap;
     }
+    return FEPIC_OK;
+}
+
+// Room for the counter slots and stats of n species.
+int fit_species(fepic_ctx* c, int n) {
+    int rc = fit_slots(c, n);
+    if (rc || (rc = reserve_pinned(c))) return rc;
     if (n > c->stat_species) {
         SpeciesStat* p = nullptr;
         const int cap = 2 * n;
@@ -1467,6 +1499,7 @@ int do_step(fepic_ctx* c, double dt, double beta, double gamma, fepic_step_stats
     NEED_DEV(c);
     if (!(dt > 0) || !std::isfinite(dt) || !std::isfinite(beta) || !std::isfinite(gamma))
         return fail(c, FEPIC_E_ARG, "bad step parameters");
+    if (const int rp = reserve_pinned(c)) return rp;
     fepic_step_stats st;
     std::memset(&st, 0, sizeof(st));
     st.gauss_drift_check_rel = st.cont_resid_rel = st.gauss_resid_rel = -1.0;
@@ -1785,25 +1818,11 @@ int fepic_create(const fepic_options* opts, fepic_ctx** out) {
             return FEPIC_E_HIP;
         }
         c->stream = c->own_stream;
-        // one pinned block that kernels write (blocks of less than a MiB cost 350 us at their
-        // first use); without room for the read-outs' part, the counters' alone
-        if (hipHostMalloc((void**)&c->h_pin, kOutBytes + kPinTail) == hipSuccess) {
-            c->h_out = c->h_pin;
-        } else {
-            (void)hipGetLastError();
-            c->h_pin = nullptr;
-        }
-        if ((!c->h_pin && hipHostMalloc((void**)&c->h_pin, kPinTail) != hipSuccess) ||
-            hipHostMalloc((void**)&c->h_sc, sizeof(CgScalars)) != hipSuccess ||
+        if (hipHostMalloc((void**)&c->h_sc, sizeof(CgScalars)) != hipSuccess ||
             hipHostMalloc((void**)&c->h_acc, sizeof(DiagAcc)) != hipSuccess) {
             delete c;
             return FEPIC_E_OOM;
         }
-        unsigned char* const tail = c->h_pin + (c->h_out ? kOutBytes : 0);
-        std::memset(tail, 0, kPinTail);
-        c->h_cnt = reinterpret_cast<PushCounters*>(tail);
-        c->h_stats = reinterpret_cast<SpeciesStat*>(tail + 128);
-        c->stat_species = (int)((kPinTail - 128) / sizeof(SpeciesStat));
         for (auto& e : c->phase_ev) (void)hipEventCreate(&e);
     }
     *out = c;
@@ -2007,7 +2026,7 @@ int fepic_upload_mesh(fepic_ctx* c, int64_t n_nodes, const double* xyz, int64_t 
         (rc = upload(c, &c->d_cell_tets, m.cell_tets)) || (rc = upload(c, &c->d_int_edges, m.dev_int_edges)))
         return rc;
     if ((rc = build_blocks(c, m.mat, c->d_sp, c->d_col))) return rc;
-    (void)reserve_read_out(c, true);   // short of room, a read-out sees to itself
+    (void)reserve_edge_order(c);   // short of room, a read-out sees to itself
     std::vector<double> g3 = {m.grid_lo[0], m.grid_lo[1], m.grid_lo[2], m.grid_inv_h[0], m.grid_inv_h[1], m.grid_inv_h[2]};
     std::vector<int32_t> gn = {m.grid_n[0], m.grid_n[1], m.grid_n[2]};
     if ((rc = upload(c, &c->d_grid, g3)) || (rc = upload(c, &c->d_grid_n, gn))) return rc;
@@ -2109,7 +2128,7 @@ int fepic_upload_mesh(fepic_ctx* c, int64_t n_nodes, const double* xyz, int64_t 
     c->d_partial = dalloc<double>(c, (int64_t)partial_buffer_doubles());
     c->d_sc = dalloc<CgScalars>(c, 1);
     c->d_cnt = dalloc<PushCounters>(c, 1);
-    if ((rc = fit_species(c, std::max<int>(4, (int)c->species.size())))) return rc;
+    if ((rc = fit_slots(c, 4))) return rc;
     c->d_acc = dalloc<DiagAcc>(c, 1);
     c->d_dotc = dalloc<unsigned int>(c, 1);
     c->d_live = dalloc<double>(c, 1);
@@ -2184,6 +2203,7 @@ int fepic_get_matrix(fepic_ctx* c, int which, int64_t cap, int64_t* nnz, int64_t
 
 int fepic_set_fields(fepic_ctx* c, const double* e, const double* e_prev, const double* b) {
     NEED_DEV(c);
+    (void)reserve_pinned(c);   // a step asks again
     const HostMesh& m = c->mesh;
     auto put_e = [&](double* dst, const double* src) -> int {
         std::vector<double> v(m.n_edges);
