@@ -195,25 +195,30 @@ int build_blocks(fepic_ctx* c, const SellMatrix& mat, const int64_t* sp, const i
     return FEPIC_OK;
 }
 
-// The lists of the one-launch solve with the auxiliary space to the device, and how many row
-// blocks its workgroups take; none if the mesh is past their limits or memory is short.
+// The lists of the one-launch solve with the auxiliary space to the device, in one
+// allocation and one copy, and how many row blocks its workgroups take; none if the mesh is
+// past their limits or memory is short.
 void prepare_one_launch(fepic_ctx* c) {
     c->solve_lists_tried = true;
     const HostSolveLists m = build_solve_lists(c->mesh);
     if (m.stride == 0) return;
-    int32_t *edge = nullptr, *cnt = nullptr, *xsp = nullptr, *node = nullptr, *n_node = nullptr, *agg = nullptr;
-    uint16_t *lc = nullptr, *xlc = nullptr;
-    uint8_t* node_agg = nullptr;
-    uint32_t* ends = nullptr;
-    int rc;
+    constexpr size_t kAlign = 256;
+    std::vector<unsigned char> all;
+    auto put = [&](const auto& v) {
+        const size_t at = all.size(), bytes = v.size() * sizeof(v[0]);
+        all.resize(at + (bytes + kAlign - 1) / kAlign * kAlign);
+        if (bytes) std::memcpy(all.data() + at, v.data(), bytes);
+        return at;
+    };
+    all.reserve(4 * (m.edge.size() + m.cnt.size() + m.xsp.size() + m.node.size() + m.n_node.size() + m.agg.size() +
+                     m.ends.size()) + 2 * (m.lc.size() + m.xlc.size()) + m.node_agg.size() + 10 * kAlign);
+    const size_t edge = put(m.edge), cnt = put(m.cnt), lc = put(m.lc), xsp = put(m.xsp), xlc = put(m.xlc),
+                 node = put(m.node), n_node = put(m.n_node), node_agg = put(m.node_agg), agg = put(m.agg),
+                 ends = put(m.ends);
+    unsigned char* d = nullptr;
     const std::string err = c->err;
-    if ((rc = upload(c, &edge, m.edge)) || (rc = upload(c, &cnt, m.cnt)) || (rc = upload(c, &xsp, m.xsp)) ||
-        (rc = upload(c, &node, m.node)) || (rc = upload(c, &n_node, m.n_node)) || (rc = upload(c, &agg, m.agg)) ||
-        (rc = upload(c, &lc, m.lc)) || (rc = upload(c, &xlc, m.xlc)) || (rc = upload(c, &node_agg, m.node_agg)) ||
-        (rc = upload(c, &ends, m.ends))) {
-        for (void* p : {(void*)edge, (void*)cnt, (void*)xsp, (void*)node, (void*)n_node, (void*)agg, (void*)lc,
-                        (void*)xlc, (void*)node_agg, (void*)ends})
-            dfree(c, p);
+    if (upload(c, &d, all) != FEPIC_OK) {
+        dfree(c, d);
         (void)hipGetLastError();
         c->err = err;
         return;
@@ -221,17 +226,17 @@ void prepare_one_launch(fepic_ctx* c) {
     SolveLists& l = c->solve_lists;
     l.n_slices = (int)m.cnt.size();
     l.stride = m.stride;
-    l.edge = edge;
-    l.cnt = cnt;
-    l.lc = reinterpret_cast<const uint2*>(lc);
-    l.xsp = xsp;
-    l.xlc = reinterpret_cast<const uint2*>(xlc);
+    l.edge = reinterpret_cast<const int32_t*>(d + edge);
+    l.cnt = reinterpret_cast<const int32_t*>(d + cnt);
+    l.lc = reinterpret_cast<const uint2*>(d + lc);
+    l.xsp = reinterpret_cast<const int32_t*>(d + xsp);
+    l.xlc = reinterpret_cast<const uint2*>(d + xlc);
     l.n_extra = m.xsp.back();
-    l.node = node;
-    l.n_node = n_node;
-    l.node_agg = node_agg;
-    l.agg = agg;
-    l.ends = ends;
+    l.node = reinterpret_cast<const int32_t*>(d + node);
+    l.n_node = reinterpret_cast<const int32_t*>(d + n_node);
+    l.node_agg = d + node_agg;
+    l.agg = reinterpret_cast<const int32_t*>(d + agg);
+    l.ends = reinterpret_cast<const uint32_t*>(d + ends);
     const int cu = n_cu();
     c->one_launch_pcg[0] = pcg_solve_blocks<double>(c->bc, l, cu);
     c->one_launch_pcg[1] = pcg_solve_blocks<float>(c->bc, l, cu);
