@@ -1146,12 +1146,17 @@ struct Inbox {
 // rows took 3.5 us per Jacobi iteration and 7.9 per FP64 PCG one; without 4.1 and 11.1, with
 // 32 x 64 3.7 and 8.5.  Up to 64 workgroups poll so little that 8 are enough (13k rows 2.98
 // us, with 16 3.09).  Gives up after `polls` rounds (*fail; at once if there are none).
+// Their number comes from LDS, read while the wave sleeps: in a scalar register for the whole
+// solve it cost k_pcg_solve<double, 2> 16 more spilled registers and 15% (239k rows).
 template <typename A, typename B>
-__device__ __forceinline__ void wait_boxes(const Mail& m, A& a, B& b, unsigned tag, int n_wg, int polls, int* fail) {
+__device__ __forceinline__ void wait_boxes(const Mail& m, A& a, B& b, unsigned tag, int n_wg, const int* s_polls,
+                                           int* fail) {
+    const int limit = *s_polls;
     if (n_wg > 64)
         __builtin_amdgcn_s_sleep(17);
     else
         __builtin_amdgcn_s_sleep(8);
+    const int polls = __builtin_amdgcn_readfirstlane(limit);
     for (int n = 0; n < polls; ++n) {
         asm volatile("" ::: "memory");   // the words are read anew in every round
         a.load(m);
@@ -1188,7 +1193,7 @@ __global__ __launch_bounds__(kBlockRows) __attribute__((amdgpu_waves_per_eu(2)))
     extern __shared__ double s_u[];
     constexpr int R = kBlockRows, H = kHaloRegs, NW = R / 64;
     __shared__ double s_dot[3][NW], s_own[3][NW];
-    __shared__ int s_fail;
+    __shared__ int s_fail, s_polls;
     const int64_t b = rg_first(rg);
     if (b >= rg_end(rg)) return;   // the whole workgroup (the grid is a multiple of eight)
     const int nb = (int)bc.nb, tid = threadIdx.x, wave = tid >> 6;
@@ -1216,7 +1221,10 @@ __global__ __launch_bounds__(kBlockRows) __attribute__((amdgpu_waves_per_eu(2)))
             hw[k] = V[h[k]].W;
         }
     }
-    if (tid == 0) s_fail = 0;
+    if (tid == 0) {
+        s_fail = 0;
+        s_polls = polls;
+    }
     double g = wave_total(t[0]), d = wave_total(t[1]), rr = wave_total(t[2]);
     const double rr0 = rr;
     double gam_old = 0.0, alpha_old = 0.0;
@@ -1264,7 +1272,7 @@ __global__ __launch_bounds__(kBlockRows) __attribute__((amdgpu_waves_per_eu(2)))
         for (int j = 0; j < 3; ++j) pin.expect(j, p_box(buf, blockIdx.x % kSolveCopies, min(tid, nb - 1)) + 16 * j, tid < nb);
 #pragma unroll
         for (int k = 0; k < H; ++k) win.expect(k, w_box(buf, k * R < bc.stride ? h[k] : 0), k * R + tid < cnt);
-        wait_boxes(mail, pin, win, tag, nb, polls, &s_fail);
+        wait_boxes(mail, pin, win, tag, nb, &s_polls, &s_fail);
 #pragma unroll
         for (int j = 0; j < 3; ++j) v[j] = pin.value(j);
 #pragma unroll
@@ -1359,7 +1367,7 @@ __global__ __launch_bounds__(kBlockRows) __attribute__((amdgpu_waves_per_eu(2)))
     static_assert(32 * kSolveAggs == R && aux_far_log(0) == 9, "a thread per component and slice of an aggregate");
     __shared__ double s_dot[2][NW], s_own[2][NW], s_far[kB][kSolveAggs][4];
     __shared__ S s_sum[2][4][4];
-    __shared__ int s_fail, s_fail_y;   // of the waits before a sum over the workgroups, and of the one for Y
+    __shared__ int s_polls, s_fail, s_fail_y;   // of the waits before a sum over the workgroups, and of the one for Y
     // one after the other in the same memory: p of the blocks and their halos, the slices'
     // records (r', th r') with a zero record, the blocks' nodal values with a zero record
     S* s_p = reinterpret_cast<S*>(lds_solve);
@@ -1487,7 +1495,10 @@ __global__ __launch_bounds__(kBlockRows) __attribute__((amdgpu_waves_per_eu(2)))
             d64[b] = reinterpret_cast<const S*>(pick<S>(g.scale64, g.scale64_f))[4 * (int64_t)sl + comp];
         }
     }
-    if (tid == 0) s_fail = s_fail_y = 0;
+    if (tid == 0) {
+        s_fail = s_fail_y = 0;
+        s_polls = polls;
+    }
     double gm = wave_total(t[0]), rr = wave_total(t[1]);
     const double rr0 = rr;
     double gam_old = 0.0;
@@ -1574,7 +1585,7 @@ __global__ __launch_bounds__(kBlockRows) __attribute__((amdgpu_waves_per_eu(2)))
                 }
                 qin.expect(k, q_box + W * (unsigned)ek, need);
             }
-            wait_boxes(mail, pin, qin, tag, nw, polls, &s_fail);
+            wait_boxes(mail, pin, qin, tag, nw, &s_polls, &s_fail);
             v[0] = pin.value(0);
             if (!sum(v, 1)) break;
             const double alpha = gm / v[0];
@@ -1668,7 +1679,7 @@ __global__ __launch_bounds__(kBlockRows) __attribute__((amdgpu_waves_per_eu(2)))
                 const bool need = f_slice[b] < L.n_slices;
                 fin.expect(b, f_box + W * (4 * (unsigned)(need ? f_slice[b] : 0) + comp), need);
             }
-            wait_boxes(mail, yin, fin, tag, nw, polls, &s_fail_y);
+            wait_boxes(mail, yin, fin, tag, nw, &s_polls, &s_fail_y);
             if (far) {
 #pragma unroll
                 for (int b = 0; b < kB; ++b) {
@@ -1720,7 +1731,7 @@ __global__ __launch_bounds__(kBlockRows) __attribute__((amdgpu_waves_per_eu(2)))
             for (int k = 0; k < kB * H; ++k)
                 zin.expect(k, z_box + W * (unsigned)((k % H) * R < bc.stride ? h[k / H][k % H] : 0),
                            (k % H) * R + tid < cnt[k / H]);
-            wait_boxes(mail, pin, zin, tag, nw, polls, &s_fail);
+            wait_boxes(mail, pin, zin, tag, nw, &s_polls, &s_fail);
             v[0] = pin.value(0);
             v[1] = pin.value(1);
             if (!sum(v, 2)) break;
