@@ -250,8 +250,9 @@ int fepic_set_solve_precision(fepic_ctx* ctx, int solve_precision);
  * made by a launch per iteration and kernel, as on larger meshes; so are the next solves, one,
  * or twice as many as the last time if none succeeded since (up to 1024), before another is
  * tried in one launch.  0 gives up at the first wait; -1 makes no one-launch solves
- * (FEPIC_E_ARG below that). */
+ * (FEPIC_E_ARG below that, and above FEPIC_SOLVE_POLLS_MAX, about ten seconds of a wait). */
 #define FEPIC_SOLVE_POLLS (1 << 17)
+#define FEPIC_SOLVE_POLLS_MAX (1 << 24)
 int fepic_set_solve_polls(fepic_ctx* ctx, int polls);
 /* How the last solve (with FEPIC_SOLVE_MIXED: its last pass) was made, FEPIC_SOLVE_FORM_*,
  * and the one-launch solves given up so far; either may be NULL. */

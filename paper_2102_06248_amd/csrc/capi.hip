@@ -1897,7 +1897,8 @@ int fepic_set_solve_precision(fepic_ctx* c, int sp) {
 
 int fepic_set_solve_polls(fepic_ctx* c, int polls) {
     if (!c) return FEPIC_E_ARG;
-    if (polls < -1) return fail(c, FEPIC_E_ARG, "polls must be -1 or more");
+    if (polls < -1 || polls > FEPIC_SOLVE_POLLS_MAX)
+        return fail(c, FEPIC_E_ARG, "polls must be -1 to FEPIC_SOLVE_POLLS_MAX");
     c->solve_polls = polls;
     return FEPIC_OK;
 }

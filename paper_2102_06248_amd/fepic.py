@@ -23,7 +23,7 @@ FEPIC_PC_JACOBI, FEPIC_PC_AUX = 0, 1
 FEPIC_WALK_AUTO, FEPIC_WALK_QUEUE, FEPIC_WALK_FUSED = 0, 1, 2
 FEPIC_SORT_AUTO = -1
 FEPIC_SOLVE_FP64, FEPIC_SOLVE_MIXED = 0, 1
-FEPIC_SOLVE_POLLS = 1 << 17
+FEPIC_SOLVE_POLLS, FEPIC_SOLVE_POLLS_MAX = 1 << 17, 1 << 24
 FEPIC_SOLVE_FORM_NONE, FEPIC_SOLVE_FORM_KERNELS, FEPIC_SOLVE_FORM_ONE_LAUNCH = -1, 0, 1
 FEPIC_PUSHER_BORIS, FEPIC_PUSHER_AB = 0, 1
 FEPIC_FIELD_WAVE, FEPIC_FIELD_NM_MFEM, FEPIC_FIELD_BD_MFEM = 0, 1, 2

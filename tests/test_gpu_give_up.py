@@ -51,8 +51,9 @@ def test_one_launch_switched_off(F):
     with F.Simulation(xyz, tets, device=0, cg_tol=TOL, **options(F, "jacobi")) as L:
         M, S, d, dt = operators(F, L)
         start(F, L, d)
-        with pytest.raises(F.FepicError):
-            F.fepic_set_solve_polls(L.ctx, -2)
+        for bad in (-2, F.FEPIC_SOLVE_POLLS_MAX + 1):
+            with pytest.raises(F.FepicError):
+                F.fepic_set_solve_polls(L.ctx, bad)
         for polls, form in ((-1, F.FEPIC_SOLVE_FORM_KERNELS), (F.FEPIC_SOLVE_POLLS, F.FEPIC_SOLVE_FORM_ONE_LAUNCH)):
             F.fepic_set_solve_polls(L.ctx, polls)
             assert check_step(F, L, M, S, dt) > 0
