@@ -10,8 +10,9 @@
 // walks the row blocks of the b % 8-th eighth of the rows, giving each XCD's L2 one
 // contiguous stretch of rows and of the vector entries their columns mostly touch.
 //
-// Global dot products never communicate between workgroups inside a kernel: the
-// once-per-solve reductions write one partial per workgroup that the next kernel sums
+// But for the one-launch solves (k_cg_solve, k_pcg_solve, which pass values between running
+// workgroups as tagged words), global dot products never communicate between workgroups
+// inside a kernel: the once-per-solve reductions write one partial per workgroup that the next kernel sums
 // (every workgroup, redundantly, in the same fixed order, so all reach the same bits);
 // the iteration dots go through FP64-atomic slots that the next kernel sums the same way.
 // Kernel boundaries give the visibility; no device-scope fences are issued.
